@@ -32,6 +32,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "rt3d.h"
 
@@ -47,6 +48,10 @@ constexpr size_t kLdsMajorantBytes = 64 * 1024;  // automatic LDS staging limit 
 // (hi(M1 c2) ^ c1 ^ k0, lo(M1 c2), hi(M0 c0) ^ c3 ^ k1, lo(M0 c0)); the key
 // is bumped by the Weyl constants between rounds.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
@@ -54,13 +59,19 @@ __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1) {
             k0 += 0x9E3779B9u;
             k1 += 0xBB67AE85u;
         }
-        const uint32_t lo0 = 0xD2511F53u * c.x;
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c.x);
-        const uint32_t lo1 = 0xCD9E8D57u * c.z;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c.z);
-        c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
+        // both halves of a product from one v_mad_u64_u32 (5.4 cycles a wave
+        // against 9.6 for v_mul_lo_u32 + v_mul_hi_u32), three-way xors as one
+        // v_bitop3_b32
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c.x;
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c.z;
+        c = make_uint4(xor3((uint32_t)(p1 >> 32), c.y, k0), (uint32_t)p1, xor3((uint32_t)(p0 >> 32), c.w, k1),
+                       (uint32_t)p0);
     }
     return c;
+}
+
+__device__ __forceinline__ uint4 philox(uint4 c, unsigned long long key) {
+    return philox(c, (uint32_t)key, (uint32_t)(key >> 32));
 }
 
 // 24-bit uniforms: [0,1) for comparisons and positions, (0,1] for logs.
@@ -184,14 +195,60 @@ __device__ __forceinline__ void turn(float& x, float& y, float& z, float mu, flo
 // which random numbers, does not depend on the order, and neither do the
 // integer tallies.
 // ---------------------------------------------------------------------------
+// Division by a launch constant: quotients of 32-bit values below 2^31 as one
+// high product and a shift, of 64-bit values below 2^33 by the reciprocal in
+// FP64 and a correction by one.  A 64-bit division by a run-time value is
+// about 150 instructions, a 32-bit one 22; a photon's emission has six of
+// them.
+struct FastDiv {
+    uint32_t d, mul, shift;
+};
+
+inline FastDiv fast_div(uint32_t d) {
+    FastDiv f;
+    f.d = d;
+    f.shift = 0;
+    while (((uint64_t)1 << f.shift) < d) ++f.shift;
+    f.mul = (uint32_t)(((uint64_t)1 << (31 + f.shift)) / d + 1);
+    return f;
+}
+
+__device__ __host__ __forceinline__ uint32_t quotient(uint32_t n, const FastDiv& f) {
+    return (uint32_t)(((uint64_t)(n << 1) * f.mul) >> 32) >> f.shift;
+}
+
+struct FastDiv33 {
+    unsigned long long d;
+    double inv;
+};
+
+inline FastDiv33 fast_div33(unsigned long long d) { return FastDiv33{d, 1.0 / (double)d}; }
+
+__device__ __host__ __forceinline__ unsigned long long quotient(unsigned long long n, const FastDiv33& f,
+                                                                unsigned long long* rem) {
+    unsigned long long q = (unsigned long long)((double)n * f.inv);
+    long long r = (long long)(n - q * f.d);
+    if (r < 0) {
+        --q;
+        r += (long long)f.d;
+    } else if (r >= (long long)f.d) {
+        ++q;
+        r -= (long long)f.d;
+    }
+    *rem = (unsigned long long)r;
+    return q;
+}
+
 struct Schedule {
     const unsigned long long* pass_first;  // [ngp + 1] prefix sums of P_n
     const unsigned long long* rem_first;   // [ngp + 1] prefix sums of count_n mod ncol
     const unsigned long long* col_offset;  // [ngp] o_n
     unsigned long long full_slots;         // ncol * sum P_n
-    unsigned long long tile_slots;         // tile_cols * sum P_n
+    FastDiv33 tile_slots;                  // tile_cols * sum P_n
+    FastDiv33 tile_cols;
     unsigned long long photon_offset;
-    uint32_t ncol, nx, tile_x, tile_y, tile_cols, ntx;
+    FastDiv nx, ntx, tile_x;
+    uint32_t ncol, tile_y;
     uint32_t po_mod;  // photon_offset mod ncol
     int ngp;
 };
@@ -199,7 +256,7 @@ struct Schedule {
 struct Slot {
     int gp;
     unsigned long long id;
-    uint32_t col;
+    uint32_t col, i, j;  // entry column, col = j nx + i
 };
 
 // Prefix sums of the full passes and of the photons left over per g-point.
@@ -232,15 +289,17 @@ __host__ __device__ inline Slot decode_slot(const Schedule& S, unsigned long lon
     Slot r;
     unsigned long long k;
     if (s < S.full_slots) {
-        const unsigned long long t = s / S.tile_slots;
-        const unsigned long long rem = s - t * S.tile_slots;
-        const unsigned long long f = rem / S.tile_cols;  // full pass over all g-points
-        const uint32_t u = (uint32_t)(rem - f * S.tile_cols);
+        unsigned long long rem, ru;
+        const uint32_t t = (uint32_t)quotient(s, S.tile_slots, &rem);
+        const unsigned long long f = quotient(rem, S.tile_cols, &ru);  // full pass over all g-points
+        const uint32_t u = (uint32_t)ru;
         r.gp = range_of(S.pass_first, S.ngp, f);
         const unsigned long long m = f - S.pass_first[r.gp];
-        const uint32_t tx = (uint32_t)t % S.ntx, ty = (uint32_t)t / S.ntx;
-        const uint32_t uy = u / S.tile_x, ux = u - uy * S.tile_x;
-        r.col = (ty * S.tile_y + uy) * S.nx + tx * S.tile_x + ux;
+        const uint32_t ty = quotient(t, S.ntx), tx = t - ty * S.ntx.d;
+        const uint32_t uy = quotient(u, S.tile_x), ux = u - uy * S.tile_x.d;
+        r.i = tx * S.tile_x.d + ux;
+        r.j = ty * S.tile_y + uy;
+        r.col = r.j * S.nx.d + r.i;
         uint32_t o = (uint32_t)S.col_offset[r.gp] + S.po_mod;
         if (o >= S.ncol) o -= S.ncol;
         const uint32_t j = r.col >= o ? r.col - o : r.col + (S.ncol - o);
@@ -254,6 +313,8 @@ __host__ __device__ inline Slot decode_slot(const Schedule& S, unsigned long lon
         if (o >= S.ncol) o -= S.ncol;
         r.col = j + o;
         if (r.col >= S.ncol) r.col -= S.ncol;
+        r.j = quotient(r.col, S.nx);
+        r.i = r.col - r.j * S.nx.d;
     }
     r.id = S.photon_offset + k;
     return r;
@@ -286,8 +347,8 @@ struct TraceParams {
     uint32_t pool;   // photon ids a wave takes from the queue at a time
     uint32_t refill; // a wave refills once this many of its lanes are idle
     int merge;       // merge consecutive deposits of a lane into one cell
-    int wave_agg;    // wave-aggregated tally atomics (same address, same instruction)
     int nx, ny, nz, bx, by, bz, mx, my, mz;
+    FastDiv div_bx, div_by;
     float dx, dy, dz, inv_dx, inv_dy, inv_dz;
     float cx, cy, cz;  // acceleration-grid cell size in metres
     float H;
@@ -305,16 +366,13 @@ enum { L_IN, L_TOA, L_ATM_DIR, L_ATM_DIF, L_SFC, L_RR_GAIN, L_RR_LOSS, L_LOST, L
 enum { S_PHOT, S_COLL, S_NULL, S_GAS, S_CLOUD, S_SFC, S_ESC, S_RR_KILL, S_RR_SURV,
        S_CROSS, S_ABSORBED, S_CAPPED, S_N };
 
-__device__ __forceinline__ void lds_add(unsigned long long* a, unsigned long long v) {
-    if (v) atomicAdd(a, v);
-}
-
-// Tally update.  agg = 0: one atomic per lane.  agg = 1 (wave-aggregated):
+// Tally update.  kAgg false: one atomic per lane.  kAgg true (wave-aggregated):
 // the lanes that update the same address in this instruction add their
 // values first and one of them issues the atomic; the loop visits each
 // distinct address of the active lanes once (scalar, wave-uniform).
-__device__ __forceinline__ void tally_add(unsigned long long* p, unsigned long long v, int agg) {
-    if (!agg) {
+template <bool kAgg>
+__device__ __forceinline__ void tally_add(unsigned long long* p, unsigned long long v) {
+    if (!kAgg) {
         atomicAdd(p, v);
         return;
     }
@@ -340,8 +398,6 @@ __device__ __forceinline__ uint64_t lane_mask_lt() {
     const uint32_t lane = __lane_id();
     return lane ? (~0ull >> (64 - lane)) : 0ull;
 }
-
-enum Outcome { kCollision = 0, kSurface = 1, kEscape = 2, kCapped = 3, kWalking = 4 };
 
 // Local optical properties at a tentative collision: extinction, absorption,
 // scattering and cloud extinction coefficients, cloud asymmetry.
@@ -373,15 +429,56 @@ __device__ __forceinline__ Local local_props(const TraceParams& P, int gp, uint3
     return L;
 }
 
+// a * b rounded to FP32 on its own.  The library is built with FP contraction,
+// and the backend then fuses any product with a following addition into one
+// FMA; the tallies are integers that depend on every rounding of a photon's
+// path, so a product that has to be rounded by itself is written this way: the
+// empty asm hides where its operand comes from.  (Not a multiplication in asm:
+// the compiler knows no hazards there, and one that follows v_rcp_f32 at once
+// reads the register before it is written.)
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+    float r = a * b;
+    asm("" : "+v"(r));
+    return r;
+}
+
+// State of a lane between loop iterations.  kLive lanes track a photon,
+// kDead lanes wait for a new one, every other state is a rare event that
+// waits until enough lanes of the wave have one (service block below).
+enum LaneState { kLive, kDead, kAtSurface, kEscaped, kCappedOut, kRoulette, kAbsorbedOut, kEnded };
+
+// Event counters of a workgroup: kCntSlots copies of each in LDS, lane l
+// updates copy l % kCntSlots.  A counter in one LDS word makes the compiler
+// emit a serial loop over the lanes of the wave (one address, different
+// values) at every update; copies at lane-dependent addresses are one
+// ds_add_u64 each.
+enum Counter { C_TOA, C_SFC_W, C_GAIN, C_LOSS, C_LOST, C_COLL, C_GAS, C_CLOUD, C_SFC, C_ESC, C_KILL, C_SURV,
+               C_ABSORBED, C_CAPPED, C_PASSES, C_ABS_COLL, C_N };
+constexpr int kCntSlots = 32;
+
+// Lanes with a pending rare event (surface, escape, roulette, photon ended)
+// before the wave handles them.  One such event comes up per loop iteration
+// and wave on average, for one lane; handled at once it costs the wave the
+// whole code path for that lane.
+constexpr uint32_t kServiceLanes = 8;
+
 // One photon per lane.  Each loop iteration of
-// a lane: (re)fill the lane with a new photon if it has none, draw the free
+// a lane: handle its pending rare event or (re)fill the lane with a new
+// photon, once enough lanes of the wave need that, draw the free
 // path's four random words, walk acceleration-grid cells (at most
 // P.max_walk crossings per iteration) until the tentative collision /
-// surface / top, then handle that event.  kLds: majorant grid of the single
+// surface / top, then handle a collision (the other events wait).  kLds:
+// majorant grid of the single
 // g-point staged in LDS.  kFactored: shared cloud field + per-g-point gas
-// profiles (several g-points in one launch).
-// Launch shape: the single-g-point kernel runs 1024-lane workgroups at 8
-// waves per SIMD (two workgroups per CU share the 160 KB LDS); the factored
+// profiles (several g-points in one launch).  kAgg: wave-aggregated tally
+// atomics.
+// Rare events deferred, counters at lane-dependent LDS addresses, no scalar
+// spills: 4.24e10 vector instructions on the 256x256x128 field with 2^26
+// photons against 6.27e10, 98.7 against 100.1 ms (bound by the tally atomics
+// there); 32x32x64 cells with 2^14 photons 1.54 against 2.29 ms; 128^3 cells,
+// 112 g-points, 4.2e6 photons 6.5 against 7.0 ms.
+// Launch shape: the single-g-point kernel runs workgroups of up to 1024 lanes
+// at 8 waves per SIMD (two workgroups per CU share the 160 KB LDS); the factored
 // kernel needs more registers and runs 256-lane workgroups at 6 waves.
 template <bool kFactored>
 struct Shape_ {
@@ -389,24 +486,34 @@ struct Shape_ {
     static constexpr int waves = kFactored ? 6 : 8;
 };
 
-template <bool kLds, bool kFactored>
+// The kernel's parameters for code that runs for a small part of the loop
+// iterations.  The pointer is opaque to the compiler, so what is read through
+// it is loaded there; read as P.x it is loaded ahead of the loop, and the
+// scalar registers that this takes are spilled to vector lanes, a
+// v_readlane at every use (629 of them in the kernel before).  The parameters are the kernel's only
+// argument, at the start of its argument segment.
+__device__ __forceinline__ const TraceParams* cold_params() {
+    auto q = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(q));
+    return (const TraceParams*)q;
+}
+
+template <bool kLds, bool kFactored, bool kAgg>
 __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     __attribute__((amdgpu_waves_per_eu(Shape_<kFactored>::waves))) trace_kernel(const TraceParams P) {
     extern __shared__ float s_maj[];
-    __shared__ unsigned long long s_ledger[L_N];
-    __shared__ unsigned long long s_stats[S_N];
-    __shared__ unsigned long long s_passes, s_absorbed_coll;
+    __shared__ unsigned long long s_cnt[C_N][kCntSlots];
 
-    if (threadIdx.x < L_N) s_ledger[threadIdx.x] = 0;
-    if (threadIdx.x < S_N) s_stats[threadIdx.x] = 0;
-    if (threadIdx.x == 0) s_passes = s_absorbed_coll = 0;
+    for (int i = threadIdx.x; i < C_N * kCntSlots; i += blockDim.x) s_cnt[i / kCntSlots][i % kCntSlots] = 0;
     if (kLds) {
         for (int i = threadIdx.x; i < P.nmaj; i += blockDim.x) s_maj[i] = P.majorant[i];
     }
     __syncthreads();
+    const int slot = threadIdx.x % kCntSlots;
+    auto count = [&](int c, unsigned long long v) { atomicAdd(&s_cnt[c][slot], v); };
 
     // ---- per-lane photon state
-    bool alive = false;
+    int st = kDead;
     unsigned long long id = 0;
     int gp = 0;
     float px = 0.f, py = 0.f, pz = 0.f, ux = 0.f, uy = 0.f, uz = -1.f;
@@ -434,50 +541,112 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     auto flush_deposit = [&]() {
         if (pend_amt) {
             const uint32_t cell = pend_key & 0x7fffffffu;
-            tally_add(pend_key & 0x80000000u ? &P.abs_dif[cell] : &P.abs_dir[cell], pend_amt, P.wave_agg);
+            tally_add<kAgg>(pend_key & 0x80000000u ? &P.abs_dif[cell] : &P.abs_dir[cell], pend_amt);
         }
         pend_key = kNoCell;
         pend_amt = 0;
     };
     auto flush_scat = [&]() {
-        lds_add(&s_stats[S_GAS], n_scat & 0xffffu);
-        lds_add(&s_stats[S_CLOUD], n_scat >> 16);
+        count(C_GAS, n_scat & 0xffffu);
+        count(C_CLOUD, n_scat >> 16);
         n_scat = 0;
     };
-    auto finish_photon = [&]() {
-        alive = false;
-        lds_add(&s_stats[S_COLL], n_coll);
-        lds_add(&s_passes, iters);
-        flush_scat();
-        n_coll = 0;
-    };
-    auto key0 = [&]() { return (uint32_t)(P.seed + (unsigned long long)(kFactored ? gp : 0)); };
-    auto key1 = [&]() { return (uint32_t)((P.seed + (unsigned long long)(kFactored ? gp : 0)) >> 32); };
-    // Russian roulette (sec. 2.3) with the current free path's counter
-    // (id, step, 1): survive with probability w, then weight one.
-    auto roulette = [&]() {
-        if (w >= P.rr_below) return;
-        const uint4 q = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), step, 1u), key0(), key1());
-        if ((q.x >> 1) < w) {
-            lds_add(&s_ledger[L_RR_GAIN], kWOne - w);
-            atomicAdd(&s_stats[S_RR_SURV], 1ull);
-            w = kWOne;
-        } else {
-            lds_add(&s_ledger[L_RR_LOSS], w);
-            atomicAdd(&s_stats[S_RR_KILL], 1ull);
-            finish_photon();
-        }
+    // the g-point's Philox key (opaque in each use: the round keys are then
+    // formed where they are needed, see cold_params)
+    auto key = [&]() {
+        unsigned long long q = P.seed;
+        asm volatile("" : "+s"(q));
+        return q + (unsigned long long)(kFactored ? gp : 0);
     };
     auto cell_ix = [&](float v, float inv, int b, int n) {
         return min(max((int)floorf(v * inv), b * n), b * n + n - 1);
     };
 
     for (;;) {
+        // ---- rare events, once enough lanes wait with one or none is live
+        const uint64_t waiting = __ballot(st > kDead);
+        if (waiting && ((uint32_t)__popcll(waiting) >= kServiceLanes || !__ballot(st == kLive))) {
+            const TraceParams& Q = *cold_params();
+            if (st == kAtSurface) {
+                // ---- Lambertian surface (sec. 2.3)
+                const int i = cell_ix(px, Q.inv_dx, bi, Q.bx);
+                const int j = cell_ix(py, Q.inv_dy, bj, Q.by);
+                const int c2 = j * Q.nx + i;
+                tally_add<kAgg>(direct ? &Q.sfc_dir[c2] : &Q.sfc_dif[c2], (unsigned long long)w);
+                const uint32_t wn = min(w, (uint32_t)rintf(Q.albedo[c2] * (float)w));
+                if (w != wn) {
+                    tally_add<kAgg>(&Q.sfc_abs[c2], (unsigned long long)(w - wn));
+                    count(C_SFC_W, w - wn);
+                }
+                count(C_SFC, 1);
+                w = wn;
+                if (w == 0) {
+                    count(C_ABSORBED, 1);
+                    st = kEnded;
+                } else {
+                    // the free path's random words again (not kept while waiting)
+                    const uint4 r = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), step, 0u), key());
+                    const float mu = sqrtf(u01_open(r.z));
+                    float sp, cp;
+                    __sincosf(6.28318530717958647f * u01(r.w), &sp, &cp);
+                    const float sn = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
+                    ux = sn * cp;
+                    uy = sn * sp;
+                    uz = mu;
+                    direct = false;
+                    if (w < Q.rr_below) {
+                        st = kRoulette;
+                    } else {
+                        ++step;
+                        st = kLive;
+                    }
+                }
+            }
+            if (st == kRoulette) {
+                // Russian roulette (sec. 2.3) with the free path's counter
+                // (id, step, 1): survive with probability w, then weight one
+                const uint4 q = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), step, 1u), key());
+                if ((q.x >> 1) < w) {
+                    count(C_GAIN, kWOne - w);
+                    count(C_SURV, 1);
+                    w = kWOne;
+                    ++step;
+                    st = kLive;
+                } else {
+                    count(C_LOSS, w);
+                    count(C_KILL, 1);
+                    st = kEnded;
+                }
+            }
+            if (st == kEscaped) {
+                // ---- leaves through the top of the domain
+                const int i = cell_ix(px, Q.inv_dx, bi, Q.bx);
+                const int j = cell_ix(py, Q.inv_dy, bj, Q.by);
+                tally_add<kAgg>(&Q.toa_up[j * Q.nx + i], (unsigned long long)w);
+                count(C_TOA, w);
+                count(C_ESC, 1);
+            }
+            if (st == kCappedOut) {
+                count(C_LOST, w);
+                count(C_CAPPED, 1);
+            }
+            if (st == kAbsorbedOut) {
+                count(C_ABSORBED, 1);
+                count(C_ABS_COLL, 1);
+            }
+            if (st > kDead) {  // the photon has ended
+                st = kDead;
+                count(C_COLL, n_coll);
+                count(C_PASSES, iters);
+                flush_scat();
+                n_coll = 0;
+            }
+        }
         // ---- refill finished lanes from the wave's pool of photon ids, once
         // enough of them are idle (the emission code then runs for many
         // lanes at once instead of for one or two) or none is alive
-        const uint64_t dead = __ballot(!alive);
-        if (dead && !drained && ((uint32_t)__popcll(dead) >= P.refill || !__ballot(alive))) {
+        const uint64_t dead = __ballot(st == kDead);
+        if (dead && !drained && ((uint32_t)__popcll(dead) >= P.refill || !__ballot(st != kDead))) {
             const uint32_t need = (uint32_t)__popcll(dead);
             const int leader = __ffsll((unsigned long long)dead) - 1;
             const unsigned long long avail = pool_end - pool_next;
@@ -489,61 +658,58 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
                 base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32) |
                        (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base);
             }
-            if (!alive) {
+            if (st == kDead) {
                 const uint32_t rank = (uint32_t)__popcll(dead & lane_mask_lt());
                 const unsigned long long local = rank < avail ? pool_next + rank : base + (rank - avail);
                 if (local < P.photons) {
                     // queue slot -> g-point, photon id and entry column
-                    const Slot sl = decode_slot(P.sched, local);
+                    const TraceParams& Q = *cold_params();
+                    const Slot sl = decode_slot(Q.sched, local);
                     gp = kFactored ? sl.gp : 0;
                     id = sl.id;
-                    const uint32_t col = sl.col;
+                    const int ic = (int)sl.i, jc = (int)sl.j;
                     // ---- emission at the top of the domain (sec. 2.3)
-                    const int ic = (int)(col % (unsigned)P.nx);
-                    const int jc = (int)(col / (unsigned)P.nx);
                     const uint4 e = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), 0xffffffffu, 0u),
-                                           key0(), key1());
+                                           key());
                     float fx = u01(e.x), fy = u01(e.y);
-                    if (P.sobol) {
+                    if (Q.sobol) {
                         // photon id is the (id div ncol)-th to enter its column
-                        const uint32_t pass = (uint32_t)(id / P.ncol);
-                        const uint4 sc = philox(make_uint4(col, 0u, 0xfffffffdu, 0u),
-                                                key0(), key1());
+                        const uint32_t pass = (uint32_t)(id / Q.ncol);
+                        const uint4 sc = philox(make_uint4(sl.col, 0u, 0xfffffffdu, 0u),
+                                                key());
                         fx = u01(owen_scramble<24>(__builtin_bitreverse32(pass), sc.x));
                         fy = u01(owen_scramble<24>(sobol_dim2(pass), sc.y));
                     }
-                    px = ((float)ic + fx) * P.dx;
-                    py = ((float)jc + fy) * P.dy;
-                    pz = P.H;
-                    const float fd = P.gp_diffuse ? P.gp_diffuse[gp] : P.diffuse_fraction;
+                    px = ((float)ic + fx) * Q.dx;
+                    py = ((float)jc + fy) * Q.dy;
+                    pz = Q.H;
+                    const float fd = Q.gp_diffuse ? Q.gp_diffuse[gp] : Q.diffuse_fraction;
                     if (u01(e.z) < fd) {
                         const uint4 q = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), 0xffffffffu, 1u),
-                                               key0(), key1());
+                                               key());
                         const float mu = sqrtf(u01_open(q.x));
                         float sp, cp;
                         __sincosf(6.28318530717958647f * u01(q.y), &sp, &cp);
-                        const float st = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
-                        ux = st * cp;
-                        uy = st * sp;
+                        const float sn = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
+                        ux = sn * cp;
+                        uy = sn * sp;
                         uz = -mu;
                         direct = false;
                     } else {
-                        ux = P.sun_x;
-                        uy = P.sun_y;
-                        uz = P.sun_z;
+                        ux = Q.sun_x;
+                        uy = Q.sun_y;
+                        uz = Q.sun_z;
                         direct = true;
                     }
-                    bi = ic / P.bx;
-                    bj = jc / P.by;
-                    bk = P.mz - 1;
+                    bi = (int)quotient((uint32_t)ic, Q.div_bx);
+                    bj = (int)quotient((uint32_t)jc, Q.div_by);
+                    bk = Q.mz - 1;
                     kmaj = __uint_as_float(kNoMajorant);
                     w = kWOne;
                     step = 0;
                     iters = 0;
                     tau = -1.f;
-                    alive = true;
-                    atomicAdd(&s_stats[S_PHOT], 1ull);
-                    lds_add(&s_ledger[L_IN], kWOne);
+                    st = kLive;
                 }
             }
             if (avail < need) {
@@ -556,197 +722,164 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
             // pool_next passes the photon count no valid id is left
             drained = pool_next >= P.photons;
         }
-        if (!__ballot(alive)) break;
-        if (!alive) continue;
+        if (!__ballot(st == kLive)) {
+            if (!__ballot(st > kDead) && drained) break;
+            continue;
+        }
+        if (st != kLive) continue;
 
         // ---- random words of this free path: tau, event, cos(theta), phi
-        const uint4 r = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), step, 0u), key0(), key1());
+        const uint4 r = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), step, 0u), key());
         if (tau < 0.f) tau = -__logf(u01_open(r.x));
         const int maj_base = kFactored ? gp * P.nmaj : 0;  // this g-point's majorant grid
 
         // ---- walk acceleration-grid cells until the path ends
-        int outcome;
-        float K;
+        const float rx = rcp(ux), ry = rcp(uy), rz = rcp(uz);
+        bool hit = false;
         for (int walked = 0;; ++walked) {
-            if (iters >= P.max_iters) { outcome = kCapped; break; }
-            if (walked >= P.max_walk) { outcome = kWalking; break; }
+            if (iters >= P.max_iters) { st = kCappedOut; break; }
+            if (walked >= P.max_walk) break;
             ++iters;
             // factored majorants carry the brick's "no cloud" flag in the sign bit
             if (__float_as_uint(kmaj) == kNoMajorant)
                 kmaj = kLds ? s_maj[(bk * P.my + bj) * P.mx + bi] : P.majorant[maj_base + (bk * P.my + bj) * P.mx + bi];
-            K = kmaj;
-            const float Km = fabsf(K);
-            const float x0 = (float)bi * P.cx, y0 = (float)bj * P.cy, z0 = (float)bk * P.cz;
-            float tx = INFINITY, ty = INFINITY, tz = INFINITY;
-            if (ux > 0.f) tx = (x0 + P.cx - px) * rcp(ux);
-            else if (ux < 0.f) tx = (x0 - px) * rcp(ux);
-            if (uy > 0.f) ty = (y0 + P.cy - py) * rcp(uy);
-            else if (uy < 0.f) ty = (y0 - py) * rcp(uy);
-            if (uz > 0.f) tz = (z0 + P.cz - pz) * rcp(uz);
-            else if (uz < 0.f) tz = (z0 - pz) * rcp(uz);
-            tx = fmaxf(tx, 0.f);
-            ty = fmaxf(ty, 0.f);
-            tz = fmaxf(tz, 0.f);
-            int axis = 0;
-            float s_exit = tx;
-            if (ty < s_exit) { s_exit = ty; axis = 1; }
-            if (tz < s_exit) { s_exit = tz; axis = 2; }
-            if (Km * s_exit >= tau) {
-                const float sc = tau * rcp(Km);
-                px += sc * ux;
-                py += sc * uy;
-                pz += sc * uz;
-                outcome = kCollision;
-                break;
-            }
-            tau -= Km * s_exit;
-            px += s_exit * ux;
-            py += s_exit * uy;
-            pz += s_exit * uz;
-            if (axis == 2) {
-                if (uz < 0.f) {
-                    if (bk == 0) { pz = 0.f; outcome = kSurface; break; }
-                    --bk;
-                    pz = (float)(bk + 1) * P.cz;
-                } else {
-                    if (bk == P.mz - 1) { outcome = kEscape; break; }
-                    ++bk;
-                    pz = (float)bk * P.cz;
+            const float Km = fabsf(kmaj);
+            // distance to the cell's face ahead in each direction
+            auto ahead = [](float p, float u, float ru, int b, float c) {
+                const float lo = mul_rounded((float)b, c);
+                const float face = u > 0.f ? lo + c : lo;
+                return fmaxf(u == 0.f ? INFINITY : (face - p) * ru, 0.f);
+            };
+            const float tx = ahead(px, ux, rx, bi, P.cx);
+            const float ty = ahead(py, uy, ry, bj, P.cy);
+            const float tz = ahead(pz, uz, rz, bk, P.cz);
+            const float txy = fminf(tx, ty);
+            const float s_exit = fminf(txy, tz);
+            const float depth = mul_rounded(Km, s_exit);
+            hit = depth >= tau;
+            const float go = hit ? tau * rcp(Km) : s_exit;
+            px = __builtin_fmaf(go, ux, px);
+            py = __builtin_fmaf(go, uy, py);
+            pz = __builtin_fmaf(go, uz, pz);
+            if (hit) break;
+            tau -= depth;
+            // into the next cell; ties go to x before y before z
+            if (tz < txy) {
+                const int up = uz < 0.f ? -1 : 1;
+                const int nk = bk + up;
+                pz = mul_rounded((float)(uz < 0.f ? bk : nk), P.cz);
+                if ((unsigned)nk >= (unsigned)P.mz) {
+                    st = uz < 0.f ? kAtSurface : kEscaped;
+                    break;
                 }
-            } else if (axis == 0) {
-                if (ux > 0.f) {
-                    bi = bi + 1 == P.mx ? 0 : bi + 1;
-                    px = (float)bi * P.cx;
-                } else {
-                    bi = bi == 0 ? P.mx - 1 : bi - 1;
-                    px = (float)(bi + 1) * P.cx;
-                }
+                bk = nk;
+            } else if (ty < tx) {
+                int nb = bj + (uy > 0.f ? 1 : -1);
+                nb = nb < 0 ? P.my - 1 : nb == P.my ? 0 : nb;
+                bj = nb;
+                py = mul_rounded((float)(uy > 0.f ? nb : nb + 1), P.cy);
             } else {
-                if (uy > 0.f) {
-                    bj = bj + 1 == P.my ? 0 : bj + 1;
-                    py = (float)bj * P.cy;
-                } else {
-                    bj = bj == 0 ? P.my - 1 : bj - 1;
-                    py = (float)(bj + 1) * P.cy;
-                }
+                int nb = bi + (ux > 0.f ? 1 : -1);
+                nb = nb < 0 ? P.mx - 1 : nb == P.mx ? 0 : nb;
+                bi = nb;
+                px = mul_rounded((float)(ux > 0.f ? nb : nb + 1), P.cx);
             }
             kmaj = __uint_as_float(kNoMajorant);  // crossed into another cell
         }
-        if (outcome == kWalking) continue;  // same free path next iteration
+        if (st == kLive && !hit) continue;  // same free path next iteration
         tau = -1.f;
+        if (!hit) continue;  // a rare event: waits for the service block
 
-        if (outcome == kCollision) {
-            // ---- tentative collision: local properties from the fine grid
-            const int i = cell_ix(px, P.inv_dx, bi, P.bx);
-            const int j = cell_ix(py, P.inv_dy, bj, P.by);
-            const int k = cell_ix(pz, P.inv_dz, bk, P.bz);
-            const uint32_t cell = (uint32_t)((k * P.ny + j) * P.nx + i);
-            bool clear = kFactored && __float_as_uint(K) >> 31;
-            if (kFactored && !clear && P.cell_mask) {
-                // a cloud-free fine cell of a cloudy acceleration cell holds a
-                // zero record too: its bit, from a small array that stays in
-                // the L2, spares the gather of a whole line of records
-                const uint32_t t = (uint32_t)(((k - bk * P.bz) * P.by + (j - bj * P.by)) * P.bx + (i - bi * P.bx));
-                const uint32_t b = (uint32_t)((bk * P.my + bj) * P.mx + bi);
-                clear = !((P.cell_mask[(size_t)b * P.mask_words + (t >> 5)] >> (t & 31)) & 1u);
-            }
-            K = fabsf(K);
-            const Local L = local_props<kFactored>(P, gp, cell, k, clear);
-            const float iK = rcp(K);
-            ++n_coll;
-            if (L.ka > 0.f) {
-                const uint32_t dep = min(w, (uint32_t)rintf((float)w * (L.ka * iK)));
-                const uint32_t key = cell | (direct ? 0u : 0x80000000u);
-                if (key != pend_key) {
-                    flush_deposit();
-                    pend_key = key;
-                }
-                pend_amt += dep;
-                if (!P.merge) flush_deposit();
-                w -= dep;
-                if (w == 0) {
-                    atomicAdd(&s_stats[S_ABSORBED], 1ull);
-                    atomicAdd(&s_absorbed_coll, 1ull);
-                    finish_photon();
-                    continue;
-                }
-            }
-            // scattering with probability k_sca / (K - k_abs), else null
-            const float den = K - L.ka;
-            const float ps = den > 0.f ? L.ks * rcp(den) : 0.f;
-            const float xi = u01(r.y);
-            if (xi < ps) {
-                float mu;
-                if (xi * L.ke < ps * L.kc) {
-                    mu = hg_cos(L.g, u01(r.z));
-                    n_scat += 0x10000u;
-                } else {
-                    mu = rayleigh_cos(u01(r.z));
-                    n_scat += 1u;
-                }
-                turn(ux, uy, uz, mu, u01(r.w));
-                direct = false;
-                if ((n_scat & 0x8000u) | (n_scat & 0x80000000u)) flush_scat();
-            }
-            roulette();
-            ++step;
-            continue;
+        // ---- tentative collision: local properties from the fine grid
+        const int i = cell_ix(px, P.inv_dx, bi, P.bx);
+        const int j = cell_ix(py, P.inv_dy, bj, P.by);
+        const int k = cell_ix(pz, P.inv_dz, bk, P.bz);
+        const uint32_t cell = (uint32_t)((k * P.ny + j) * P.nx + i);
+        bool clear = kFactored && __float_as_uint(kmaj) >> 31;
+        if (kFactored && !clear && P.cell_mask) {
+            // a cloud-free fine cell of a cloudy acceleration cell holds a
+            // zero record too: its bit, from a small array that stays in
+            // the L2, spares the gather of a whole line of records
+            const uint32_t t = (uint32_t)(((k - bk * P.bz) * P.by + (j - bj * P.by)) * P.bx + (i - bi * P.bx));
+            const uint32_t b = (uint32_t)((bk * P.my + bj) * P.mx + bi);
+            clear = !((P.cell_mask[(size_t)b * P.mask_words + (t >> 5)] >> (t & 31)) & 1u);
         }
-        if (outcome == kSurface) {
-            // ---- Lambertian surface (sec. 2.3)
-            const int i = cell_ix(px, P.inv_dx, bi, P.bx);
-            const int j = cell_ix(py, P.inv_dy, bj, P.by);
-            const int c2 = j * P.nx + i;
-            tally_add(direct ? &P.sfc_dir[c2] : &P.sfc_dif[c2], (unsigned long long)w, P.wave_agg);
-            const uint32_t wn = min(w, (uint32_t)rintf(P.albedo[c2] * (float)w));
-            if (w != wn) {
-                tally_add(&P.sfc_abs[c2], (unsigned long long)(w - wn), P.wave_agg);
-                lds_add(&s_ledger[L_SFC], w - wn);
+        const float K = fabsf(kmaj);
+        const Local L = local_props<kFactored>(P, gp, cell, k, clear);
+        const float iK = rcp(K);
+        ++n_coll;
+        if (L.ka > 0.f) {
+            const uint32_t dep = min(w, (uint32_t)rintf((float)w * (L.ka * iK)));
+            const uint32_t key = cell | (direct ? 0u : 0x80000000u);
+            if (key != pend_key) {
+                flush_deposit();
+                pend_key = key;
             }
-            atomicAdd(&s_stats[S_SFC], 1ull);
-            w = wn;
+            pend_amt += dep;
+            if (!P.merge) flush_deposit();
+            w -= dep;
             if (w == 0) {
-                atomicAdd(&s_stats[S_ABSORBED], 1ull);
-                finish_photon();
+                st = kAbsorbedOut;
                 continue;
             }
-            const float mu = sqrtf(u01_open(r.z));
-            float sp, cp;
-            __sincosf(6.28318530717958647f * u01(r.w), &sp, &cp);
-            const float st = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
-            ux = st * cp;
-            uy = st * sp;
-            uz = mu;
+        }
+        // scattering with probability k_sca / (K - k_abs), else null
+        const float den = K - L.ka;
+        const float ps = den > 0.f ? L.ks * rcp(den) : 0.f;
+        const float xi = u01(r.y);
+        if (xi < ps) {
+            float mu;
+            if (xi * L.ke < ps * L.kc) {
+                mu = hg_cos(L.g, u01(r.z));
+                n_scat += 0x10000u;
+            } else {
+                mu = rayleigh_cos(u01(r.z));
+                n_scat += 1u;
+            }
+            turn(ux, uy, uz, mu, u01(r.w));
             direct = false;
-            roulette();
-            ++step;
-            continue;
+            if ((n_scat & 0x8000u) | (n_scat & 0x80000000u)) flush_scat();
         }
-        if (outcome == kEscape) {
-            // ---- leaves through the top of the domain
-            const int i = cell_ix(px, P.inv_dx, bi, P.bx);
-            const int j = cell_ix(py, P.inv_dy, bj, P.by);
-            tally_add(&P.toa_up[j * P.nx + i], (unsigned long long)w, P.wave_agg);
-            lds_add(&s_ledger[L_TOA], w);
-            atomicAdd(&s_stats[S_ESC], 1ull);
-            finish_photon();
-            continue;
-        }
-        // iteration cap reached
-        lds_add(&s_ledger[L_LOST], w);
-        atomicAdd(&s_stats[S_CAPPED], 1ull);
-        finish_photon();
+        if (w < P.rr_below) st = kRoulette;
+        else ++step;
     }
 
     flush_deposit();
     __syncthreads();
-    if (threadIdx.x == 0) {
-        s_stats[S_CROSS] = s_passes - s_stats[S_COLL] - s_stats[S_SFC] - s_stats[S_ESC] - s_stats[S_CAPPED];
-        s_stats[S_NULL] = s_stats[S_COLL] - s_stats[S_GAS] - s_stats[S_CLOUD] - s_absorbed_coll;
+    const TraceParams& Q = *cold_params();
+    // sums of the counter copies, then the ledger and stats entries
+    __shared__ unsigned long long s_sum[C_N];
+    if (threadIdx.x < C_N) {
+        unsigned long long v = 0;
+        for (int q = 0; q < kCntSlots; ++q) v += s_cnt[threadIdx.x][q];
+        s_sum[threadIdx.x] = v;
     }
     __syncthreads();
-    if (threadIdx.x < L_N && s_ledger[threadIdx.x]) atomicAdd(&P.ledger[threadIdx.x], s_ledger[threadIdx.x]);
-    if (threadIdx.x < S_N && s_stats[threadIdx.x]) atomicAdd(&P.stats[threadIdx.x], s_stats[threadIdx.x]);
+    if (threadIdx.x == 0) {
+        auto led = [&](int e, unsigned long long v) { if (v) atomicAdd(&Q.ledger[e], v); };
+        auto sta = [&](int e, unsigned long long v) { if (v) atomicAdd(&Q.stats[e], v); };
+        if (blockIdx.x == 0) {  // every queue slot is traced, each with weight one
+            led(L_IN, Q.photons * kWOne);
+            sta(S_PHOT, Q.photons);
+        }
+        led(L_TOA, s_sum[C_TOA]);
+        led(L_SFC, s_sum[C_SFC_W]);
+        led(L_RR_GAIN, s_sum[C_GAIN]);
+        led(L_RR_LOSS, s_sum[C_LOSS]);
+        led(L_LOST, s_sum[C_LOST]);
+        const unsigned long long coll = s_sum[C_COLL], gas = s_sum[C_GAS], cloud = s_sum[C_CLOUD];
+        sta(S_COLL, coll);
+        sta(S_NULL, coll - gas - cloud - s_sum[C_ABS_COLL]);
+        sta(S_GAS, gas);
+        sta(S_CLOUD, cloud);
+        sta(S_SFC, s_sum[C_SFC]);
+        sta(S_ESC, s_sum[C_ESC]);
+        sta(S_RR_KILL, s_sum[C_KILL]);
+        sta(S_RR_SURV, s_sum[C_SURV]);
+        sta(S_CROSS, s_sum[C_PASSES] - coll - s_sum[C_SFC] - s_sum[C_ESC] - s_sum[C_CAPPED]);
+        sta(S_ABSORBED, s_sum[C_ABSORBED]);
+        sta(S_CAPPED, s_sum[C_CAPPED]);
+    }
 }
 
 // Heating entries of the energy ledger: ledger[ATM_DIR] = sum(abs_dir),
@@ -1187,12 +1320,16 @@ void schedule_of(const Shape& s, int ngp, const uint64_t* photons, const rt3d_op
     S->col_offset = col_offset;
     S->ngp = ngp;
     S->ncol = (uint32_t)s.ncol;
-    S->nx = (uint32_t)s.nx;
-    tile_shape(s, o, &S->tile_x, &S->tile_y);
-    S->tile_cols = S->tile_x * S->tile_y;
-    S->ntx = (uint32_t)s.nx / S->tile_x;
+    S->nx = fast_div((uint32_t)s.nx);
+    uint32_t tx, ty;
+    tile_shape(s, o, &tx, &ty);
+    S->tile_x = fast_div(tx);
+    S->tile_y = ty;
+    S->ntx = fast_div((uint32_t)s.nx / tx);
     S->full_slots = passes * s.ncol;
-    S->tile_slots = passes * S->tile_cols;
+    // never used as a divisor without full passes (full_slots is 0 then)
+    S->tile_cols = fast_div33((unsigned long long)tx * ty);
+    S->tile_slots = fast_div33(std::max(1ull, passes * S->tile_cols.d));
     S->photon_offset = o.photon_offset;
     S->po_mod = (uint32_t)(o.photon_offset % s.ncol);
 }
@@ -1296,6 +1433,8 @@ rt3d_status prepare(const rt3d_grid* grid, int ngp, const uint64_t* photons, con
     P.nx = s.nx; P.ny = s.ny; P.nz = s.nz;
     P.bx = s.bx; P.by = s.by; P.bz = s.bz;
     P.mx = s.mx; P.my = s.my; P.mz = s.mz;
+    P.div_bx = fast_div((uint32_t)s.bx);
+    P.div_by = fast_div((uint32_t)s.by);
     P.dx = grid->dx; P.dy = grid->dy; P.dz = grid->dz;
     P.inv_dx = 1.0f / grid->dx; P.inv_dy = 1.0f / grid->dy; P.inv_dz = 1.0f / grid->dz;
     P.cx = (float)s.bx * grid->dx; P.cy = (float)s.by * grid->dy; P.cz = (float)s.bz * grid->dz;
@@ -1310,7 +1449,6 @@ rt3d_status prepare(const rt3d_grid* grid, int ngp, const uint64_t* photons, con
     P.pool = o.pool_photons > 0 ? (uint32_t)o.pool_photons : 256u;
     P.refill = o.refill_lanes > 0 ? (uint32_t)o.refill_lanes : 16u;
     P.merge = (o.flags & RT3D_FLAG_NO_MERGE) ? 0 : 1;
-    P.wave_agg = (o.flags & RT3D_FLAG_WAVE_AGGREGATE) ? 1 : 0;
     P.sobol = (o.flags & RT3D_FLAG_SOBOL_ENTRY) ? 1 : 0;
     P.seed = seed;
     P.photons = total;
@@ -1346,15 +1484,20 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     int max_lds = 0;
     HIP_TRY(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
     const size_t maj_bytes = L.s.nmaj * sizeof(float);
-    const size_t lds_limit = L.o.lds_majorant > 0 ? (size_t)max_lds - 1024 : kLdsMajorantBytes;
+    const size_t own_lds = 8 * (C_N * kCntSlots + C_N);  // the kernel's static LDS
+    const size_t lds_limit = L.o.lds_majorant > 0 ? (size_t)max_lds - own_lds : kLdsMajorantBytes;
     const bool use_lds =
-        L.ngp == 1 && L.o.lds_majorant >= 0 && maj_bytes <= lds_limit && maj_bytes + 1024 <= (size_t)max_lds;
+        L.ngp == 1 && L.o.lds_majorant >= 0 && maj_bytes <= lds_limit && maj_bytes + own_lds <= (size_t)max_lds;
     const size_t lds = use_lds ? maj_bytes : 0;
     // crossings per loop iteration: a short walk keeps the lanes of a wave
     // in step (a long clear-sky walk of one lane would hold the others)
     L.P.max_walk = L.o.max_walk > 0 ? L.o.max_walk : (use_lds ? 3 : 2);
-    auto kernel = factored ? (use_lds ? trace_kernel<true, true> : trace_kernel<false, true>)
-                           : (use_lds ? trace_kernel<true, false> : trace_kernel<false, false>);
+    auto pick = [&](auto agg) {
+        constexpr bool kAgg = decltype(agg)::value;
+        return factored ? (use_lds ? trace_kernel<true, true, kAgg> : trace_kernel<false, true, kAgg>)
+                        : (use_lds ? trace_kernel<true, false, kAgg> : trace_kernel<false, false, kAgg>);
+    };
+    auto kernel = (L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) ? pick(std::true_type{}) : pick(std::false_type{});
     int ncu = 0;
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     const int threads = factored ? Shape_<true>::threads : Shape_<false>::threads;
