@@ -227,8 +227,9 @@ typedef struct {
                                 loop iteration before the wave re-converges;
                                 0 = automatic (3 with LDS majorants, else 2) */
     int32_t pool_photons;    /* photon ids a wave takes from the work queue
-                                at a time, 0 = 256, else >= 64 (one grab
-                                must cover every lane of a wave);
+                                at a time, 0 = automatic (256, less where a
+                                wave's share of the photons is small), else
+                                >= 64 (one grab covers every lane of a wave);
                                 1..63 and negative values: RT3D_EINVAL */
     int32_t refill_lanes;    /* a wave starts new photons once at least this
                                 many of its 64 lanes are idle (or none is

@@ -456,11 +456,12 @@ enum Counter { C_TOA, C_SFC_W, C_GAIN, C_LOSS, C_LOST, C_COLL, C_GAS, C_CLOUD, C
                C_ABSORBED, C_CAPPED, C_PASSES, C_ABS_COLL, C_N };
 constexpr int kCntSlots = 32;
 
-// Lanes with a pending rare event (surface, escape, roulette, photon ended)
-// before the wave handles them.  One such event comes up per loop iteration
-// and wave on average, for one lane; handled at once it costs the wave the
-// whole code path for that lane.
-constexpr uint32_t kServiceLanes = 8;
+// A wave handles pending rare events (surface, escape, roulette, photon ended)
+// once one in kServiceShare of its photons has one.  About one comes up per
+// loop iteration of a full wave; handled at once it costs the wave the whole
+// code path for one lane.  A share, not a count: where few photons are left
+// in a wave none should wait for long.
+constexpr uint32_t kServiceShare = 8;
 
 // One photon per lane.  Each loop iteration of
 // a lane: handle its pending rare event or (re)fill the lane with a new
@@ -565,7 +566,7 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     for (;;) {
         // ---- rare events, once enough lanes wait with one or none is live
         const uint64_t waiting = __ballot(st > kDead);
-        if (waiting && ((uint32_t)__popcll(waiting) >= kServiceLanes || !__ballot(st == kLive))) {
+        if (waiting && kServiceShare * (uint32_t)__popcll(waiting) >= (uint32_t)__popcll(__ballot(st != kDead))) {
             const TraceParams& Q = *cold_params();
             if (st == kAtSurface) {
                 // ---- Lambertian surface (sec. 2.3)
@@ -661,7 +662,9 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
             if (st == kDead) {
                 const uint32_t rank = (uint32_t)__popcll(dead & lane_mask_lt());
                 const unsigned long long local = rank < avail ? pool_next + rank : base + (rank - avail);
-                if (local < P.photons) {
+                // (a grab may hold fewer ids than lanes wait: the others try
+                // again in the next iteration)
+                if (rank < avail + P.pool && local < P.photons) {
                     // queue slot -> g-point, photon id and entry column
                     const TraceParams& Q = *cold_params();
                     const Slot sl = decode_slot(Q.sched, local);
@@ -713,7 +716,7 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
                 }
             }
             if (avail < need) {
-                pool_next = base + (need - avail);
+                pool_next = base + min((unsigned long long)P.pool, need - avail);
                 pool_end = base + P.pool;
             } else {
                 pool_next += need;
@@ -1478,6 +1481,8 @@ rt3d_status clear_outputs(const Launch& L, const rt3d_tallies* out, hipStream_t 
     return zero_u64((unsigned long long*)out->stats, RT3D_STATS_N, st);
 }
 
+constexpr unsigned kWavePhotons = 16;  // photons a wave has at least, where there are few
+
 rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
@@ -1500,15 +1505,32 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     auto kernel = (L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) ? pick(std::true_type{}) : pick(std::false_type{});
     int ncu = 0;
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    const int threads = factored ? Shape_<true>::threads : Shape_<false>::threads;
+    int threads = factored ? Shape_<true>::threads : Shape_<false>::threads;
+    // Few photons: a wave per kWavePhotons of them, spread over the CUs in
+    // smaller workgroups (a launch then lasts as long as its longest photon,
+    // and an iteration is shorter the fewer lanes and waves share it), and
+    // the work queue handed out in grabs that leave every wave some: a
+    // quarter of a wave's share, 16 to 256.  32x32x64 cells, 2^14 photons:
+    // 1325 us with 64 waves on 16 CUs (grabs of 256), 754 with 64 photons a
+    // wave on all CUs, 716 with 16 (8: 733); 90x66x50 cells, 1.5e6 photons:
+    // 3480 with grabs of 256, 3397 with 32, 3271 with 64.
+    const unsigned long long few = (L.total + kWavePhotons - 1) / kWavePhotons;
+    if (!L.o.grid_blocks && !L.o.block_threads)
+        threads = (int)std::min<unsigned long long>(threads, 64 * ((few + ncu - 1) / ncu));
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds));
     if (per_cu < 1) per_cu = 1;
     unsigned blocks = L.o.grid_blocks ? (unsigned)L.o.grid_blocks : (unsigned)(ncu * per_cu);
     // never more lanes than photons need
-    const unsigned long long max_blocks = (L.total + threads - 1) / threads;
+    const unsigned long long per_block = L.o.grid_blocks || L.o.block_threads ? threads : (threads / 64) * kWavePhotons;
+    const unsigned long long max_blocks = (L.total + per_block - 1) / per_block;
     if (blocks > max_blocks) blocks = (unsigned)max_blocks;
     if (blocks < 1) blocks = 1;
+    if (L.o.pool_photons == 0) {
+        const unsigned long long share = L.total / ((unsigned long long)blocks * (threads / 64));
+        const unsigned long long least = std::min<unsigned long long>(64, std::max<unsigned long long>(16, share));
+        L.P.pool = (uint32_t)std::min<unsigned long long>(256, std::max<unsigned long long>(least, share / 64 * 16));
+    }
     if (L.o.flags & RT3D_FLAG_TIME) {
         if (!g_t0) HIP_TRY(hipEventCreate(&g_t0));
         if (!g_t1) HIP_TRY(hipEventCreate(&g_t1));
