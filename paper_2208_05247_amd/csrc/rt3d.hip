@@ -162,7 +162,10 @@ __device__ __forceinline__ void turn(float& x, float& y, float& z, float mu, flo
     __sincosf(6.28318530717958647f * t, &sp, &cp);
     const float st = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
     float nx, ny, nz;
-    const float s2 = x * x + y * y;
+    // the order of every rounding is written out (see mul_rounded): for a sum
+    // of two products the compiler may fuse either, and does not choose the
+    // same one in every kernel
+    const float s2 = __builtin_fmaf(y, y, x * x);
     if (s2 < 1e-24f) {
         nx = st * cp;
         ny = st * sp;
@@ -170,11 +173,11 @@ __device__ __forceinline__ void turn(float& x, float& y, float& z, float mu, flo
     } else {
         const float is = rsqrtf(s2);
         const float s = s2 * is;
-        nx = st * (x * z * cp - y * sp) * is + x * mu;
-        ny = st * (y * z * cp + x * sp) * is + y * mu;
-        nz = -st * cp * s + z * mu;
+        nx = __builtin_fmaf(x, mu, st * __builtin_fmaf(x * z, cp, -(y * sp)) * is);
+        ny = __builtin_fmaf(y, mu, st * __builtin_fmaf(x, sp, y * z * cp) * is);
+        nz = __builtin_fmaf(z, mu, -(cp * st * s));
     }
-    const float n = rsqrtf(nx * nx + ny * ny + nz * nz);
+    const float n = rsqrtf(__builtin_fmaf(nz, nz, __builtin_fmaf(ny, ny, nx * nx)));
     x = nx * n;
     y = ny * n;
     z = nz * n;
@@ -320,6 +323,52 @@ __host__ __device__ inline Slot decode_slot(const Schedule& S, unsigned long lon
     return r;
 }
 
+// ---------------------------------------------------------------------------
+// Deposit buffer.  A 64-bit atomic to a heating tally is performed beyond the
+// L2, at most about 2.1e10 a second on tallies that the Infinity Cache holds
+// and 1.8e10 on larger ones, and the tracer makes some 30 per photon: more
+// than half of its time.  Where the caller's workspace has room, deposits are
+// written to memory instead, 8 bytes each in the order they come up, and added
+// to the tallies from there:
+//   trace_kernel         waves append deposits (cell and direct/diffuse bit,
+//                        amount) to chunks of kChunk that they take from the
+//                        buffer (wave w the w mod kTileChunks'th chunk of the
+//                        next tile: one counter for all would be asked for
+//                        more often than the 13 ns an atomic to one address
+//                        takes); when it is full, every wave stores its
+//                        lanes' photons and ends;
+//   deposit_sort_kernel  orders each tile of kTileDeposits by bin (kBinCells
+//                        consecutive cells) in place, and writes where each
+//                        bin starts in the tile;
+//   deposit_add_kernel   one workgroup per bin reads the bin's run of every
+//                        tile, sums it in LDS and adds the sums to the tallies.
+// Rounds of the three follow until no photon is left; the number launched is
+// an upper estimate (a round with nothing to do ends at once), and the last
+// one adds what does not fit by atomics.  The sums are of integers: the
+// tallies are those of the atomics, bit for bit.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kChunk = 256;                         // deposits a wave takes room for at a time
+constexpr uint32_t kTileChunks = 64;                     // chunks of a tile
+constexpr uint32_t kTileDeposits = kChunk * kTileChunks; // 128 KiB, sorted in LDS
+constexpr int kBinShift = 13;                            // a bin's 2 x 2^13 sums (64 bits) are 128 KiB of LDS
+constexpr uint32_t kBinCells = 1u << kBinShift;
+constexpr uint32_t kMaxBins = 2048;
+constexpr uint32_t kMaxRounds = 8192;
+constexpr int kLaneWords = 24;  // a lane's photon and pending deposits, stored between rounds
+
+struct Deposits {
+    uint32_t* used;         // [2][kTileChunks] 128 bytes apart: chunks taken of each column (past ntiles: full)
+    unsigned long long* waves;  // [3][nwaves] queue ids left (next, end), finished
+    uint32_t* lanes;        // [kLaneWords][nlanes]
+    uint32_t* count;        // [ntiles][kTileChunks] deposits in each chunk
+    uint16_t* start;        // [ntiles][nbins + 1] first deposit of each bin in a sorted tile
+    uint2* item;            // [ntiles][kTileChunks][kChunk] (cell | diffuse << 31, amount)
+    uint32_t ntiles, nbins, nwaves, nlanes;
+
+    // column q's counter in round r (its set is cleared during round r - 1)
+    __device__ uint32_t* used_in(int r, uint32_t q) const { return used + 32 * (kTileChunks * (r & 1) + q); }
+};
+
 struct TraceParams {
     // medium: kFactored = false: cells = (k_ext, ssa, k_ext_cloud, g) per cell;
     //         kFactored = true:  cells = (k_ext_cloud, cloud k_abs, g, 0) per cell,
@@ -360,6 +409,8 @@ struct TraceParams {
     uint32_t max_iters;
     unsigned long long seed;  // g-point n draws with Philox key seed + n
     unsigned long long photons, photon_offset, ncol;
+    Deposits dep;             // kBinned only
+    int round, last_round;
 };
 
 enum { L_IN, L_TOA, L_ATM_DIR, L_ATM_DIF, L_SFC, L_RR_GAIN, L_RR_LOSS, L_LOST, L_N };
@@ -471,20 +522,25 @@ constexpr uint32_t kServiceShare = 8;
 // surface / top, then handle a collision (the other events wait).  kLds:
 // majorant grid of the single
 // g-point staged in LDS.  kFactored: shared cloud field + per-g-point gas
-// profiles (several g-points in one launch).  kAgg: wave-aggregated tally
-// atomics.
+// profiles (several g-points in one launch).  kTally: heating deposits by
+// atomics, by wave-aggregated atomics (so are the surface tallies then), or
+// through the deposit buffer.
 // Rare events deferred, counters at lane-dependent LDS addresses, no scalar
 // spills: 4.24e10 vector instructions on the 256x256x128 field with 2^26
 // photons against 6.27e10, 98.7 against 100.1 ms (bound by the tally atomics
 // there); 32x32x64 cells with 2^14 photons 1.54 against 2.29 ms; 128^3 cells,
 // 112 g-points, 4.2e6 photons 6.5 against 7.0 ms.
-// Launch shape: the single-g-point kernel runs workgroups of up to 1024 lanes
-// at 8 waves per SIMD (two workgroups per CU share the 160 KB LDS); the factored
-// kernel needs more registers and runs 256-lane workgroups at 6 waves.
+// Launch shape: the single-g-point kernel runs workgroups of up to 768 lanes,
+// two per CU (which share the 160 KB LDS), at 6 waves per SIMD and 80 vector
+// registers (8 waves at 64 registers spill with the deposit buffer: 83.0
+// against 81.4 ms on the 256x256x128 field); the factored kernel runs 256-lane
+// workgroups at 6 waves.
+enum Tally { kDirect, kAggregated, kBinned };
+
 template <bool kFactored>
 struct Shape_ {
-    static constexpr int threads = kFactored ? 256 : 1024;
-    static constexpr int waves = kFactored ? 6 : 8;
+    static constexpr int threads = kFactored ? 256 : 768;
+    static constexpr int waves = 6;
 };
 
 // The kernel's parameters for code that runs for a small part of the loop
@@ -499,11 +555,21 @@ __device__ __forceinline__ const TraceParams* cold_params() {
     return (const TraceParams*)q;
 }
 
-template <bool kLds, bool kFactored, bool kAgg>
+template <bool kLds, bool kFactored, int kTally>
 __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     __attribute__((amdgpu_waves_per_eu(Shape_<kFactored>::waves))) trace_kernel(const TraceParams P) {
+    constexpr bool kAgg = kTally == kAggregated;
     extern __shared__ float s_maj[];
     __shared__ unsigned long long s_cnt[C_N][kCntSlots];
+
+    const uint32_t wave = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+    const uint32_t lane_ix = blockIdx.x * blockDim.x + threadIdx.x;
+    bool drained = false;
+    if (kTally == kBinned && P.round) {
+        // nothing left to do for the whole workgroup: end
+        drained = P.dep.waves[2 * P.dep.nwaves + wave] != 0;
+        if (!__syncthreads_or(!drained)) return;
+    }
 
     for (int i = threadIdx.x; i < C_N * kCntSlots; i += blockDim.x) s_cnt[i / kCntSlots][i % kCntSlots] = 0;
     if (kLds) {
@@ -526,9 +592,9 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     float kmaj = __uint_as_float(kNoMajorant);
     uint32_t w = 0, step = 0, iters = 0;
     bool direct = false;
-    // merged deposit: cell index, bit 31 set for diffuse
-    uint32_t pend_key = kNoCell;
-    unsigned long long pend_amt = 0;
+    // merged deposit: cell index, bit 31 set for diffuse; and the one before
+    // it, which the next loop iteration writes out (amount 0: none)
+    uint32_t pend_key = kNoCell, pend_amt = 0, out_key = 0, out_amt = 0;
     // per-photon counters (folded into LDS when the photon ends).  Brick
     // crossings and null collisions are derived when the workgroup ends:
     // crossings = passes - collisions - surface hits - escapes - capped,
@@ -537,15 +603,49 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
 
     // ---- per-wave photon-id pool (wave-uniform, kept in scalar registers)
     unsigned long long pool_next = 0, pool_end = 0;
-    bool drained = false;
 
-    auto flush_deposit = [&]() {
-        if (pend_amt) {
-            const uint32_t cell = pend_key & 0x7fffffffu;
-            tally_add<kAgg>(pend_key & 0x80000000u ? &P.abs_dif[cell] : &P.abs_dir[cell], pend_amt);
-        }
-        pend_key = kNoCell;
-        pend_amt = 0;
+    // ---- kBinned: the wave's chunk of the deposit buffer (wave-uniform)
+    constexpr uint32_t kNoChunk = 0xffffffffu;
+    uint32_t chunk = kNoChunk, chunk_pos = kChunk;
+    bool full = false, suspended = false;
+
+    // every word of a lane's state that lives from one round to the next
+    auto each_word = [&](auto&& f) {
+        uint32_t lo = (uint32_t)id, hi = (uint32_t)(id >> 32), fl = (uint32_t)st | (direct ? 256u : 0u);
+        auto fw = [&](int n, float& v) {
+            uint32_t b = __float_as_uint(v);
+            f(n, b);
+            v = __uint_as_float(b);
+        };
+        auto iw = [&](int n, int& v) {
+            uint32_t b = (uint32_t)v;
+            f(n, b);
+            v = (int)b;
+        };
+        f(0, lo); f(1, hi); f(2, fl); iw(3, gp);
+        fw(4, px); fw(5, py); fw(6, pz); fw(7, ux); fw(8, uy); fw(9, uz);
+        iw(10, bi); iw(11, bj); iw(12, bk); fw(13, tau); fw(14, kmaj);
+        f(15, w); f(16, step); f(17, iters); f(18, pend_key); f(19, pend_amt); f(20, out_key); f(21, out_amt);
+        f(22, n_coll); f(23, n_scat);
+        static_assert(kLaneWords == 24, "one word per field");
+        id = (unsigned long long)lo | ((unsigned long long)hi << 32);
+        st = (int)(fl & 255u);
+        direct = fl & 256u;
+    };
+    if (kTally == kBinned && P.round && !drained) {
+        const Deposits& D = cold_params()->dep;
+        each_word([&](int n, uint32_t& v) { v = D.lanes[(size_t)n * D.nlanes + lane_ix]; });
+        auto uniform = [](unsigned long long v) {
+            return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+                   (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+        };
+        pool_next = uniform(D.waves[wave]);
+        pool_end = uniform(D.waves[D.nwaves + wave]);
+        drained = pool_next >= cold_params()->photons;
+    }
+    auto add_heat = [&](uint32_t key, uint32_t amt) {
+        const uint32_t cell = key & 0x7fffffffu;
+        tally_add<kAgg>(key & 0x80000000u ? &P.abs_dif[cell] : &P.abs_dir[cell], (unsigned long long)amt);
     };
     auto flush_scat = [&]() {
         count(C_GAS, n_scat & 0xffffu);
@@ -564,6 +664,48 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     };
 
     for (;;) {
+        // ---- the deposits of the last iteration
+        if (kTally != kBinned) {
+            if (out_amt) add_heat(out_key, out_amt);
+            out_amt = 0;
+        } else if (const uint64_t depositing = __ballot(out_amt != 0)) {
+            const uint32_t n = (uint32_t)__popcll(depositing);
+            if (chunk_pos + n > kChunk && !full) {
+                const Deposits& D = cold_params()->dep;
+                if (chunk != kNoChunk && __lane_id() == 0) D.count[chunk] = chunk_pos;
+                // its own column first, then a few others that are not used up
+                chunk = kNoChunk;
+                chunk_pos = 0;
+                for (uint32_t q = 0; q < 8 && chunk == kNoChunk; ++q) {
+                    const uint32_t column = (wave + 9 * q) % kTileChunks;
+                    uint32_t c = 0;
+                    if (__lane_id() == 0) c = atomicAdd(D.used_in(cold_params()->round, column), 1u);
+                    c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+                    if (c < D.ntiles) chunk = c * kTileChunks + column;
+                }
+                if (chunk == kNoChunk) {
+                    // no room: end here, and go on in the next round; but once
+                    // no new photons come, the few deposits left are added by
+                    // atomics (the longest photons' time is spent once then)
+                    full = true;
+                    const unsigned long long handed_out =
+                        __hip_atomic_load(cold_params()->queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (!cold_params()->last_round && handed_out < cold_params()->photons) {
+                        suspended = true;
+                        break;
+                    }
+                }
+            }
+            if (!full) {
+                if (out_amt)
+                    P.dep.item[(size_t)chunk * kChunk + chunk_pos + (uint32_t)__popcll(depositing & lane_mask_lt())] =
+                        make_uint2(out_key, out_amt);
+                chunk_pos += n;
+            } else if (out_amt) {
+                add_heat(out_key, out_amt);
+            }
+            out_amt = 0;
+        }
         // ---- rare events, once enough lanes wait with one or none is live
         const uint64_t waiting = __ballot(st > kDead);
         if (waiting && kServiceShare * (uint32_t)__popcll(waiting) >= (uint32_t)__popcll(__ballot(st != kDead))) {
@@ -814,12 +956,15 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         if (L.ka > 0.f) {
             const uint32_t dep = min(w, (uint32_t)rintf((float)w * (L.ka * iK)));
             const uint32_t key = cell | (direct ? 0u : 0x80000000u);
-            if (key != pend_key) {
-                flush_deposit();
+            // the merged deposit goes out when the photon deposits elsewhere
+            // (or its sum would pass 32 bits)
+            if (key != pend_key || pend_amt + dep < dep || !P.merge) {
+                out_key = pend_key;
+                out_amt = pend_amt;
                 pend_key = key;
+                pend_amt = 0;
             }
             pend_amt += dep;
-            if (!P.merge) flush_deposit();
             w -= dep;
             if (w == 0) {
                 st = kAbsorbedOut;
@@ -847,9 +992,22 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         else ++step;
     }
 
-    flush_deposit();
-    __syncthreads();
     const TraceParams& Q = *cold_params();
+    if (kTally == kBinned) {
+        const Deposits& D = Q.dep;
+        if (chunk != kNoChunk && __lane_id() == 0) D.count[chunk] = chunk_pos;
+        if (suspended) {
+            each_word([&](int n, uint32_t& v) { D.lanes[(size_t)n * D.nlanes + lane_ix] = v; });
+            pend_amt = 0;  // (not yet added)
+        }
+        if (__lane_id() == 0) {
+            D.waves[wave] = pool_next;
+            D.waves[D.nwaves + wave] = pool_end;
+            D.waves[2 * D.nwaves + wave] = suspended ? 0 : 1;
+        }
+    }
+    if (pend_amt) add_heat(pend_key, pend_amt);
+    __syncthreads();
     // sums of the counter copies, then the ledger and stats entries
     __shared__ unsigned long long s_sum[C_N];
     if (threadIdx.x < C_N) {
@@ -861,7 +1019,7 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     if (threadIdx.x == 0) {
         auto led = [&](int e, unsigned long long v) { if (v) atomicAdd(&Q.ledger[e], v); };
         auto sta = [&](int e, unsigned long long v) { if (v) atomicAdd(&Q.stats[e], v); };
-        if (blockIdx.x == 0) {  // every queue slot is traced, each with weight one
+        if (blockIdx.x == 0 && Q.round == 0) {  // every queue slot is traced, each with weight one
             led(L_IN, Q.photons * kWOne);
             sta(S_PHOT, Q.photons);
         }
@@ -882,6 +1040,169 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         sta(S_CROSS, s_sum[C_PASSES] - coll - s_sum[C_SFC] - s_sum[C_ESC] - s_sum[C_CAPPED]);
         sta(S_ABSORBED, s_sum[C_ABSORBED]);
         sta(S_CAPPED, s_sum[C_CAPPED]);
+    }
+}
+
+// The longest column: the maximum over the wave's lanes of their counters.
+__device__ __forceinline__ uint32_t tiles_used(uint32_t mine) {
+    static_assert(kTileChunks == 64, "one column per lane");
+    for (int o = 32; o > 0; o >>= 1) mine = max(mine, (uint32_t)__shfl_xor((int)mine, o));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)mine);
+}
+
+// Sorts each tile of the deposit buffer by bin, in place.  One workgroup per
+// tile: its 16384 deposits (16 a lane, in registers) count themselves into LDS
+// counters per bin, which also gives each its rank within the bin, the counts
+// are scanned to the bins' starts, and the tile is put in order in LDS and
+// written back in one piece (scattered 8-byte stores to memory would be
+// 32 bytes each).  Bound by its 16 bytes of memory traffic per deposit.
+__global__ void __launch_bounds__(1024) deposit_sort_kernel(const Deposits D, int round) {
+    __shared__ uint2 s_item[kTileDeposits];
+    __shared__ uint32_t s_bin[kMaxBins];
+    __shared__ uint32_t s_part[16];
+    __shared__ uint32_t s_total;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ uint32_t s_used[kTileChunks];
+    if (tid < kTileChunks) {
+        s_used[tid] = *D.used_in(round, tid);
+        if (blockIdx.x == 0) *D.used_in(round + 1, tid) = 0;
+    }
+    __syncthreads();
+    const uint32_t ntiles = min(tiles_used(s_used[lane]), D.ntiles);
+    constexpr int kPer = kTileDeposits / 1024;
+    uint2 v[kPer];
+    auto load = [&](uint32_t t) {
+        const uint2* tile = D.item + (size_t)t * kTileDeposits;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const uint32_t p = i * 1024 + tid, c = p / kChunk;
+            v[i] = make_uint2(0u, 0u);
+            if (t < s_used[c] && p % kChunk < D.count[t * kTileChunks + c]) v[i] = tile[p];
+        }
+    };
+    if (blockIdx.x < ntiles) load(blockIdx.x);
+#pragma unroll 1
+    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        for (uint32_t b = tid; b < D.nbins; b += 1024) s_bin[b] = 0;
+        __syncthreads();
+        uint2* tile = D.item + (size_t)t * kTileDeposits;
+        uint32_t rank[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)  // (a deposit's amount is never 0)
+            if (v[i].y) rank[i] = atomicAdd(&s_bin[(v[i].x & 0x7fffffffu) >> kBinShift], 1u);
+        __syncthreads();
+        // exclusive scan of the counts, two bins a lane
+        const uint32_t c0 = 2 * tid < D.nbins ? s_bin[2 * tid] : 0u;
+        const uint32_t c1 = 2 * tid + 1 < D.nbins ? s_bin[2 * tid + 1] : 0u;
+        uint32_t sum = c0 + c1;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(sum, o);
+            if ((int)lane >= o) sum += u;
+        }
+        if (lane == 63) s_part[wave] = sum;
+        __syncthreads();
+        uint32_t before = sum - c0 - c1;
+        for (uint32_t q = 0; q < wave; ++q) before += s_part[q];
+        uint16_t* start = D.start + (size_t)t * (D.nbins + 1);
+        if (2 * tid < D.nbins) {
+            s_bin[2 * tid] = before;
+            start[2 * tid] = (uint16_t)before;
+        }
+        if (2 * tid + 1 < D.nbins) {
+            s_bin[2 * tid + 1] = before + c0;
+            start[2 * tid + 1] = (uint16_t)(before + c0);
+        }
+        if (tid == 1023) {
+            s_total = before + c0 + c1;
+            start[D.nbins] = (uint16_t)(before + c0 + c1);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            if (v[i].y) s_item[s_bin[(v[i].x & 0x7fffffffu) >> kBinShift] + rank[i]] = v[i];
+        __syncthreads();
+        const uint32_t total = s_total;
+        // the next tile's deposits are on their way while this one is stored
+        if (t + gridDim.x < ntiles) load(t + gridDim.x);
+        for (uint32_t p = tid; p < total; p += 1024) tile[p] = s_item[p];
+        __syncthreads();  // before the next tile clears the counters
+    }
+}
+
+// Adds the deposits of one bin to the tallies: each half-wave takes the bin's
+// run of one sorted tile at a time (the run's place from the table, read for
+// 64 tiles at once), 16 tiles in flight per half-wave, and sums it in LDS;
+// the sums that are not zero are then added to the tallies, which nobody else
+// writes in this launch.  Neighbouring bins run on the same XCD, so that the
+// 128-byte lines of the table are shared in its L2.
+__global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int round, uint32_t ncell,
+                                                           unsigned long long* __restrict__ abs_dir,
+                                                           unsigned long long* __restrict__ abs_dif) {
+    __shared__ unsigned long long s_sum[2 * kBinCells];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t per_xcd = (D.nbins + 7) / 8;
+    const uint32_t bin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const uint32_t ntiles = min(tiles_used(*D.used_in(round, lane)), D.ntiles);
+    if (bin >= D.nbins || ntiles == 0) return;
+    for (uint32_t i = tid; i < 2 * kBinCells; i += 1024) s_sum[i] = 0;
+    __syncthreads();
+    const uint32_t hl = lane & 31;
+    constexpr int kFlight = 16;
+    auto place = [&](uint32_t t, uint32_t& first, uint32_t& last) {
+        first = last = 0;
+        if (t < ntiles) {
+            const uint16_t* start = D.start + (size_t)t * (D.nbins + 1) + bin;
+            first = start[0];
+            last = start[1];
+        }
+    };
+    uint32_t first_next, last_next;
+    place(wave * 64 + lane, first_next, last_next);
+    for (uint32_t t0 = wave * 64; t0 < ntiles; t0 += 16 * 64) {
+        const uint32_t first = first_next, last = last_next;
+        place(t0 + 16 * 64 + lane, first_next, last_next);
+        // the run of tile t0 + l: where it starts (counted from tile t0) and its length
+        const uint32_t at = lane * kTileDeposits + first, len = last - first;
+        const uint2* item = D.item + (size_t)t0 * kTileDeposits;
+        auto sum = [&](const uint2& v) {
+            atomicAdd(&s_sum[(v.x & (kBinCells - 1)) | ((v.x >> 31) << kBinShift)], (unsigned long long)v.y);
+        };
+#pragma unroll 1
+        for (int q = 0; q < 64; q += 2 * kFlight) {
+            uint2 v[kFlight];
+            uint32_t n[kFlight];
+#pragma unroll
+            for (int f = 0; f < kFlight; ++f) {
+                const int src = q + 2 * f + (int)(lane >> 5);
+                const uint32_t from = __shfl(at, src);
+                n[f] = __shfl(len, src);
+                // (a lane past the run reads its first deposit again: no branch
+                // between the loads, so all of them are in flight)
+                v[f] = item[from + (hl < n[f] ? hl : 0u)];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < kFlight; ++f)
+                if (hl < n[f]) sum(v[f]);
+            // runs of more than 32
+            bool more = false;
+#pragma unroll
+            for (int f = 0; f < kFlight; ++f) more |= n[f] > 32;
+            if (__ballot(more)) {
+                for (int f = 0; f < 2 * kFlight; f += 2) {
+                    const int src = q + f + (int)(lane >> 5);
+                    const uint32_t from = __shfl(at, src), m = __shfl(len, src);
+                    for (uint32_t i = 32 + hl; i < m; i += 32) sum(item[from + i]);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < kBinCells; i += 1024) {
+        const size_t cell = (size_t)bin * kBinCells + i;
+        if (cell >= ncell) break;
+        if (s_sum[i]) abs_dir[cell] += s_sum[i];
+        if (s_sum[kBinCells + i]) abs_dif[cell] += s_sum[kBinCells + i];
     }
 }
 
@@ -1337,12 +1658,52 @@ void schedule_of(const Shape& s, int ngp, const uint64_t* photons, const rt3d_op
     S->po_mod = (uint32_t)(o.photon_offset % s.ncol);
 }
 
+// The deposit buffer in the part of the workspace behind the sections above,
+// or false where there is no room for it or no use: at least kMinTiles tiles,
+// at most kMaxBins bins, kMinPhotons photons, one g-point.  256x256x128 cells
+// (1024 bins, a buffer of 1 GiB), whole call, atomics against the buffer: 2^22
+// photons 7.8 / 7.0 ms (one round), 2^23 14.1 / 14.4, 2^24 26.4 / 22.1, 2^25
+// 51.3 / 41.8, 2^26 101.1 / 81.4.  Of the 81.4 ms the sort takes 13.4 (2.5 TB/s)
+// and the addition 13.1.  The kernel for several g-points, slower itself,
+// gained at most 2 % (128^3 cells, 112 g-points, 3.4e7 photons: 38.3 / 37.4 ms)
+// and lost up to 4 % below 8e6 photons, so it keeps the atomics.
+constexpr uint32_t kMinTiles = 256;
+constexpr unsigned long long kMinPhotons = 1ull << 24;
+
+bool deposit_buffer(const Shape& s, unsigned long long photons, char* at, size_t bytes, uint32_t nlanes,
+                    Deposits* D) {
+    const size_t nbins = (s.ncell + kBinCells - 1) / kBinCells;
+    if (nbins > kMaxBins || photons < kMinPhotons) return false;
+    D->nbins = (uint32_t)nbins;
+    D->nlanes = nlanes;
+    D->nwaves = nlanes / 64;
+    const size_t fixed = 2 * kTileChunks * 128 + align256(24 * (size_t)D->nwaves) +
+                         align256(4 * (size_t)kLaneWords * nlanes);
+    const size_t per_tile = 8 * (size_t)kTileDeposits + 4 * kTileChunks + 2 * (nbins + 1);
+    if (bytes < fixed + 1024 + kMinTiles * per_tile) return false;
+    D->ntiles = (uint32_t)std::min<size_t>((bytes - fixed - 1024) / per_tile, 1u << 20);
+    D->item = (uint2*)at;
+    at += 8 * (size_t)kTileDeposits * D->ntiles;
+    D->used = (uint32_t*)at;
+    at += 2 * kTileChunks * 128;
+    D->waves = (unsigned long long*)at;
+    at += align256(24 * (size_t)D->nwaves);
+    D->lanes = (uint32_t*)at;
+    at += align256(4 * (size_t)kLaneWords * nlanes);
+    D->count = (uint32_t*)at;
+    at += 4 * (size_t)kTileChunks * D->ntiles;
+    D->start = (uint16_t*)at;
+    return true;
+}
+
 struct Launch {
     rt3d_options o;
     Shape s;
     int ngp;
     unsigned long long total;
     char* ws;
+    char* spare;         // workspace behind the sections of layout_of
+    size_t spare_bytes;
     uint32_t* flag;
     float* maj;
     float4* cells;
@@ -1374,8 +1735,8 @@ rt3d_status prepare(const rt3d_grid* grid, int ngp, const uint64_t* photons, con
     if (o.refill_lanes < 0 || o.refill_lanes > 64) return RT3D_EINVAL;
     if (o.tile_x < 0 || o.tile_y < 0 || (o.tile_x && s.nx % o.tile_x) || (o.tile_y && s.ny % o.tile_y))
         return RT3D_EINVAL;
-    if (o.block_threads && o.block_threads != (factored ? Shape_<true>::threads : Shape_<false>::threads))
-        return RT3D_EINVAL;
+    // the one size that each kernel takes (1024: the kernel's largest, fewer lanes)
+    if (o.block_threads && o.block_threads != (factored ? 256 : 1024)) return RT3D_EINVAL;
     unsigned long long total = 0;
     for (int n = 0; n < ngp; ++n) {
         if (total + photons[n] < total) return RT3D_EINVAL;
@@ -1390,6 +1751,8 @@ rt3d_status prepare(const rt3d_grid* grid, int ngp, const uint64_t* photons, con
     L->ngp = ngp;
     L->total = total;
     L->ws = (char*)workspace;
+    L->spare = L->ws + lay.total;
+    L->spare_bytes = workspace_bytes - lay.total;
     L->flag = (uint32_t*)(L->ws + 128);
     L->maj = (float*)(L->ws + lay.maj);
     L->cells = (float4*)(L->ws + lay.cells);
@@ -1497,12 +1860,13 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     // crossings per loop iteration: a short walk keeps the lanes of a wave
     // in step (a long clear-sky walk of one lane would hold the others)
     L.P.max_walk = L.o.max_walk > 0 ? L.o.max_walk : (use_lds ? 3 : 2);
-    auto pick = [&](auto agg) {
-        constexpr bool kAgg = decltype(agg)::value;
-        return factored ? (use_lds ? trace_kernel<true, true, kAgg> : trace_kernel<false, true, kAgg>)
-                        : (use_lds ? trace_kernel<true, false, kAgg> : trace_kernel<false, false, kAgg>);
+    auto pick = [&](auto tally) {
+        constexpr int kTally = decltype(tally)::value;
+        return factored ? (use_lds ? trace_kernel<true, true, kTally> : trace_kernel<false, true, kTally>)
+                        : (use_lds ? trace_kernel<true, false, kTally> : trace_kernel<false, false, kTally>);
     };
-    auto kernel = (L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) ? pick(std::true_type{}) : pick(std::false_type{});
+    auto kernel = (L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) ? pick(std::integral_constant<int, kAggregated>{})
+                                                         : pick(std::integral_constant<int, kDirect>{});
     int ncu = 0;
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     int threads = factored ? Shape_<true>::threads : Shape_<false>::threads;
@@ -1536,8 +1900,30 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
         if (!g_t1) HIP_TRY(hipEventCreate(&g_t1));
         HIP_TRY(hipEventRecord(g_t0, st));
     }
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, st, L.P);
-    HIP_TRY(hipGetLastError());
+    Deposits& D = L.P.dep;
+    if (!factored && !(L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) &&
+        deposit_buffer(L.s, L.total, L.spare, L.spare_bytes, blocks * (unsigned)threads, &D)) {
+        kernel = use_lds ? trace_kernel<true, false, kBinned> : trace_kernel<false, false, kBinned>;
+        // 64 deposits a photon are more than the fields in use give (26 to 31)
+        const unsigned long long room = (unsigned long long)D.ntiles * kTileDeposits;
+        const int rounds = (int)std::min<unsigned long long>(kMaxRounds, 1 + L.total / (room / 64 + 1));
+        hipLaunchKernelGGL(fill_u32_kernel, dim3(4), dim3(256), 0, st, D.used, (size_t)2 * kTileChunks * 32, 0u);
+        HIP_TRY(hipGetLastError());
+        for (int r = 0; r < rounds; ++r) {
+            L.P.round = r;
+            L.P.last_round = r == rounds - 1;
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, st, L.P);
+            HIP_TRY(hipGetLastError());
+            hipLaunchKernelGGL(deposit_sort_kernel, dim3(std::min<unsigned>(D.ntiles, (unsigned)ncu)), dim3(1024), 0, st, D, r);
+            HIP_TRY(hipGetLastError());
+            hipLaunchKernelGGL(deposit_add_kernel, dim3((D.nbins + 7) / 8 * 8), dim3(1024), 0, st, D, r,
+                               (uint32_t)L.s.ncell, L.P.abs_dir, L.P.abs_dif);
+            HIP_TRY(hipGetLastError());
+        }
+    } else {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, st, L.P);
+        HIP_TRY(hipGetLastError());
+    }
     if (L.o.flags & RT3D_FLAG_TIME) {
         HIP_TRY(hipEventRecord(g_t1, st));
         g_timed = true;
@@ -1692,8 +2078,7 @@ rt3d_status rt3d_trace_noalloc(const rt3d_grid* grid, const rt3d_optical_props* 
     void* ws = nullptr;
     const rt3d_status st = scratch_address(&ws);
     if (st != RT3D_OK) return st;
-    return rt3d_trace(grid, props, surface_albedo, sza_deg, azimuth_deg, photons, seed, opt, out, ws,
-                      RT3D_NOALLOC_SCRATCH_BYTES, stream);
+    return rt3d_trace(grid, props, surface_albedo, sza_deg, azimuth_deg, photons, seed, opt, out, ws, need, stream);
 }
 
 rt3d_status rt3d_trace_batched(const rt3d_grid* grid, int32_t n_gpoints, const rt3d_batched_medium* medium,

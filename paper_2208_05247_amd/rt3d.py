@@ -216,11 +216,24 @@ def schedule_slots(grid, photons, col_offsets, opt: Options, first_slot: int = 0
     return gp, ids, cols
 
 
+class _WorkspaceBytes(int):
+    """A workspace size that also says how much more memory the tracer can use
+    (bytes of deposit buffer, see alloc_workspace)."""
+    spare = 0
+
+
+# largest grid whose deposits the tracer collects in a buffer
+DEPOSIT_BUFFER_CELLS = 2048 << 13
+
+
 def workspace_size(grid, opt: Options) -> int:
     n = load().rt3d_workspace_size(ctypes.byref(grid_struct(grid)), ctypes.byref(opt))
     if n == 0:
         raise Rt3dError(EINVAL, "rt3d_workspace_size")
-    return int(n)
+    size = _WorkspaceBytes(n)
+    if grid.nx * grid.ny * grid.nz <= DEPOSIT_BUFFER_CELLS:
+        size.spare = max(8 * size, 128 << 20)
+    return size
 
 
 def alloc_tallies(grid, device="cuda") -> dict:
@@ -232,9 +245,19 @@ def alloc_tallies(grid, device="cuda") -> dict:
 
 
 def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
-    ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
+    """A workspace of nbytes, 256-byte aligned.  For a size that came from
+    workspace_size it is larger by a deposit buffer (eight times the size, at
+    least 128 MiB, for grids of up to DEPOSIT_BUFFER_CELLS; left out where
+    memory is short): with many photons rt3d_trace collects heating deposits
+    there instead of adding each to its tally by an atomic (same results)."""
+    spare = getattr(nbytes, "spare", 0)
+    try:
+        ws = torch.empty(nbytes + spare + 256, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        spare = 0
+        ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
     off = (-ws.data_ptr()) % 256
-    return ws[off:off + nbytes]
+    return ws[off:off + nbytes + spare]
 
 
 def tallies_struct(t: dict) -> TalliesStruct:
