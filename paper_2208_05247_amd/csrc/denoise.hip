@@ -166,7 +166,8 @@ constexpr int kHaloVox = (kZ + 2) * kHaloY * kHaloX;
 // holds a whole number of batches (tile_slots), and slots outside the domain
 // or past the halo read the 16-byte zero block.  The caller waits for the
 // loads (vmcnt) before the barrier that publishes the tile.
-constexpr int tile_slots(int halo_vox) { return (halo_vox * 2 + 63) / 64 * 64; }
+constexpr int tile_slots_of(int pieces) { return (pieces + 63) / 64 * 64; }
+constexpr int tile_slots(int halo_vox) { return tile_slots_of(halo_vox * 2); }
 
 template <int NZ, int HY, int NT>
 __device__ __forceinline__ void stage_halo16_lds(uint4* tile, const ConvArgs& a, int c0, int x0, int y0, int z0) {
@@ -966,9 +967,10 @@ __global__ void flip_weights_kernel(const uint16_t* __restrict__ w, uint16_t* __
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient: dw[co][t][ci] += sum_v dz[v][co] x[v + off(t)][ci]
+// Weight gradient: dw[co][t][ci] += sum_v dz[v][co] x[v + off(t)][ci], and the
+// bias gradient db[co] += sum_v dz[v][co].
 // GEMM rows = output channels, columns = input channels, reduction over 16
-// voxels of one x-row per MFMA.  One wave: (co tile, ci tile, tap, rows).
+// voxels of one x-row per MFMA.
 // ---------------------------------------------------------------------------
 struct WgradArgs {
     const uint16_t* dz;
@@ -977,28 +979,211 @@ struct WgradArgs {
     const uint16_t* x2;
     int c1, c2;
     float* dw;
-    float* partial;  // per-row-chunk partial dw [chunks][cout][taps][cin], or null: atomics into dw
-    int D, H, W, rows_per_wave;
+    float* db;       // or null
+    float* partial;  // per-chunk partial dw [chunks][cout][taps][cin], or null: atomics into dw
+    float* partial_b;  // per-chunk partial db [chunks][cout] (with partial)
+    int D, H, W;
+    int chunks;        // parts of the voxels, one workgroup each
 };
 
-template <int KS>
-__global__ void __launch_bounds__(256) conv_wgrad_kernel(const WgradArgs a) {
+// The 3x3x3 weight gradient.  Both MFMA operands run along voxels, which are
+// the slow dimension of channels-last data: ds_read_b64_tr_b16 reads a block
+// of 4 voxels x 16 channels from LDS and gives each of 16 lanes one channel's
+// four voxels (lane l of the 16 addresses voxel l / 4, channels 4 (l % 4) ..;
+// checked on the device), so a fragment is two such reads and a tap's shift is
+// an address.
+// A workgroup of 4 waves owns NCO x 32 output and NCI x 32 input channels of
+// one chunk of the voxels; wave w accumulates taps 7 w .. 7 w + 6 (the 28th
+// slot multiplies dz with ones: the bias gradient).  The chunk is a range of
+// (tile of TY x 32 voxels, plane) units, planes innermost: the input planes
+// z-1, z, z+1 of a tile stay in LDS, in a ring of four whose fourth plane
+// (and the next plane of dz) is loaded while this one is computed.
+// What bounds it: LDS reads (82 of 128 bytes a cycle with NCO = 2, at the
+// MFMAs' full rate) and MFMA issue, at one wave a SIMD.  Measured on 128^3
+// voxels: 96 -> 32 channels (NCI = 3) 0.91 ms, 381 TFLOP/s; 192 -> 64 at 64^3
+// (NCO = 2) 0.24 ms, 370 TFLOP/s.  With operands gathered from global memory
+// by 2-byte loads, a wave per (32 x 32 channels, tap), they took 3.8 and 1.0 ms
+// (32 -> 64 channels on 64x60x52 voxels, whole call: 394 us, now 70).
+template <int NCO, int NCI, int TY>
+struct WgradTile {
+    static constexpr int kRows = TY + 2;
+    static constexpr int kSlab = tile_slots_of(kRows * kHaloX * 4);  // 16-byte pieces of one 32-channel plane
+    static constexpr int kPlane = kSlab * NCI;
+    static constexpr int kDzSlab = TY * kTX * 4;
+    static constexpr int kDzPlane = kDzSlab * NCO;
+    static constexpr int kPieces = 4 * kPlane + 2 * kDzPlane;
+};
+
+typedef short bf16x4_bits __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) bf16x4_bits lds_bf16x4;
+
+// One MFMA operand fragment: 16 voxels x 32 channels, voxel 8 (lane / 32) + k
+// of channel lane % 32 in element k.  at: the lane's byte address for the
+// first voxel (see wgrad_lane_offset).
+__device__ __forceinline__ bf16x8 read_fragment(const char* at) {
+    const bf16x4_bits lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4*)at);
+    const bf16x4_bits hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4*)(at + 4 * 64));
+    typedef short s8 __attribute__((ext_vector_type(8)));
+    const s8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// Byte offset of the lane's part of a fragment in [voxel][32 channels] data.
+__device__ __forceinline__ int wgrad_lane_offset(int lane) {
+    return (8 * (lane >> 5) + ((lane & 15) >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+}
+
+template <int NCO, int NCI, int TY>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) conv3_wgrad_kernel(const WgradArgs a) {
+    using T = WgradTile<NCO, NCI, TY>;
+    extern __shared__ uint4 s_tile[];
+    uint4* const s_x = s_tile;                  // ring of 4 planes
+    uint4* const s_dz = s_tile + 4 * T::kPlane; // ring of 2 planes
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int cin = a.c1 + a.c2;
+    const int nci = (cin + 32 * NCI - 1) / (32 * NCI), nco = a.cout / (32 * NCO);
+    const int task = blockIdx.x % (nci * nco), chunk = blockIdx.x / (nci * nco);
+    const int ci0 = (task % nci) * 32 * NCI, co0 = (task / nci) * 32 * NCO;
+    const int tiles_x = (a.W + kTX - 1) / kTX, tiles_y = (a.H + TY - 1) / TY;
+    const long units = (long)tiles_x * tiles_y * a.D;
+    const long u0 = units * chunk / a.chunks, u1 = units * (chunk + 1) / a.chunks;
+
+    f32x16 acc[7][NCO][NCI];
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+#pragma unroll
+        for (int o = 0; o < NCO; ++o)
+#pragma unroll
+            for (int i = 0; i < NCI; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[q][o][i][e] = 0.0f;
+
+    // 16-byte pieces straight to LDS, 64 a wave instruction; what lies outside
+    // the domain or the channels reads zeros
+    auto put = [&](uint4* to, const uint16_t* src) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+    };
+    auto load_x = [&](int x0, int y0, int z) {
+        uint4* const plane = s_x + (z & 3) * T::kPlane;
+        for (int bt = wave; bt < T::kPlane / 64; bt += 4) {
+            const int sl = bt / (T::kSlab / 64);
+            const int i = (bt - sl * (T::kSlab / 64)) * 64 + lane;
+            const int vx = i >> 2, hy = vx / kHaloX, hx = vx - hy * kHaloX;
+            const int x = x0 + hx - 1, y = y0 + hy - 1, c = ci0 + 32 * sl + 8 * (i & 3);
+            const long vox = ((long)z * a.H + y) * a.W + x;
+            const uint16_t* src = c < a.c1 ? a.x1 + vox * a.c1 + c : a.x2 + vox * a.c2 + (c - a.c1);
+            const bool in = hy < T::kRows && c < cin && x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
+            put(plane + bt * 64, in ? src : reinterpret_cast<const uint16_t*>(dn_zero16));
+        }
+    };
+    auto load_dz = [&](int x0, int y0, int z) {
+        uint4* const plane = s_dz + (z & 1) * T::kDzPlane;
+        for (int bt = wave; bt < T::kDzPlane / 64; bt += 4) {
+            const int sl = bt / (T::kDzSlab / 64);
+            const int i = (bt - sl * (T::kDzSlab / 64)) * 64 + lane;
+            const int vx = i >> 2, x = x0 + (vx & 31), y = y0 + (vx >> 5);
+            const uint16_t* src = a.dz + (((long)z * a.H + y) * a.W + x) * a.cout + co0 + 32 * sl + 8 * (i & 3);
+            put(plane + bt * 64, x < a.W && y < a.H && z < a.D ? src : reinterpret_cast<const uint16_t*>(dn_zero16));
+        }
+    };
+    const char* const lane_x = (const char*)s_x + wgrad_lane_offset(lane);
+    const char* const lane_dz = (const char*)s_dz + wgrad_lane_offset(lane);
+    const bool bias_wave = wave == 3;
+    bf16x8 ones;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) ones[k] = (__bf16)1.0f;
+
+    int x0 = 0, y0 = 0;
+    for (long u = u0; u < u1; ++u) {
+        const int z = (int)(u % a.D);
+        if (u == u0 || z == 0) {  // a new tile: its first planes
+            const long tile = u / a.D;
+            x0 = (int)(tile % tiles_x) * kTX;
+            y0 = (int)(tile / tiles_x) * TY;
+            __syncthreads();
+            load_x(x0, y0, z - 1);
+            load_x(x0, y0, z);
+            load_x(x0, y0, z + 1);
+            load_dz(x0, y0, z);
+        }
+        wait_loads();
+        __syncthreads();  // this unit's planes are there, the last one's are no longer read
+        if (z + 1 < a.D && u + 1 < u1) {
+            load_x(x0, y0, z + 2);
+            load_dz(x0, y0, z + 1);
+        }
+        const char* tap_at[7];
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+            const int t = min(7 * wave + q, 26);
+            const int tz = t / 9, ty = (t / 3) % 3, tx = t % 3;
+            tap_at[q] = lane_x + (((z + tz - 1) & 3) * T::kPlane * 16 + (ty * kHaloX + tx) * 64);
+        }
+        const char* const dz_at = lane_dz + (z & 1) * T::kDzPlane * 16;
+#pragma unroll 1
+        for (int r = 0; r < TY; ++r) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                bf16x8 av[NCO];
+#pragma unroll
+                for (int o = 0; o < NCO; ++o)
+                    av[o] = read_fragment(dz_at + r * (kTX * 64) + o * (T::kDzSlab * 16) + h * (16 * 64));
+#pragma unroll
+                for (int q = 0; q < 7; ++q)
+#pragma unroll
+                    for (int i = 0; i < NCI; ++i) {
+                        bf16x8 bv = read_fragment(tap_at[q] + r * (kHaloX * 64) + i * (T::kSlab * 16) + h * (16 * 64));
+                        if (q == 6 && bias_wave) bv = ones;
+#pragma unroll
+                        for (int o = 0; o < NCO; ++o)
+                            acc[q][o][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[o], bv, acc[q][o][i], 0, 0, 0);
+                    }
+            }
+        }
+    }
+    // element e of lane l: row (output channel) 8 (e / 4) + 4 (l / 32) + e % 4,
+    // column (input channel) l % 32
+    const int n = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int q = 0; q < 7; ++q) {
+        const int t = 7 * wave + q;
+#pragma unroll
+        for (int o = 0; o < NCO; ++o)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int co = co0 + 32 * o + 8 * (e >> 2) + 4 * half + (e & 3);
+                if (t == 27) {  // every column holds the sum over the chunk's voxels
+                    if (a.db && ci0 == 0 && n == 0) {
+                        if (a.partial) a.partial_b[(long)chunk * a.cout + co] = acc[q][o][0][e];
+                        else atomicAdd(&a.db[co], acc[q][o][0][e]);
+                    }
+                    continue;
+                }
+#pragma unroll
+                for (int i = 0; i < NCI; ++i) {
+                    const int ci = ci0 + 32 * i + n;
+                    if (ci >= cin) continue;
+                    const long at = ((long)co * 27 + t) * cin + ci;
+                    if (a.partial) a.partial[(long)chunk * a.cout * 27 * cin + at] = acc[q][o][i][e];
+                    else atomicAdd(&a.dw[at], acc[q][o][i][e]);
+                }
+            }
+    }
+}
+
+// The 1x1x1 weight gradient (the head): one wave per 32 x 32 channels and
+// chunk of rows; the same chunk's bias gradient from the first input tile.
+__global__ void __launch_bounds__(256) conv1_wgrad_kernel(const WgradArgs a) {
     const int lane = threadIdx.x & 63;
     const long wave = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    constexpr int taps = KS * KS * KS;
     const int cin = a.c1 + a.c2;
     const int ntco = a.cout / 32, ntci = (cin + 31) / 32;
     const long nrows = (long)a.D * a.H;
-    const long nchunks = (nrows + a.rows_per_wave - 1) / a.rows_per_wave;
-    const long ntasks = (long)ntco * ntci * taps * nchunks;
-    if (wave >= ntasks) return;
+    if (wave >= (long)ntco * ntci * a.chunks) return;
     const int cot = (int)(wave % ntco);
-    long rest = wave / ntco;
-    const int cit = (int)(rest % ntci);
-    rest /= ntci;
-    const int t = (int)(rest % taps);
-    const long chunk = rest / taps;
-    const int dz = t / (KS * KS) - KS / 2, dy = (t / KS) % KS - KS / 2, dx = t % KS - KS / 2;
+    const int cit = (int)((wave / ntco) % ntci);
+    const long chunk = wave / ((long)ntco * ntci);
     const int m = lane & 31, half = lane >> 5;
     const int co = cot * 32 + m;
     const int ci = cit * 32 + m;
@@ -1006,72 +1191,61 @@ __global__ void __launch_bounds__(256) conv_wgrad_kernel(const WgradArgs a) {
     const uint16_t* xs = ci < a.c1 ? a.x1 : a.x2;
     const int xc = ci < a.c1 ? a.c1 : a.c2;
     const int xci = ci < a.c1 ? ci : ci - a.c1;
-    f32x16 acc;
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-    const long r0 = chunk * a.rows_per_wave;
-    const long r1 = r0 + a.rows_per_wave < nrows ? r0 + a.rows_per_wave : nrows;
+    f32x16 acc, accb;
+    for (int r = 0; r < 16; ++r) acc[r] = accb[r] = 0.0f;
+    bf16x8 ones;
+    for (int k = 0; k < 8; ++k) ones[k] = (__bf16)1.0f;
+    const long r0 = nrows * chunk / a.chunks, r1 = nrows * (chunk + 1) / a.chunks;
     for (long row = r0; row < r1; ++row) {
-        const int zz = (int)(row / a.H), yy = (int)(row % a.H);
-        const int z = zz + dz, y = yy + dy;
-        const bool row_ok = z >= 0 && z < a.D && y >= 0 && y < a.H;
-        const long vrow = row * a.W;                    // first voxel of the output row
-        const long srow = ((long)z * a.H + y) * a.W;    // first voxel of the shifted input row
+        const long vrow = row * a.W;
         for (int x0 = 0; x0 < a.W; x0 += 16) {
             bf16x8 av, bv;
+#pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int x = x0 + 8 * half + i;
                 const bool xin = x < a.W;
                 const uint16_t g = xin ? a.dz[(vrow + x) * a.cout + co] : (uint16_t)0;
-                const int xs_ = x + dx;
-                const bool sin = row_ok && xin && ci_ok && xs_ >= 0 && xs_ < a.W;
-                const uint16_t v = sin ? xs[(srow + xs_) * xc + xci] : (uint16_t)0;
+                const uint16_t v = xin && ci_ok ? xs[(vrow + x) * xc + xci] : (uint16_t)0;
                 av[i] = __builtin_bit_cast(__bf16, g);
                 bv[i] = __builtin_bit_cast(__bf16, v);
             }
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
+            accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ones, accb, 0, 0, 0);
         }
     }
-    const int n = cit * 32 + m;  // input channel (column)
-    if (n < cin) {
-        for (int r = 0; r < 16; ++r) {
-            const int mm = cot * 32 + 8 * (r >> 2) + 4 * half + (r & 3);  // output channel (row)
-            if (a.partial)
-                a.partial[((chunk * a.cout + mm) * taps + t) * cin + n] = acc[r];
-            else
-                atomicAdd(&a.dw[((long)mm * taps + t) * cin + n], acc[r]);
+    for (int r = 0; r < 16; ++r) {
+        const int mm = cot * 32 + 8 * (r >> 2) + 4 * half + (r & 3);  // output channel (row)
+        if (a.db && cit == 0 && m == 0) {
+            if (a.partial) a.partial_b[chunk * a.cout + mm] = accb[r];
+            else atomicAdd(&a.db[mm], accb[r]);
         }
+        if (!ci_ok) continue;
+        if (a.partial) a.partial[(chunk * a.cout + mm) * cin + ci] = acc[r];
+        else atomicAdd(&a.dw[(long)mm * cin + ci], acc[r]);
     }
 }
 
-// db[c] += sum over voxels of dz[v][c]; with `partial`, block b stores its
-// sum in partial[b][c] instead (summed in a fixed order afterwards)
-__global__ void bias_grad_kernel(const uint16_t* __restrict__ dz, float* __restrict__ db, size_t nvox, int c,
-                                 float* __restrict__ partial) {
-    __shared__ float part[256];
-    const int ch = blockIdx.y;
+// dw[i] += sum over p = 0 .. chunks-1, in that order, of partial[p][i], and
+// the same for db: 16 loads in flight per thread.
+__global__ void sum_partials_kernel(const float* __restrict__ partial, float* __restrict__ dw, size_t nw,
+                                    const float* __restrict__ partial_b, float* __restrict__ db, int nb, int chunks) {
+    const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    const bool bias = i >= nw;
+    if (i >= nw + nb) return;
+    const float* src = bias ? partial_b + (i - nw) : partial + i;
+    const size_t stride = bias ? (size_t)nb : nw;
     float s = 0.0f;
-    for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < nvox; v += (size_t)gridDim.x * blockDim.x)
-        s += bf2f(dz[v * c + ch]);
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) part[threadIdx.x] += part[threadIdx.x + h];
-        __syncthreads();
+    int p = 0;
+    for (; p + 16 <= chunks; p += 16) {
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = src[(size_t)(p + k) * stride];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) s += v[k];
     }
-    if (threadIdx.x == 0) {
-        if (partial) partial[(size_t)blockIdx.x * c + ch] = part[0];
-        else atomicAdd(&db[ch], part[0]);
-    }
-}
-
-// out[i] += sum over p = 0 .. nparts-1, in that order, of partial[p][i]
-__global__ void sum_partials_kernel(const float* __restrict__ partial, float* __restrict__ out, size_t n,
-                                    int nparts) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (int p = 0; p < nparts; ++p) s += partial[(size_t)p * n + i];
-        out[i] += s;
-    }
+    for (; p < chunks; ++p) s += src[(size_t)p * stride];
+    if (bias) db[i - nw] += s;
+    else dw[i] += s;
 }
 
 // ---------------------------------------------------------------------------
@@ -1484,16 +1658,19 @@ rt3d_status rt3d_dn_flip_weights(const uint16_t* w, uint16_t* wt, int32_t cout, 
 
 namespace {
 
-// Launch plan of the weight gradient: the (output tile, input tile, tap)
-// tasks are split over row chunks so that about 4096 waves are in flight.
+// Launch plan of the weight gradient: the voxels are split into chunks so
+// that the (chunk, channel tile) workgroups fill the CUs once (one workgroup
+// per CU holds the accumulators), but no more chunks than there are units of
+// work.
 struct WgradPlan {
     WgradArgs a;
-    long chunks, waves;
-    int taps;
+    int taps, tasks;      // channel tiles
+    int nco, nci;         // 32-channel tiles of a workgroup (3x3x3)
     size_t nw;            // cout * taps * cin
-    unsigned bias_blocks; // blocks per channel of the bias gradient
     size_t ws_bytes;      // workspace of the deterministic variant
 };
+
+constexpr long kWgradWorkgroups = 256;
 
 bool wgrad_plan(const rt3d_dn_conv* c, WgradPlan* p) {
     if (!c || c->up1) return false;
@@ -1502,49 +1679,63 @@ bool wgrad_plan(const rt3d_dn_conv* c, WgradPlan* p) {
     WgradArgs& a = p->a;
     a.cout = c->cout; a.c1 = c->c1; a.c2 = c->c2;
     a.D = c->D; a.H = c->H; a.W = c->W;
-    a.partial = nullptr;
+    a.partial = a.partial_b = nullptr;
     p->taps = c->ksize * c->ksize * c->ksize;
-    const long base_tasks = (long)(c->cout / 32) * ((c->c1 + c->c2 + 31) / 32) * p->taps;
-    const long nrows = (long)c->D * c->H;
-    long chunks = 4096 / base_tasks;
-    if (chunks < 1) chunks = 1;
-    if (chunks > nrows) chunks = nrows;
-    a.rows_per_wave = (int)((nrows + chunks - 1) / chunks);
-    p->chunks = (nrows + a.rows_per_wave - 1) / a.rows_per_wave;
-    p->waves = base_tasks * p->chunks;
+    const int tco = c->cout / 32, tci = (c->c1 + c->c2 + 31) / 32;
+    long units, most;
+    if (c->ksize == 3) {
+        // two output tiles share each input fragment where there are two;
+        // else up to three input tiles share each output fragment
+        p->nco = tco % 2 == 0 ? 2 : 1;
+        p->nci = p->nco == 2 ? 1 : tci % 3 == 0 ? 3 : tci % 2 == 0 ? 2 : 1;
+        p->tasks = (tco / p->nco) * (tci / p->nci);
+        const int ty = p->nci == 3 ? 2 : 4;
+        units = (long)((c->W + kTX - 1) / kTX) * ((c->H + ty - 1) / ty) * c->D;
+        most = kWgradWorkgroups / p->tasks;
+    } else {
+        p->nco = p->nci = 1;
+        p->tasks = tco * tci;
+        units = (long)c->D * c->H;
+        most = 4096 / p->tasks;
+    }
+    if (most < 1) most = 1;
+    a.chunks = (int)(units < most ? units : most);
     p->nw = (size_t)c->cout * p->taps * (c->c1 + c->c2);
-    const size_t nvox = (size_t)c->D * c->H * c->W;
-    p->bias_blocks = blocks_for(nvox, 256, 256);
-    p->ws_bytes = ((p->chunks * p->nw * sizeof(float) + 255) / 256) * 256 +
-                  (size_t)p->bias_blocks * c->cout * sizeof(float);
+    p->ws_bytes = ((a.chunks * p->nw * sizeof(float) + 255) / 256) * 256 + (size_t)a.chunks * c->cout * sizeof(float);
     return true;
+}
+
+template <int NCO, int NCI, int TY>
+rt3d_status wgrad3_launch(const WgradPlan& plan, const WgradArgs& a, hipStream_t st) {
+    constexpr size_t lds = sizeof(uint4) * WgradTile<NCO, NCI, TY>::kPieces;
+    hipLaunchKernelGGL((conv3_wgrad_kernel<NCO, NCI, TY>), dim3((unsigned)(plan.tasks * a.chunks)), dim3(256), lds, st, a);
+    DN_TRY(hipGetLastError());
+    return RT3D_OK;
 }
 
 rt3d_status wgrad_run(const rt3d_dn_conv* c, const WgradPlan& plan, const uint16_t* x1, const uint16_t* x2,
                       const uint16_t* dz, float* dw, float* db, float* part_w, float* part_b, hipStream_t st) {
     WgradArgs a = plan.a;
-    a.dz = dz; a.x1 = x1; a.x2 = x2; a.dw = dw; a.partial = part_w;
-    const unsigned blocks = (unsigned)((plan.waves + 3) / 4);
-    if (c->ksize == 3)
-        hipLaunchKernelGGL(conv_wgrad_kernel<3>, dim3(blocks), dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL(conv_wgrad_kernel<1>, dim3(blocks), dim3(256), 0, st, a);
-    DN_TRY(hipGetLastError());
-    if (part_w) {
-        hipLaunchKernelGGL(sum_partials_kernel, dim3(blocks_for(plan.nw)), dim3(256), 0, st, part_w, dw, plan.nw,
-                           (int)plan.chunks);
+    a.dz = dz; a.x1 = x1; a.x2 = x2; a.dw = dw; a.db = db; a.partial = part_w; a.partial_b = part_b;
+    rt3d_status r = RT3D_OK;
+    if (c->ksize == 1) {
+        hipLaunchKernelGGL(conv1_wgrad_kernel, dim3((unsigned)((plan.tasks * a.chunks + 3) / 4)), dim3(256), 0, st, a);
         DN_TRY(hipGetLastError());
+    } else if (plan.nco == 2) {
+        r = wgrad3_launch<2, 1, 4>(plan, a, st);
+    } else if (plan.nci == 3) {
+        r = wgrad3_launch<1, 3, 2>(plan, a, st);
+    } else if (plan.nci == 2) {
+        r = wgrad3_launch<1, 2, 4>(plan, a, st);
+    } else {
+        r = wgrad3_launch<1, 1, 4>(plan, a, st);
     }
-    if (db) {
-        const size_t nvox = (size_t)c->D * c->H * c->W;
-        hipLaunchKernelGGL(bias_grad_kernel, dim3(plan.bias_blocks, c->cout), dim3(256), 0, st, dz, db, nvox,
-                           c->cout, part_b);
+    if (r != RT3D_OK) return r;
+    if (part_w) {
+        const int nb = db ? c->cout : 0;
+        hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((plan.nw + nb + 255) / 256)), dim3(256), 0, st, part_w,
+                           dw, plan.nw, part_b, db, nb, a.chunks);
         DN_TRY(hipGetLastError());
-        if (part_b) {
-            hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, st, part_b, db, (size_t)c->cout,
-                               (int)plan.bias_blocks);
-            DN_TRY(hipGetLastError());
-        }
     }
     return RT3D_OK;
 }
@@ -1572,7 +1763,7 @@ rt3d_status rt3d_dn_conv3d_wgrad_ws(const rt3d_dn_conv* c, const uint16_t* x1, c
     if (!x1 || !dz || !dw || (c && c->c2 > 0 && !x2) || !wgrad_plan(c, &plan)) return RT3D_EINVAL;
     if (!workspace || workspace_bytes < plan.ws_bytes || ((uintptr_t)workspace & 255)) return RT3D_EINVAL;
     float* part_w = (float*)workspace;
-    float* part_b = (float*)((char*)workspace + ((plan.chunks * plan.nw * sizeof(float) + 255) / 256) * 256);
+    float* part_b = (float*)((char*)workspace + ((plan.a.chunks * plan.nw * sizeof(float) + 255) / 256) * 256);
     return wgrad_run(c, plan, x1, x2, dz, dw, db, part_w, part_b, (hipStream_t)stream);
 }
 
