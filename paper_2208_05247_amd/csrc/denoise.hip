@@ -13,10 +13,10 @@
 // with 8 channels of one voxel (zero outside the domain) and the B operand
 // with 8 input channels of one output channel's weights.  The accumulator of
 // lane l, element r holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-// 3x3x3 layers run from an input halo staged in LDS (conv3_tiled_kernel,
-// conv3_c32_kernel, conv3_c4_kernel); the 1x1x1 head uses conv_fwd_kernel,
+// 3x3x3 layers run from an input halo staged in LDS (conv3_kernel,
+// conv3_c4_kernel); the 1x1x1 head uses conv_fwd_kernel,
 // one wave per 32 x 32 output tile with its operands read directly, or in
-// inference runs inside conv3_c32_kernel after the last 3x3x3 layer.
+// inference runs inside conv3_kernel after the last 3x3x3 layer.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -85,6 +85,9 @@ struct ConvArgs {
     const float* hb;       // [32] or null
     float* hy;
     int hcols;
+    // conv3_kernel: first output channel and number of channel slabs of this
+    // launch; BF16 output only, in 16-byte pieces
+    int co_base, slabs, store16;
 };
 
 template <int KS>
@@ -142,63 +145,108 @@ __global__ void __launch_bounds__(256) conv_fwd_kernel(const ConvArgs a) {
     }
 }
 
-// Tiled 3x3x3 convolution.  A workgroup (4 waves) owns an output tile of
-// kZ z-slices x kTY y-rows x kTX x-voxels and a slab of up to 64 output
-// channels.  For each 16-channel input chunk the
-// ((kZ+2) x (kTY+2) x (kTX+2))-voxel input halo is loaded straight into LDS
-// once (zero outside the domain), so a staged plane serves kZ output planes;
-// every wave then runs the 27 taps over its 2 rows x 2 cout tiles in each output
-// plane: A fragments are contiguous 1 KiB rows of the staged halo, B
-// fragments (weights) come from global memory, where the small weight
-// tensor stays cache resident, one tap ahead of their use, and each is used
-// by 2 kZ MFMAs.
-constexpr int kTY = 8, kTX = 32, kZ = 2;
-constexpr int kHaloY = kTY + 2, kHaloX = kTX + 2;
-constexpr int kHaloVox = (kZ + 2) * kHaloY * kHaloX;
+constexpr int kTX = 32;           // voxels of an output row: the rows of an MFMA
+constexpr int kHaloX = kTX + 2;
+constexpr int kTY32 = 16;         // output rows of the first layer's workgroups
+constexpr int kHaloY32 = kTY32 + 2;
 
-// Stages the input halo of one 16-channel chunk, planes z0-1 .. z0+NZ and
-// rows y0-1 .. y0+HY-2 of columns x0-1 .. x0+kTX, into LDS as two 16-byte
-// halves per voxel (slot 2 v + part), with NT threads.  The loads go
-// straight to LDS (global_load_lds_dwordx4: lane l of a wave writes its 16
-// bytes at the wave's LDS base + 16 l, checked on the device), so no
-// registers hold the data and all of a chunk's loads are in flight at once.
-// Slots are filled in batches of 64, one wave instruction each; the tile
-// holds a whole number of batches (tile_slots), and slots outside the domain
-// or past the halo read the 16-byte zero block.  The caller waits for the
-// loads (vmcnt) before the barrier that publishes the tile.
 constexpr int tile_slots_of(int pieces) { return (pieces + 63) / 64 * 64; }
 constexpr int tile_slots(int halo_vox) { return tile_slots_of(halo_vox * 2); }
 
-template <int NZ, int HY, int NT>
-__device__ __forceinline__ void stage_halo16_lds(uint4* tile, const ConvArgs& a, int c0, int x0, int y0, int z0) {
-    constexpr int kSlots = NZ * HY * kHaloX * 2, kBatches = (kSlots + 63) / 64, kWaves = NT / 64;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// Stages the input halo of one 16-channel chunk, planes z0-1 .. z0+NZ-2 and
+// rows y0-1 .. y0+HY-2 of columns x0-1 .. x0+kTX, into LDS as two 16-byte
+// halves per voxel (slot 2 v + part).  The 32 inner voxels of a row are one
+// load straight to LDS (global_load_lds_dwordx4: lane l of a wave writes its
+// 16 bytes at the wave's LDS base + 16 l, checked on the device): the row's
+// place is the same for the whole wave, so an address is a scalar plus the
+// lane's own offset (decoded per 16-byte piece it was 28 vector instructions
+// per load, and staging a fifth of the convolution's time).  The two outer
+// voxels of each row go through registers.  What lies outside the domain reads
+// the 16-byte zero block.  The caller waits for the loads (vmcnt) before the
+// barrier that publishes the tile.
+template <int NZ, int HY>
+__device__ __forceinline__ void stage_halo16(uint4* tile, const ConvArgs& a, int c0, int x0, int y0, int z0, int wave,
+                                             int lane) {
+    constexpr int kRows = NZ * HY;
     const bool from1 = c0 < a.c1;
-    const uint16_t* base = from1 ? a.x1 + c0 : a.x2 + (c0 - a.c1);
-    const long cs = from1 ? a.c1 : a.c2;
-    const bool half_res = from1 && a.up1;
-    for (int bt = wave; bt < kBatches; bt += kWaves) {
-        const int i = bt * 64 + lane;
-        const int vx = i >> 1, part = i & 1;
-        const int hx = vx % kHaloX, hy = (vx / kHaloX) % HY, hz = vx / (kHaloX * HY);
-        const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
-        const bool in = i < kSlots && x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
-        const long vox = half_res ? ((long)(z >> 1) * (a.H >> 1) + (y >> 1)) * (a.W >> 1) + (x >> 1)
-                                  : ((long)z * a.H + y) * a.W + x;
-        const uint16_t* src = in ? base + vox * cs + 8 * part : reinterpret_cast<const uint16_t*>(dn_zero16);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                         (__attribute__((address_space(3))) void*)(tile + bt * 64), 16, 0, 0);
+    const uint16_t* const base = from1 ? a.x1 + c0 : a.x2 + (c0 - a.c1);
+    const int cs = from1 ? a.c1 : a.c2;
+    const int hr = from1 && a.up1 ? 1 : 0;  // half resolution
+    const int h = a.H >> hr, w = a.W >> hr;
+    const uint16_t* const zero = reinterpret_cast<const uint16_t*>(dn_zero16);
+    // outer voxels: piece i = 4 row + 2 side + half
+    for (int i = wave * 64 + lane; i < 4 * kRows; i += 256) {
+        const int row = i >> 2, side = (i >> 1) & 1, part = i & 1;
+        const int x = side ? x0 + kTX : x0 - 1, y = y0 + row % HY - 1, z = z0 + row / HY - 1;
+        const bool in = x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
+        const uint16_t* src = in ? base + (((long)(z >> hr) * h + (y >> hr)) * w + (x >> hr)) * cs + 8 * part : zero;
+        tile[(row * kHaloX + (side ? kHaloX - 1 : 0)) * 2 + part] = *reinterpret_cast<const uint4*>(src);
+    }
+    const int x = x0 + (lane >> 1);
+    const uint32_t lane_at = (uint32_t)((x >> hr) * cs + 8 * (lane & 1));
+    for (int row = wave; row < kRows; row += 4) {
+        const int y = y0 + row % HY - 1, z = z0 + row / HY - 1;
+        const bool in = y >= 0 && y < a.H && z >= 0 && z < a.D && x < a.W;
+        const uint16_t* const at = base + ((long)(z >> hr) * h + (y >> hr)) * w * cs;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(in ? at + lane_at : zero),
+                                         (__attribute__((address_space(3))) void*)(tile + (row * kHaloX + 1) * 2), 16, 0,
+                                         0);
     }
 }
 
 __device__ __forceinline__ void wait_loads() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) conv3_tiled_kernel(const ConvArgs a) {
-    __shared__ uint4 tile[tile_slots(kHaloVox)];  // 16 channels = two 16-byte halves per voxel
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// Weights through a buffer resource: a 32-bit lane offset and a scalar offset
+// per load.  (As 64-bit addresses the 27 taps' take 54 vector registers.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_resource(const uint16_t* w, long n) {
+    const long bytes = 2 * n;
+    return __builtin_amdgcn_make_buffer_rsrc((void*)w, 0, (int)(uint32_t)(bytes < 0xffffffffL ? bytes : 0xffffffffL),
+                                             0x00027000);
+}
+
+__device__ __forceinline__ uint4 load_weights(__amdgpu_buffer_rsrc_t r, uint32_t lane, uint32_t uniform) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane, (int)uniform, 0));
+}
+
+// Tiled 3x3x3 convolution.  A workgroup (4 waves) owns an output tile of kZ
+// z-slices x kRows y-rows x 32 voxels and NCT x 32 output channels (NCT 1: 16
+// rows, 4 a wave; NCT 2: 8 rows, a wave has 4 of them and one of the two
+// channel tiles).  For each 16-channel input chunk the
+// (kZ+2) x (kRows+2) x 34-voxel halo is loaded straight into LDS.  Per z-slice
+// of the kernel a wave keeps its 9 weight fragments in registers (the next
+// slice's are loaded meanwhile), walks the 6 staged input rows its outputs need
+// in both planes that slice reaches, 3 x-shifts each, and feeds every fragment
+// it reads from LDS to all (up to 3) of its output rows that use it: half an
+// LDS read and an eighth of a weight load per MFMA.  All LDS offsets are
+// constants from one lane address.
+// What bounds it (128 -> 64 and 64 -> 64 channels, 44x90x118 voxels, the launch
+// alone): 425 us when every wave loaded both channel tiles' weights (8.8 TB/s
+// from the L2; 291 with the loads left out), 354 in this split, 332 with
+// stage_halo16; about 60 of those are staging that the CU's other workgroup does not hide.
+// The matrix cores themselves sustain 1.6-1.8 PFLOP/s on such operands.
+// With a head (ConvArgs::hw, NCT 1) the
+// 1x1x1 convolution follows in the epilogue and only its output is stored.
+constexpr int kZ = 2;
+
+template <int NCT>
+struct ConvTile {
+    static constexpr int kRows = 16 / NCT, kHaloY = kRows + 2;
+    static constexpr int kHaloVox = (kZ + 2) * kHaloY * kHaloX;
+};
+// the fused head reuses the halo tile: 4 waves x kZ x 4 rows x 32 x 32 BF16
+// activations, then per wave one output row of 32 voxels x 2 FP32
+static_assert(4 * kZ * 4 * 32 * 32 * 2 <= ConvTile<1>::kHaloVox * 2 * 16, "head scratch exceeds the halo tile");
+constexpr int kHeadOutOffset = 4 * kZ * 4 * 32 * 32 * 2;  // bytes
+static_assert(kHeadOutOffset + 4 * 32 * 2 * 4 <= ConvTile<1>::kHaloVox * 2 * 16, "head output scratch exceeds the halo tile");
+
+template <int NCT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) conv3_kernel(const ConvArgs a) {
+    using T = ConvTile<NCT>;
+    __shared__ uint4 tile[tile_slots(T::kHaloVox)];  // 16 channels = two 16-byte halves per voxel
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int m = lane & 31, half = lane >> 5;
-    const int nslab = (a.cout + 63) / 64;
-    const int tiles_x = (a.W + kTX - 1) / kTX, tiles_y = (a.H + kTY - 1) / kTY;
+    const int nslab = a.slabs;
+    const int tiles_x = (a.W + kTX - 1) / kTX, tiles_y = (a.H + T::kRows - 1) / T::kRows;
     long b = blockIdx.x;
     const int slab = (int)(b % nslab);
     b /= nslab;
@@ -206,205 +254,55 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
     b /= tiles_x;
     const int tyi = (int)(b % tiles_y);
     const int z0 = (int)(b / tiles_y) * kZ;
-    const int x0 = txi * kTX, y0 = tyi * kTY;
-    const int co0 = slab * 64;
-    const int nct = min(2, (a.cout - co0) / 32);
+    const int x0 = txi * kTX, y0 = tyi * T::kRows;
     const int cin = a.c1 + a.c2;
-    const int row0 = 2 * wave;  // rows row0, row0 + 1 of the tile
-    f32x16 acc[kZ][2][2];
+    const int row0 = 4 * (wave / NCT);
+    const int n0 = a.co_base + 32 * (slab * NCT + wave % NCT);  // this wave's 32 output channels
+    f32x16 acc[kZ][4];
 #pragma unroll
     for (int oz = 0; oz < kZ; ++oz)
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[oz][r][ct][e] = 0.0f;
-
-    // weight fragments of (chunk c, tap t) for this lane's output channels;
-    // the next tap's are loaded before the current tap's MFMAs run, so their
-    // latency hides behind them (branch-free: past the last chunk or channel
-    // tile the address is clamped in bounds and the fragment is never used)
-    auto load_b = [&](int c, int t, uint4* out) {
-        const int cc = min(c, cin - 16);
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-            const int co = min(co0 + 32 * ct + m, a.cout - 1);
-            out[ct] = *(const uint4*)(a.w + ((long)co * 27 + t) * cin + cc + 8 * half);
-        }
-    };
-    uint4 bv[2];
-    load_b(0, 0, bv);
-    for (int c0 = 0; c0 < cin; c0 += 16) {
-        __syncthreads();  // the previous chunk's halo is no longer read
-        stage_halo16_lds<kZ + 2, kHaloY, 256>(tile, a, c0, x0, y0, z0);
-        wait_loads();
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < 27; ++t) {
-            const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-            uint4 bn[2];
-            if (t < 26) load_b(c0, t + 1, bn);
-            else load_b(c0 + 16, 0, bn);
-            __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
-#pragma unroll
-            for (int oz = 0; oz < kZ; ++oz)
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    // output plane oz reads staged plane oz + dz
-                    const uint4 av = tile[(((oz + dz) * kHaloY + row0 + r + dy) * kHaloX + m + dx) * 2 + half];
-#pragma unroll
-                    for (int ct = 0; ct < 2; ++ct)
-                        if (ct < nct)
-                            acc[oz][r][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                as_bf16x8(av), as_bf16x8(bv[ct]), acc[oz][r][ct], 0, 0, 0);
-                }
-            bv[0] = bn[0];
-            bv[1] = bn[1];
-        }
-    }
-    if (!a.yf && a.y1 && a.o1 == a.cout && nct == 2) {
-        // BF16 output through LDS, as in conv3_c4_kernel: each wave writes
-        // one output row of its slab (32 voxels x 64 channels, 4 KiB) to its
-        // own slice of the halo tile and stores it as 16-byte pieces (8
-        // channels of one voxel), 4 per lane, instead of 2-byte stores
-        static_assert(4 * 32 * 64 * 2 <= tile_slots(kHaloVox) * 16, "row scratch exceeds the halo tile");
-        __syncthreads();  // every wave is done reading the halo
-        uint16_t* row = reinterpret_cast<uint16_t*>(tile) + wave * (32 * 64);
-        float bias[2];
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) bias[ct] = a.bias ? a.bias[co0 + 32 * ct + m] : 0.0f;
-#pragma unroll
-        for (int oz = 0; oz < kZ; ++oz) {
-            const int zz = z0 + oz;
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int y = y0 + row0 + r;
-#pragma unroll
-                for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        float v = acc[oz][r][ct][e] + bias[ct];
-                        if (a.relu) v = fmaxf(v, 0.0f);
-                        row[(8 * (e >> 2) + 4 * half + (e & 3)) * 64 + 32 * ct + m] = f2bf(v);
-                    }
-                // LDS instructions of one wave complete in order; the barrier
-                // keeps the compiler from moving the reads across the writes
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int q = it * 64 + lane;  // voxel q / 8, channels co0 + 8 (q % 8) ..
-                    const int x = x0 + (q >> 3);
-                    const uint4 v = *reinterpret_cast<const uint4*>(row + (q >> 3) * 64 + 8 * (q & 7));
-                    if (zz < a.D && y < a.H && x < a.W)
-                        *reinterpret_cast<uint4*>(a.y1 + (((long)zz * a.H + y) * a.W + x) * a.cout + co0 + 8 * (q & 7)) = v;
-                }
-                __builtin_amdgcn_wave_barrier();  // the next row's writes follow these reads
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int oz = 0; oz < kZ; ++oz) {
-        const int zz = z0 + oz;
-        if (zz >= a.D) continue;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int y = y0 + row0 + r;
-            if (y >= a.H) continue;
-#pragma unroll
-            for (int ct = 0; ct < 2; ++ct) {
-                if (ct >= nct) continue;
-                const int n = co0 + 32 * ct + m;
-                const float bias = a.bias ? a.bias[n] : 0.0f;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int x = x0 + 8 * (e >> 2) + 4 * half + (e & 3);
-                    if (x >= a.W) continue;
-                    float v = acc[oz][r][ct][e] + bias;
-                    if (a.relu) v = fmaxf(v, 0.0f);
-                    const long vox = ((long)zz * a.H + y) * a.W + x;
-                    if (a.yf && n < a.yf_cols) a.yf[vox * a.yf_cols + n] = v;
-                    if (n < a.o1) {
-                        if (a.y1) a.y1[vox * a.o1 + n] = f2bf(v);
-                    } else if (a.y2) {
-                        a.y2[vox * (a.cout - a.o1) + (n - a.o1)] = f2bf(v);
-                    }
-                }
-            }
-        }
-    }
-}
-
-// 3x3x3 convolution with exactly 32 output channels (one MFMA column tile,
-// so an input fragment cannot be shared between output-channel tiles).
-// Instead each wave owns 4 output rows in each of the workgroup's 2 output
-// z-slices and, per z-slice of the kernel, keeps its 9 weight fragments of
-// the current 16-channel chunk in registers: it walks the 6 staged input
-// rows its outputs need in both input planes that kernel slice reaches,
-// 3 x-shifts each, and feeds every fragment it reads from LDS to all (up
-// to 3) of its output rows that use it.  Workgroup tile: 2 z x 16 rows x
-// 32 voxels, so a staged input plane serves two output planes (4 planes
-// staged per 2 outputs instead of 3 per 1).  With a head (ConvArgs::hw) the
-// 1x1x1 convolution follows in the epilogue and only its output is stored.
-constexpr int kTY32 = 16;
-constexpr int kHaloY32 = kTY32 + 2;
-constexpr int kZ32 = 2;
-constexpr int kHaloVox32 = (kZ32 + 2) * kHaloY32 * kHaloX;
-// the fused head reuses the halo tile: 4 waves x kZ32 x 4 rows x 32 x 32 BF16
-// activations, then per wave one output row of 32 voxels x 2 FP32
-static_assert(4 * kZ32 * 4 * 32 * 32 * 2 <= kHaloVox32 * 2 * 16, "head scratch exceeds the halo tile");
-constexpr int kHeadOutOffset = 4 * kZ32 * 4 * 32 * 32 * 2;  // bytes
-static_assert(kHeadOutOffset + 4 * 32 * 2 * 4 <= kHaloVox32 * 2 * 16, "head output scratch exceeds the halo tile");
-
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) conv3_c32_kernel(const ConvArgs a) {
-    __shared__ uint4 tile[tile_slots(kHaloVox32)];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int m = lane & 31, half = lane >> 5;
-    const int tiles_x = (a.W + kTX - 1) / kTX, tiles_y = (a.H + kTY32 - 1) / kTY32;
-    long b = blockIdx.x;
-    const int txi = (int)(b % tiles_x);
-    b /= tiles_x;
-    const int tyi = (int)(b % tiles_y);
-    const int z0 = (int)(b / tiles_y) * kZ32;
-    const int x0 = txi * kTX, y0 = tyi * kTY32;
-    const int cin = a.c1 + a.c2;
-    const int row0 = 4 * wave;
-    f32x16 acc[kZ32][4];
-#pragma unroll
-    for (int oz = 0; oz < kZ32; ++oz)
 #pragma unroll
         for (int o = 0; o < 4; ++o)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[oz][o][e] = 0.0f;
 
+    const auto wres = weight_resource(a.w + (long)n0 * 27 * cin, 32L * 27 * cin);
+    const uint32_t lane_w = (uint32_t)(m * 27 * cin + 8 * half) * 2;
+    // the 9 weight fragments of (chunk c, z-slice dz); past the last chunk the
+    // address is clamped and the fragments are never used
+    auto load_b = [&](int c, int dz, uint4* out) {
+        const int cc = min(c, cin - 16);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) out[t] = load_weights(wres, lane_w, (uint32_t)((dz * 9 + t) * cin + cc) * 2);
+    };
+    const uint4* const at = tile + (row0 * kHaloX + m) * 2 + half;
+    uint4 bnext[9];
+    load_b(0, 0, bnext);
     for (int c0 = 0; c0 < cin; c0 += 16) {
-        __syncthreads();
-        stage_halo16_lds<kZ32 + 2, kHaloY32, 256>(tile, a, c0, x0, y0, z0);
+        __syncthreads();  // the previous chunk's halo is no longer read
+        stage_halo16<kZ + 2, T::kHaloY>(tile, a, c0, x0, y0, z0, wave, lane);
         wait_loads();
         __syncthreads();
+#pragma unroll
         for (int dz = 0; dz < 3; ++dz) {
-            // the 9 weight fragments of this z-slice of the kernel
             uint4 bv[9];
 #pragma unroll
-            for (int t = 0; t < 9; ++t)
-                bv[t] = *(const uint4*)(a.w + ((long)m * 27 + dz * 9 + t) * cin + c0 + 8 * half);
-            // the 12 staged rows (2 output planes x 6 input rows) this wave
-            // reads for this kernel slice, each as 3 x-shifted fragments; the
-            // fragments of the next row are read before this row's MFMAs
+            for (int t = 0; t < 9; ++t) bv[t] = bnext[t];
+            if (dz < 2) load_b(c0, dz + 1, bnext);
+            else load_b(c0 + 16, 0, bnext);
+            // the fragments of the next row are read before this row's MFMAs
             // run, so the LDS latency hides behind them
             auto row_frags = [&](int step, uint4* av) {
                 const int oz = step / 6, r = step % 6;  // output plane oz reads staged plane oz + dz
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
-                    av[dx] = tile[(((oz + dz) * kHaloY32 + row0 + r) * kHaloX + m + dx) * 2 + half];
+                for (int dx = 0; dx < 3; ++dx) av[dx] = at[(((oz + dz) * T::kHaloY + r) * kHaloX + dx) * 2];
             };
-            uint4 cur[3], nxt[3];
-            row_frags(0, cur);
+            uint4 av[2][3];
+            row_frags(0, av[0]);
 #pragma unroll
-            for (int step = 0; step < kZ32 * 6; ++step) {
+            for (int step = 0; step < kZ * 6; ++step) {
                 const int oz = step / 6, r = step % 6;
-                if (step + 1 < kZ32 * 6) row_frags(step + 1, nxt);
+                if (step + 1 < kZ * 6) row_frags(step + 1, av[(step + 1) & 1]);
                 // keeps the scheduler from hoisting the reads of later rows
                 // ahead of these MFMAs (it would spill at 2 waves/SIMD)
                 __builtin_amdgcn_sched_barrier(0);
@@ -415,26 +313,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
                         const int dy = r - o;  // output row o reads halo row o + dy
                         if (dy >= 0 && dy <= 2)
                             acc[oz][o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                as_bf16x8(cur[dx]), as_bf16x8(bv[dy * 3 + dx]), acc[oz][o], 0, 0, 0);
+                                as_bf16x8(av[step & 1][dx]), as_bf16x8(bv[dy * 3 + dx]), acc[oz][o], 0, 0, 0);
                     }
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx) cur[dx] = nxt[dx];
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
     const int n = m;
-    const float bias = a.bias ? a.bias[n] : 0.0f;
-    if (a.hw) {
+    const float bias = a.bias ? a.bias[n0 + m] : 0.0f;
+    if (NCT == 1 && a.hw) {
         // Fused head.  Each wave writes its BF16 activations, 32 voxels x 32
         // channels per output row, to its own part of the (no longer needed)
         // halo tile, so that a lane can read the 8 consecutive channels of
         // one voxel that the A operand takes; the head then runs the same
         // two MFMAs per row as the 1x1x1 convolution kernel, in the same
         // order, so its output is bitwise that of the unfused pair.
-        uint16_t* ht = reinterpret_cast<uint16_t*>(tile) + wave * (kZ32 * 4 * 32 * 32);
+        uint16_t* ht = reinterpret_cast<uint16_t*>(tile) + wave * (kZ * 4 * 32 * 32);
         __syncthreads();  // every wave is done reading the halo
 #pragma unroll
-        for (int oz = 0; oz < kZ32; ++oz)
+        for (int oz = 0; oz < kZ; ++oz)
 #pragma unroll
             for (int o = 0; o < 4; ++o)
 #pragma unroll
@@ -449,7 +346,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
         for (int c = 0; c < 2; ++c) hwv[c] = *(const uint4*)(a.hw + m * 32 + 16 * c + 8 * half);
         const float hbias = a.hb ? a.hb[n] : 0.0f;
 #pragma unroll
-        for (int oz = 0; oz < kZ32; ++oz) {
+        for (int oz = 0; oz < kZ; ++oz) {
             const int zz = z0 + oz;
             if (zz >= a.D) continue;
 #pragma unroll
@@ -497,8 +394,48 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
         }
         return;
     }
+    if (a.store16) {
+        // BF16 output through LDS: a lane holds one channel of 16 voxels, so
+        // direct stores would be 2 bytes each; each wave instead writes one
+        // output row (32 voxels x 32 channels, 2 KiB) to its own slice of the
+        // halo tile and stores it as 16-byte pieces (8 channels of one voxel),
+        // 2 per lane.  The 32 channels lie in y1 or in y2 (o1 is a multiple
+        // of 32).
+        static_assert(4 * 32 * 32 * 2 <= tile_slots(T::kHaloVox) * 16, "row scratch exceeds the halo tile");
+        __syncthreads();  // every wave is done reading the halo
+        uint16_t* row = reinterpret_cast<uint16_t*>(tile) + wave * (32 * 32);
+        uint16_t* const dst = n0 < a.o1 ? a.y1 + n0 : a.y2 + (n0 - a.o1);
+        const int stride = n0 < a.o1 ? a.o1 : a.cout - a.o1;
 #pragma unroll
-    for (int oz = 0; oz < kZ32; ++oz) {
+        for (int oz = 0; oz < kZ; ++oz) {
+            const int zz = z0 + oz;
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                const int y = y0 + row0 + o;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    float v = acc[oz][o][e] + bias;
+                    if (a.relu) v = fmaxf(v, 0.0f);
+                    row[(8 * (e >> 2) + 4 * half + (e & 3)) * 32 + m] = f2bf(v);
+                }
+                // LDS instructions of one wave complete in order; the barrier
+                // keeps the compiler from moving the reads across the writes
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    const int q = it * 64 + lane;  // voxel q / 4, channels 8 (q % 4) ..
+                    const int x = x0 + (q >> 2);
+                    const uint4 v = *reinterpret_cast<const uint4*>(row + (q >> 2) * 32 + 8 * (q & 3));
+                    if (zz < a.D && y < a.H && x < a.W)
+                        *reinterpret_cast<uint4*>(dst + (((long)zz * a.H + y) * a.W + x) * stride + 8 * (q & 3)) = v;
+                }
+                __builtin_amdgcn_wave_barrier();  // the next row's writes follow these reads
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int oz = 0; oz < kZ; ++oz) {
         const int zz = z0 + oz;
         if (zz >= a.D) continue;
 #pragma unroll
@@ -512,11 +449,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
                 float v = acc[oz][o][e] + bias;
                 if (a.relu) v = fmaxf(v, 0.0f);
                 const long vox = ((long)zz * a.H + y) * a.W + x;
-                if (a.yf && n < a.yf_cols) a.yf[vox * a.yf_cols + n] = v;
-                if (n < a.o1) {
-                    if (a.y1) a.y1[vox * a.o1 + n] = f2bf(v);
+                const int c = n0 + m;
+                if (a.yf && c < a.yf_cols) a.yf[vox * a.yf_cols + c] = v;
+                if (c < a.o1) {
+                    if (a.y1) a.y1[vox * a.o1 + c] = f2bf(v);
                 } else if (a.y2) {
-                    a.y2[vox * (a.cout - a.o1) + (n - a.o1)] = f2bf(v);
+                    a.y2[vox * (a.cout - a.o1) + (c - a.o1)] = f2bf(v);
                 }
             }
         }
@@ -528,7 +466,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
 // holds the three x-taps of one (z, y) tap pair: A = channels 0-3 of voxels
 // x-1, x, x+1 and four zeros, B = the matching 12 weights and four zeros, so
 // a row takes 9 MFMAs instead of 27 of 16 mostly-zero channels.  Tile and
-// reuse as in conv3_c32_kernel (16 rows x 32 voxels, 4 rows per wave, every
+// reuse as in conv3_kernel (16 rows x 32 voxels, 4 rows per wave, every
 // staged input row fed to all output rows that use it).
 constexpr int kHaloVoxC4 = 3 * kHaloY32 * kHaloX;
 
@@ -806,7 +744,7 @@ conv3_c4_pool_kernel(const ConvArgs a, uint16_t* __restrict__ yp) {
 // x, 0-4 of voxel x+1 and the zero (the B operand the matching weights, taken
 // from the 16-channel weight rows w[co][t][16]).  Pooling as in
 // conv3_c4_pool_kernel; bitwise equal to the unpacked first layer
-// (conv3_c32_kernel on 16-channel features) only up to the order of the
+// (conv3_kernel on 16-channel features) only up to the order of the
 // products within a K-chunk, as the packed 4-channel layer is.
 constexpr int kHaloVoxC5P = 4 * kHaloY32 * kHaloX;
 
@@ -1557,6 +1495,17 @@ __global__ void unfeature_kernel(const float* __restrict__ pred, float scale, si
 // ===========================================================================
 // C ABI (include/rt3d_denoise.h)
 // ===========================================================================
+namespace {
+
+// Workgroups of conv3_kernel<NCT> per channel slab.
+template <int NCT>
+long conv3_tiles(const rt3d_dn_conv* c) {
+    constexpr int rows = ConvTile<NCT>::kRows;
+    return (long)((c->D + kZ - 1) / kZ) * ((c->H + rows - 1) / rows) * ((c->W + kTX - 1) / kTX);
+}
+
+}  // namespace
+
 extern "C" {
 
 const char* rt3d_dn_last_error(void) { return d_err; }
@@ -1600,19 +1549,27 @@ rt3d_status rt3d_dn_conv3d_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const 
     a.up1 = c->up1 ? 1 : 0;
     a.yf_cols = c->yf_cols ? c->yf_cols : c->cout;
     a.hw = nullptr; a.hb = nullptr; a.hy = nullptr; a.hcols = 0;
+    a.co_base = 0; a.slabs = 1; a.store16 = 0;
     if (four) {
         const long tiles = (long)c->D * ((c->H + kTY32 - 1) / kTY32) * ((c->W + kTX - 1) / kTX);
         if (tiles > 0x7fffffffL) return RT3D_EINVAL;
         hipLaunchKernelGGL(conv3_c4_kernel, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
-    } else if (c->ksize == 3 && c->cout == 32) {
-        const long tiles = (long)((c->D + kZ32 - 1) / kZ32) * ((c->H + kTY32 - 1) / kTY32) * ((c->W + kTX - 1) / kTX);
-        if (tiles > 0x7fffffffL) return RT3D_EINVAL;
-        hipLaunchKernelGGL(conv3_c32_kernel, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
     } else if (c->ksize == 3) {
-        const long tiles =
-            (long)((c->D + kZ - 1) / kZ) * ((c->H + kTY - 1) / kTY) * ((c->W + kTX - 1) / kTX) * ((c->cout + 63) / 64);
-        if (tiles > 0x7fffffffL) return RT3D_EINVAL;
-        hipLaunchKernelGGL(conv3_tiled_kernel, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
+        a.store16 = y1 && !yf && ((uintptr_t)y1 | (uintptr_t)(o1 < c->cout ? y2 : nullptr)) % 16 == 0;
+        // 64 output channels per workgroup; 32 that are left over by themselves
+        const int wide = c->cout / 64, narrow = (c->cout / 32) % 2;
+        const long tiles = conv3_tiles<2>(c) * wide, rest = conv3_tiles<1>(c) * narrow;
+        if (tiles > 0x7fffffffL || rest > 0x7fffffffL) return RT3D_EINVAL;
+        if (wide) {
+            a.slabs = wide;
+            hipLaunchKernelGGL(conv3_kernel<2>, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
+            DN_TRY(hipGetLastError());
+        }
+        if (narrow) {
+            a.co_base = 64 * wide;
+            a.slabs = 1;
+            hipLaunchKernelGGL(conv3_kernel<1>, dim3((unsigned)rest), dim3(256), 0, (hipStream_t)stream, a);
+        }
     } else {
         const long waves = (long)c->D * c->H * ((c->W + 31) / 32) * (c->cout / 32);
         const unsigned blocks = (unsigned)((waves + 3) / 4);
@@ -1637,9 +1594,10 @@ rt3d_status rt3d_dn_conv3d_fwd_head(const rt3d_dn_conv* c, const uint16_t* x1, c
     a.up1 = c->up1 ? 1 : 0;
     a.yf_cols = 32;
     a.hw = hw; a.hb = hb; a.hy = hy; a.hcols = hcols;
-    const long tiles = (long)((c->D + kZ32 - 1) / kZ32) * ((c->H + kTY32 - 1) / kTY32) * ((c->W + kTX - 1) / kTX);
+    a.co_base = 0; a.slabs = 1; a.store16 = 0;
+    const long tiles = conv3_tiles<1>(c);
     if (tiles > 0x7fffffffL) return RT3D_EINVAL;
-    hipLaunchKernelGGL(conv3_c32_kernel, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(conv3_kernel<1>, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
     DN_TRY(hipGetLastError());
     return RT3D_OK;
 }
