@@ -137,6 +137,18 @@ rt3d_status rt3d_dn_pool2(const uint16_t* x, uint16_t* y, int32_t D, int32_t H, 
 rt3d_status rt3d_dn_up2(const uint16_t* x, uint16_t* y, int32_t D, int32_t H, int32_t W, int32_t C,
                         int32_t backward, void* stream);
 
+/* Two steps of the backward pass in one launch each, bitwise the calls in
+ * turn; C a multiple of 8, device pointers 16-byte aligned (else RT3D_EINVAL).
+ * rt3d_dn_up2_relu_bwd: rt3d_dn_up2 backward of dy [2D][2H][2W][C], then
+ * rt3d_dn_relu_bwd through act [D][H][W][C], into dx.
+ * rt3d_dn_pool2_add_relu_bwd: rt3d_dn_pool2 backward of dy
+ * [D/2][H/2][W/2][C], rt3d_dn_add of de [D][H][W][C], rt3d_dn_relu_bwd through
+ * act, into dx (which may be de). */
+rt3d_status rt3d_dn_up2_relu_bwd(const uint16_t* dy, const uint16_t* act, uint16_t* dx, int32_t D, int32_t H, int32_t W,
+                                 int32_t C, void* stream);
+rt3d_status rt3d_dn_pool2_add_relu_bwd(const uint16_t* dy, const uint16_t* de, const uint16_t* act, uint16_t* dx,
+                                       int32_t D, int32_t H, int32_t W, int32_t C, void* stream);
+
 /* Residual head and squared-error loss: pred[v][c] = out[v][c] + base[v][c]
  * for c < nout (out is FP32 [vox][cpad], base/target/pred FP32 [vox][nout]);
  * if target != NULL: *loss += sum (pred - target)^2 (FP64) and dout[v][c] =

@@ -70,6 +70,8 @@ def load():
         "rt3d_dn_add": [P, P, P, U, P],
         "rt3d_dn_pool2": [P, P, I, I, I, I, I, P],
         "rt3d_dn_up2": [P, P, I, I, I, I, I, P],
+        "rt3d_dn_up2_relu_bwd": [P, P, P, I, I, I, I, P],
+        "rt3d_dn_pool2_add_relu_bwd": [P, P, P, P, I, I, I, I, P],
         "rt3d_dn_mse": [P, I, P, P, I, U, P, P, P, P],
         "rt3d_dn_adam": [P, P, P, P, P, U, ctypes.c_float, ctypes.c_float, ctypes.c_float, ctypes.c_float, I, P],
         "rt3d_dn_to_bf16": [P, P, U, P],
@@ -220,6 +222,21 @@ def up2(x, backward=False, out=None):
     else:
         D, H, W, C = out.shape
     _check(load().rt3d_dn_up2(_p(x), _p(out), D, H, W, C, int(backward), _s()), "rt3d_dn_up2")
+    return out
+
+
+def up2_relu_bwd(dy, act, out):
+    """up2 backward and relu_bwd through act in one launch."""
+    D, H, W, C = out.shape
+    _check(load().rt3d_dn_up2_relu_bwd(_p(dy), _p(act), _p(out), D, H, W, C, _s()), "rt3d_dn_up2_relu_bwd")
+    return out
+
+
+def pool2_add_relu_bwd(dy, de, act, out):
+    """pool2 backward, the sum with de and relu_bwd through act in one launch."""
+    D, H, W, C = out.shape
+    _check(load().rt3d_dn_pool2_add_relu_bwd(_p(dy), _p(de), _p(act), _p(out), D, H, W, C, _s()),
+           "rt3d_dn_pool2_add_relu_bwd")
     return out
 
 
@@ -379,9 +396,7 @@ class Denoiser:
         """dout: BF16 [D][H][W][32] gradient at the head output.  Fills the
         FP32 gradients (cleared first)."""
         a = self.acts
-        for k in self.g:
-            self.g[k].zero_()
-            self.gbias[k].zero_()
+        torch._foreach_zero_([*self.g.values(), *self.gbias.values()])
         like = lambda t: torch.empty_like(t)
         self._wgrad("head", a["d0"], None, dout)
         dd0 = like(a["d0"])
@@ -390,36 +405,27 @@ class Denoiser:
         self._wgrad("d0", a["u0"], a["e0"], dd0)
         du0, de0 = like(a["u0"]), like(a["e0"])
         self._data_grad("d0", dd0, du0, de0)
-        dd1 = up2(du0, backward=True, out=like(a["d1"]))
-        relu_bwd(dd1, a["d1"], dd1)
+        dd1 = up2_relu_bwd(du0, a["d1"], like(a["d1"]))
         self._wgrad("d1", a["u1"], a["e1"], dd1)
         du1, de1 = like(a["u1"]), like(a["e1"])
         self._data_grad("d1", dd1, du1, de1)
-        dd2 = up2(du1, backward=True, out=like(a["d2"]))
-        relu_bwd(dd2, a["d2"], dd2)
+        dd2 = up2_relu_bwd(du1, a["d2"], like(a["d2"]))
         self._wgrad("d2", a["u2"], a["e2"], dd2)
         du2, de2 = like(a["u2"]), like(a["e2"])
         self._data_grad("d2", dd2, du2, de2)
-        db_ = up2(du2, backward=True, out=like(a["b"]))
-        relu_bwd(db_, a["b"], db_)
+        db_ = up2_relu_bwd(du2, a["b"], like(a["b"]))
         self._wgrad("b", a["p2"], None, db_)
         dp2 = like(a["p2"])
         self._data_grad("b", db_, dp2)
-        t = pool2(dp2, backward=True, out=like(a["e2"]))
-        add(de2, t, de2)
-        relu_bwd(de2, a["e2"], de2)
+        pool2_add_relu_bwd(dp2, de2, a["e2"], de2)
         self._wgrad("e2", a["p1"], None, de2)
         dp1 = like(a["p1"])
         self._data_grad("e2", de2, dp1)
-        t = pool2(dp1, backward=True, out=like(a["e1"]))
-        add(de1, t, de1)
-        relu_bwd(de1, a["e1"], de1)
+        pool2_add_relu_bwd(dp1, de1, a["e1"], de1)
         self._wgrad("e1", a["p0"], None, de1)
         dp0 = like(a["p0"])
         self._data_grad("e1", de1, dp0)
-        t = pool2(dp0, backward=True, out=like(a["e0"]))
-        add(de0, t, de0)
-        relu_bwd(de0, a["e0"], de0)
+        pool2_add_relu_bwd(dp0, de0, a["e0"], de0)
         self._wgrad("e0", a["x0"], None, de0)
         del self.acts
 
