@@ -18,9 +18,11 @@ def make(g, shape, shift):
     n = 1
     for v in shape:
         n *= v
-    t = torch.randn(n + shift, generator=g).to(torch.bfloat16).cuda()
-    t[::7] = 0
-    return t[shift:].view(shape)
+    v = torch.randn(n, generator=g).to(torch.bfloat16).cuda()
+    v[::7] = 0
+    t = torch.empty(n + shift, dtype=torch.bfloat16, device="cuda")[shift:]
+    t.copy_(v)
+    return t.view(shape)
 
 
 @pytest.mark.parametrize("D,H,W,C", [(2, 2, 2, 8), (1, 1, 1, 32), (3, 5, 7, 24), (4, 2, 6, 64), (2, 3, 33, 40)])
