@@ -145,6 +145,18 @@ __global__ void __launch_bounds__(256) conv_fwd_kernel(const ConvArgs a) {
     }
 }
 
+// Loads from memory that may be the 16-byte zero block.  The compiler loses the
+// address space where a pointer is selected, and a flat load in its place also
+// counts as a read of LDS: it waits for every load into LDS in flight.
+typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 load_global8(const void* p) {
+    return __builtin_bit_cast(uint2, *(const __attribute__((address_space(1))) uint2v*)p);
+}
+__device__ __forceinline__ uint4 load_global16(const void* p) {
+    return __builtin_bit_cast(uint4, *(const __attribute__((address_space(1))) uint4v*)p);
+}
+
 constexpr int kTX = 32;           // voxels of an output row: the rows of an MFMA
 constexpr int kHaloX = kTX + 2;
 constexpr int kTY32 = 16;         // output rows of the first layer's workgroups
@@ -152,6 +164,8 @@ constexpr int kHaloY32 = kTY32 + 2;
 
 constexpr int tile_slots_of(int pieces) { return (pieces + 63) / 64 * 64; }
 constexpr int tile_slots(int halo_vox) { return tile_slots_of(halo_vox * 2); }
+
+__device__ __forceinline__ void wait_loads() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Stages the input halo of one 16-channel chunk, planes z0-1 .. z0+NZ-2 and
 // rows y0-1 .. y0+HY-2 of columns x0-1 .. x0+kTX, into LDS as two 16-byte
@@ -161,40 +175,55 @@ constexpr int tile_slots(int halo_vox) { return tile_slots_of(halo_vox * 2); }
 // place is the same for the whole wave, so an address is a scalar plus the
 // lane's own offset (decoded per 16-byte piece it was 28 vector instructions
 // per load, and staging a fifth of the convolution's time).  The two outer
-// voxels of each row go through registers.  What lies outside the domain reads
-// the 16-byte zero block.  The caller waits for the loads (vmcnt) before the
-// barrier that publishes the tile.
+// voxels of each row go through registers, their loads in flight together with
+// the others.  What lies outside the domain reads the 16-byte zero block.  The
+// caller's barrier afterwards publishes the tile.
 template <int NZ, int HY>
-__device__ __forceinline__ void stage_halo16(uint4* tile, const ConvArgs& a, int c0, int x0, int y0, int z0, int wave,
-                                             int lane) {
-    constexpr int kRows = NZ * HY;
-    const bool from1 = c0 < a.c1;
-    const uint16_t* const base = from1 ? a.x1 + c0 : a.x2 + (c0 - a.c1);
-    const int cs = from1 ? a.c1 : a.c2;
-    const int hr = from1 && a.up1 ? 1 : 0;  // half resolution
-    const int h = a.H >> hr, w = a.W >> hr;
-    const uint16_t* const zero = reinterpret_cast<const uint16_t*>(dn_zero16);
-    // outer voxels: piece i = 4 row + 2 side + half
-    for (int i = wave * 64 + lane; i < 4 * kRows; i += 256) {
-        const int row = i >> 2, side = (i >> 1) & 1, part = i & 1;
-        const int x = side ? x0 + kTX : x0 - 1, y = y0 + row % HY - 1, z = z0 + row / HY - 1;
-        const bool in = x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
-        const uint16_t* src = in ? base + (((long)(z >> hr) * h + (y >> hr)) * w + (x >> hr)) * cs + 8 * part : zero;
-        tile[(row * kHaloX + (side ? kHaloX - 1 : 0)) * 2 + part] = *reinterpret_cast<const uint4*>(src);
-    }
-    const int x = x0 + (lane >> 1);
-    const uint32_t lane_at = (uint32_t)((x >> hr) * cs + 8 * (lane & 1));
-    for (int row = wave; row < kRows; row += 4) {
-        const int y = y0 + row % HY - 1, z = z0 + row / HY - 1;
-        const bool in = y >= 0 && y < a.H && z >= 0 && z < a.D && x < a.W;
-        const uint16_t* const at = base + ((long)(z >> hr) * h + (y >> hr)) * w * cs;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(in ? at + lane_at : zero),
-                                         (__attribute__((address_space(3))) void*)(tile + (row * kHaloX + 1) * 2), 16, 0,
-                                         0);
-    }
-}
+struct Halo16 {
+    static constexpr int kRows = NZ * HY;
+    static constexpr int kOuter = (4 * kRows + 255) / 256;  // outer pieces a lane moves: i = 4 row + 2 side + half
+    const uint16_t* base;
+    int cs, hr, h, w;  // channels, 1 at half resolution, extent there
+    uint4 outer[kOuter];
 
-__device__ __forceinline__ void wait_loads() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+    // Before the barrier after which the tile may be overwritten.
+    __device__ __forceinline__ void load_outer(const ConvArgs& a, int c0, int x0, int y0, int z0) {
+        const bool from1 = c0 < a.c1;
+        base = from1 ? a.x1 + c0 : a.x2 + (c0 - a.c1);
+        cs = from1 ? a.c1 : a.c2;
+        hr = from1 && a.up1 ? 1 : 0;
+        h = a.H >> hr;
+        w = a.W >> hr;
+#pragma unroll
+        for (int k = 0; k < kOuter; ++k) {
+            const int i = (int)threadIdx.x + 256 * k, row = i >> 2, side = (i >> 1) & 1, part = i & 1;
+            const int x = side ? x0 + kTX : x0 - 1, y = y0 + row % HY - 1, z = z0 + row / HY - 1;
+            const bool in = row < kRows && x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
+            const uint16_t* src = base + (((long)(z >> hr) * h + (y >> hr)) * w + (x >> hr)) * cs + 8 * part;
+            outer[k] = load_global16(in ? src : reinterpret_cast<const uint16_t*>(dn_zero16));
+        }
+    }
+    // After it: the inner voxels, a wait for all loads, the outer voxels.
+    __device__ __forceinline__ void stage(uint4* tile, const ConvArgs& a, int x0, int y0, int z0, int wave, int lane) {
+        const uint16_t* const zero = reinterpret_cast<const uint16_t*>(dn_zero16);
+        const int x = x0 + (lane >> 1);
+        const uint32_t lane_at = (uint32_t)((x >> hr) * cs + 8 * (lane & 1));
+        for (int row = wave; row < kRows; row += 4) {
+            const int y = y0 + row % HY - 1, z = z0 + row / HY - 1;
+            const bool in = y >= 0 && y < a.H && z >= 0 && z < a.D && x < a.W;
+            const uint16_t* const at = base + ((long)(z >> hr) * h + (y >> hr)) * w * cs;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(in ? at + lane_at : zero),
+                                             (__attribute__((address_space(3))) void*)(tile + (row * kHaloX + 1) * 2), 16,
+                                             0, 0);
+        }
+        wait_loads();
+#pragma unroll
+        for (int k = 0; k < kOuter; ++k) {
+            const int i = (int)threadIdx.x + 256 * k, row = i >> 2, side = (i >> 1) & 1, part = i & 1;
+            if (row < kRows) tile[(row * kHaloX + (side ? kHaloX - 1 : 0)) * 2 + part] = outer[k];
+        }
+    }
+};
 
 // Weights through a buffer resource: a 32-bit lane offset and a scalar offset
 // per load.  (As 64-bit addresses the 27 taps' take 54 vector registers.)
@@ -222,7 +251,9 @@ __device__ __forceinline__ uint4 load_weights(__amdgpu_buffer_rsrc_t r, uint32_t
 // What bounds it (128 -> 64 and 64 -> 64 channels, 44x90x118 voxels, the launch
 // alone): 425 us when every wave loaded both channel tiles' weights (8.8 TB/s
 // from the L2; 291 with the loads left out), 354 in this split, 332 with
-// stage_halo16; about 60 of those are staging that the CU's other workgroup does not hide.
+// Halo16 (337 with its outer voxels waited for before its inner ones are
+// loaded); about 60 of those are staging that the CU's other workgroup does
+// not hide.
 // The matrix cores themselves sustain 1.6-1.8 PFLOP/s on such operands.
 // With a head (ConvArgs::hw, NCT 1) the
 // 1x1x1 convolution follows in the epilogue and only its output is stored.
@@ -279,9 +310,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
     uint4 bnext[9];
     load_b(0, 0, bnext);
     for (int c0 = 0; c0 < cin; c0 += 16) {
+        Halo16<kZ + 2, T::kHaloY> halo;
+        halo.load_outer(a, c0, x0, y0, z0);
         __syncthreads();  // the previous chunk's halo is no longer read
-        stage_halo16<kZ + 2, T::kHaloY>(tile, a, c0, x0, y0, z0, wave, lane);
-        wait_loads();
+        halo.stage(tile, a, x0, y0, z0, wave, lane);
         __syncthreads();
 #pragma unroll
         for (int dz = 0; dz < 3; ++dz) {
@@ -499,8 +531,8 @@ __global__ void __launch_bounds__(256) conv3_c4_kernel(const ConvArgs a) {
                 // a voxel outside the domain reads zeros from dn_zero16: the
                 // address is selected, so the load cannot sink into a branch
                 // (which would wait for it before the next one is issued)
-                vv[j] = *(in ? (const uint2*)(a.x1 + (((long)zc * a.H + yc) * a.W + xc) * 4)
-                             : reinterpret_cast<const uint2*>(dn_zero16));
+                vv[j] = load_global8(in ? a.x1 + (((long)zc * a.H + yc) * a.W + xc) * 4
+                                        : reinterpret_cast<const uint16_t*>(dn_zero16));
             }
 #pragma unroll
             for (int j = 0; j < SB; ++j) {
@@ -632,8 +664,8 @@ conv3_c4_pool_kernel(const ConvArgs a, uint16_t* __restrict__ yp) {
                 const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
                 const bool in = x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
                 const int xc = min(max(x, 0), a.W - 1), yc = min(max(y, 0), a.H - 1), zc = min(max(z, 0), a.D - 1);
-                vv[j] = *(in ? (const uint2*)(a.x1 + (((long)zc * a.H + yc) * a.W + xc) * 4)
-                             : reinterpret_cast<const uint2*>(dn_zero16));
+                vv[j] = load_global8(in ? a.x1 + (((long)zc * a.H + yc) * a.W + xc) * 4
+                                        : reinterpret_cast<const uint16_t*>(dn_zero16));
             }
 #pragma unroll
             for (int j = 0; j < SB; ++j) {
@@ -777,8 +809,8 @@ conv3_c5_pool_kernel(const ConvArgs a, uint16_t* __restrict__ yp) {
                 const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
                 const bool in = x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
                 const int xc = min(max(x, 0), a.W - 1), yc = min(max(y, 0), a.H - 1), zc = min(max(z, 0), a.D - 1);
-                vv[j] = *(in ? (const uint4*)(a.x1 + (((long)zc * a.H + yc) * a.W + xc) * 8)
-                             : reinterpret_cast<const uint4*>(dn_zero16));
+                vv[j] = load_global16(in ? a.x1 + (((long)zc * a.H + yc) * a.W + xc) * 8
+                                         : reinterpret_cast<const uint16_t*>(dn_zero16));
             }
 #pragma unroll
             for (int j = 0; j < SB; ++j) {
@@ -930,18 +962,24 @@ struct WgradArgs {
 // four voxels (lane l of the 16 addresses voxel l / 4, channels 4 (l % 4) ..;
 // checked on the device), so a fragment is two such reads and a tap's shift is
 // an address.
-// A workgroup of 4 waves owns NCO x 32 output and NCI x 32 input channels of
-// one chunk of the voxels; wave w accumulates taps 7 w .. 7 w + 6 (the 28th
-// slot multiplies dz with ones: the bias gradient).  The chunk is a range of
+// A workgroup of 8 waves owns NCO x 32 output and NCI x 32 input channels of
+// one chunk of the voxels.  Of the nine (z, y) rows of three taps each wave has
+// one; the three taps of the ninth, and dz times ones (the bias gradient), go
+// to waves 0-3, so that each SIMD has seven.  The chunk is a range of
 // (tile of TY x 32 voxels, plane) units, planes innermost: the input planes
 // z-1, z, z+1 of a tile stay in LDS, in a ring of four whose fourth plane
 // (and the next plane of dz) is loaded while this one is computed.
-// What bounds it: LDS reads (82 of 128 bytes a cycle with NCO = 2, at the
-// MFMAs' full rate) and MFMA issue, at one wave a SIMD.  Measured on 128^3
-// voxels: 96 -> 32 channels (NCI = 3) 0.91 ms, 381 TFLOP/s; 192 -> 64 at 64^3
-// (NCO = 2) 0.24 ms, 370 TFLOP/s.  With operands gathered from global memory
-// by 2-byte loads, a wave per (32 x 32 channels, tap), they took 3.8 and 1.0 ms
-// (32 -> 64 channels on 64x60x52 voxels, whole call: 394 us, now 70).
+// What bounds it: the latency of those loads, which the compiler's wait before
+// the next LDS read exposes (a third of the time; held in registers instead
+// they cost as much in addresses: 473 us against 430 in the first case below).
+// Measured on 128^3 voxels: 96 -> 32 channels (NCI = 3) 0.43 ms, 810 TFLOP/s;
+// 192 -> 64 at 64^3 (NCO = 2) 0.21 ms, 420 TFLOP/s; 16 -> 32 (NCI = 1, two
+// workgroups a CU) 0.14 ms, 0.19 with one.  With 4 waves of seven taps they
+// took 0.91, 0.24 and 0.22 ms: at 336 accumulators a lane, more than the 256
+// accumulation registers, the compiler moved them around every MFMA.  With
+// operands gathered from global memory by 2-byte loads, a wave per (32 x 32
+// channels, tap), 3.8 and 1.0 ms (32 -> 64 channels on 64x60x52 voxels, whole
+// call: 394 us, then 70, now 55).
 template <int NCO, int NCI, int TY>
 struct WgradTile {
     static constexpr int kRows = TY + 2;
@@ -955,15 +993,28 @@ struct WgradTile {
 typedef short bf16x4_bits __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4_bits lds_bf16x4;
 
+// Four voxels of the lane's channel (two registers of two BF16).  at: the
+// lane's byte address for the first voxel (see wgrad_lane_offset).
+__device__ __forceinline__ uint2 read_voxels(const char* at) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4*)at));
+}
+
 // One MFMA operand fragment: 16 voxels x 32 channels, voxel 8 (lane / 32) + k
-// of channel lane % 32 in element k.  at: the lane's byte address for the
-// first voxel (see wgrad_lane_offset).
+// of channel lane % 32 in element k.
 __device__ __forceinline__ bf16x8 read_fragment(const char* at) {
-    const bf16x4_bits lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4*)at);
-    const bf16x4_bits hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4*)(at + 4 * 64));
-    typedef short s8 __attribute__((ext_vector_type(8)));
-    const s8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, v);
+    const uint2 lo = read_voxels(at), hi = read_voxels(at + 4 * 64);
+    return as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y));
+}
+
+// The fragments of the three taps of a row, from one window of 12 voxels: the
+// second is the first moved on by one voxel (16 bits), the third by two (a
+// register).  Three reads instead of six.
+__device__ __forceinline__ void read_row(const char* at, bf16x8* out) {
+    const uint2 a = read_voxels(at), b = read_voxels(at + 4 * 64), c = read_voxels(at + 8 * 64);
+    out[0] = as_bf16x8(make_uint4(a.x, a.y, b.x, b.y));
+    out[1] = as_bf16x8(make_uint4(__builtin_amdgcn_alignbit(a.y, a.x, 16), __builtin_amdgcn_alignbit(b.x, a.y, 16),
+                                  __builtin_amdgcn_alignbit(b.y, b.x, 16), __builtin_amdgcn_alignbit(c.x, b.y, 16)));
+    out[2] = as_bf16x8(make_uint4(a.y, b.x, b.y, c.x));
 }
 
 // Byte offset of the lane's part of a fragment in [voxel][32 channels] data.
@@ -972,7 +1023,9 @@ __device__ __forceinline__ int wgrad_lane_offset(int lane) {
 }
 
 template <int NCO, int NCI, int TY>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) conv3_wgrad_kernel(const WgradArgs a) {
+__global__ void __launch_bounds__(512)
+    __attribute__((amdgpu_waves_per_eu(NCO * NCI == 1 ? 4 : 2, NCO * NCI == 1 ? 4 : 2)))
+    conv3_wgrad_kernel(const WgradArgs a) {
     using T = WgradTile<NCO, NCI, TY>;
     extern __shared__ uint4 s_tile[];
     uint4* const s_x = s_tile;                  // ring of 4 planes
@@ -986,9 +1039,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
     const long units = (long)tiles_x * tiles_y * a.D;
     const long u0 = units * chunk / a.chunks, u1 = units * (chunk + 1) / a.chunks;
 
-    f32x16 acc[7][NCO][NCI];
+    f32x16 acc[4][NCO][NCI];
 #pragma unroll
-    for (int q = 0; q < 7; ++q)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int o = 0; o < NCO; ++o)
 #pragma unroll
@@ -996,43 +1049,68 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[q][o][i][e] = 0.0f;
 
-    // 16-byte pieces straight to LDS, 64 a wave instruction; what lies outside
-    // the domain or the channels reads zeros
+    // 16-byte pieces straight to LDS, 64 a wave instruction (16 voxels x 32
+    // channels, of one row: a scalar address plus the lane's own offset); what
+    // lies outside the domain or the channels reads zeros
+    const uint16_t* const zero = reinterpret_cast<const uint16_t*>(dn_zero16);
     auto put = [&](uint4* to, const uint16_t* src) {
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                          (__attribute__((address_space(3))) void*)to, 16, 0, 0);
     };
+    const int part = lane & 3, vx = lane >> 2;  // of a piece within 16 voxels
     auto load_x = [&](int x0, int y0, int z) {
         uint4* const plane = s_x + (z & 3) * T::kPlane;
-        for (int bt = wave; bt < T::kPlane / 64; bt += 4) {
-            const int sl = bt / (T::kSlab / 64);
-            const int i = (bt - sl * (T::kSlab / 64)) * 64 + lane;
-            const int vx = i >> 2, hy = vx / kHaloX, hx = vx - hy * kHaloX;
-            const int x = x0 + hx - 1, y = y0 + hy - 1, c = ci0 + 32 * sl + 8 * (i & 3);
-            const long vox = ((long)z * a.H + y) * a.W + x;
-            const uint16_t* src = c < a.c1 ? a.x1 + vox * a.c1 + c : a.x2 + vox * a.c2 + (c - a.c1);
-            const bool in = hy < T::kRows && c < cin && x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
-            put(plane + bt * 64, in ? src : reinterpret_cast<const uint16_t*>(dn_zero16));
+        for (int k = wave; k < NCI * T::kRows * 2; k += 8) {
+            const int sl = k / (T::kRows * 2), hy = (k / 2) % T::kRows, j = k % 2;
+            const int c0 = ci0 + 32 * sl, y = y0 + hy - 1, x = x0 + 16 * j + vx;
+            const long row = ((long)z * a.H + y) * a.W + x0 + 16 * j;
+            const bool in = z >= 0 && z < a.D && y >= 0 && y < a.H && x < a.W;
+            const uint16_t* src;
+            if (c0 + 32 <= a.c1) {
+                src = a.x1 + row * a.c1 + c0 + (uint32_t)(vx * a.c1 + 8 * part);
+            } else if (c0 >= a.c1 && c0 + 32 <= cin) {
+                src = a.x2 + row * a.c2 + (c0 - a.c1) + (uint32_t)(vx * a.c2 + 8 * part);
+            } else {  // the two inputs meet in this slab, or it is not full
+                const int c = c0 + 8 * part;
+                src = c < a.c1 ? a.x1 + (row + vx) * a.c1 + c : a.x2 + (row + vx) * a.c2 + (c - a.c1);
+                if (c >= cin) src = zero;
+            }
+            put(plane + sl * T::kSlab + (hy * kHaloX + 1 + 16 * j) * 4, in ? src : zero);
         }
+    };
+    // the outer voxels of the rows, one piece a lane, through a register: read
+    // ahead, written (put_edge) once the plane's place in the ring is free
+    constexpr int kEdge = NCI * T::kRows * 8;
+    static_assert(kEdge <= 512, "one outer piece a lane");
+    const int e_sl = (int)threadIdx.x / (T::kRows * 8), e_hy = ((int)threadIdx.x / 8) % T::kRows;
+    const int e_side = ((int)threadIdx.x / 4) & 1, e_c = ci0 + 32 * e_sl + 8 * part;
+    auto get_edge = [&](int x0, int y0, int z) {
+        const int x = e_side ? x0 + kTX : x0 - 1, y = y0 + e_hy - 1;
+        const bool in = (int)threadIdx.x < kEdge && e_c < cin && x >= 0 && x < a.W && y >= 0 && y < a.H && z >= 0 && z < a.D;
+        const long vox = ((long)z * a.H + y) * a.W + x;
+        const uint16_t* src = e_c < a.c1 ? a.x1 + vox * a.c1 + e_c : a.x2 + vox * a.c2 + (e_c - a.c1);
+        return load_global16(in ? src : zero);
+    };
+    auto put_edge = [&](int z, uint4 v) {
+        if ((int)threadIdx.x < kEdge)
+            s_x[(z & 3) * T::kPlane + e_sl * T::kSlab + (e_hy * kHaloX + (e_side ? kHaloX - 1 : 0)) * 4 + part] = v;
     };
     auto load_dz = [&](int x0, int y0, int z) {
         uint4* const plane = s_dz + (z & 1) * T::kDzPlane;
-        for (int bt = wave; bt < T::kDzPlane / 64; bt += 4) {
-            const int sl = bt / (T::kDzSlab / 64);
-            const int i = (bt - sl * (T::kDzSlab / 64)) * 64 + lane;
-            const int vx = i >> 2, x = x0 + (vx & 31), y = y0 + (vx >> 5);
-            const uint16_t* src = a.dz + (((long)z * a.H + y) * a.W + x) * a.cout + co0 + 32 * sl + 8 * (i & 3);
-            put(plane + bt * 64, x < a.W && y < a.H && z < a.D ? src : reinterpret_cast<const uint16_t*>(dn_zero16));
+        for (int k = wave; k < NCO * TY * 2; k += 8) {
+            const int sl = k / (TY * 2), hy = (k / 2) % TY, j = k % 2;
+            const int y = y0 + hy, x = x0 + 16 * j + vx;
+            const uint16_t* src = a.dz + (((long)z * a.H + y) * a.W + x0 + 16 * j) * a.cout + co0 + 32 * sl +
+                                  (uint32_t)(vx * a.cout + 8 * part);
+            put(plane + sl * T::kDzSlab + (hy * kTX + 16 * j) * 4, x < a.W && y < a.H ? src : zero);
         }
     };
     const char* const lane_x = (const char*)s_x + wgrad_lane_offset(lane);
     const char* const lane_dz = (const char*)s_dz + wgrad_lane_offset(lane);
-    const bool bias_wave = wave == 3;
-    bf16x8 ones;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) ones[k] = (__bf16)1.0f;
 
     int x0 = 0, y0 = 0;
+    uint4 edge = make_uint4(0u, 0u, 0u, 0u);
+    bool ahead = false;  // the next plane's outer voxels are in `edge`
     for (long u = u0; u < u1; ++u) {
         const int z = (int)(u % a.D);
         if (u == u0 || z == 0) {  // a new tile: its first planes
@@ -1040,52 +1118,70 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
             x0 = (int)(tile % tiles_x) * kTX;
             y0 = (int)(tile / tiles_x) * TY;
             __syncthreads();
-            load_x(x0, y0, z - 1);
-            load_x(x0, y0, z);
-            load_x(x0, y0, z + 1);
+            for (int k = -1; k <= 1; ++k) {
+                load_x(x0, y0, z + k);
+                put_edge(z + k, get_edge(x0, y0, z + k));
+            }
             load_dz(x0, y0, z);
+        } else if (ahead) {
+            put_edge(z + 1, edge);  // (no wave has read that place since the last barrier)
         }
         wait_loads();
         __syncthreads();  // this unit's planes are there, the last one's are no longer read
-        if (z + 1 < a.D && u + 1 < u1) {
+        ahead = z + 1 < a.D && u + 1 < u1;
+        if (ahead) {
             load_x(x0, y0, z + 2);
             load_dz(x0, y0, z + 1);
+            edge = get_edge(x0, y0, z + 2);
         }
-        const char* tap_at[7];
-#pragma unroll
-        for (int q = 0; q < 7; ++q) {
-            const int t = min(7 * wave + q, 26);
-            const int tz = t / 9, ty = (t / 3) % 3, tx = t % 3;
-            tap_at[q] = lane_x + (((z + tz - 1) & 3) * T::kPlane * 16 + (ty * kHaloX + tx) * 64);
-        }
-        const char* const dz_at = lane_dz + (z & 1) * T::kDzPlane * 16;
+        // the wave's row of taps, and its tap of the ninth row
+        auto row_at = [&](int g) { return lane_x + ((z + g / 3 - 1) & 3) * (T::kPlane * 16) + g % 3 * (kHaloX * 64); };
+        const char* at_row = row_at(wave);
+        const char* at_tap = row_at(8) + (wave < 3 ? wave : 0) * 64;
+        const char* at_dz = lane_dz + (z & 1) * T::kDzPlane * 16;
 #pragma unroll 1
         for (int r = 0; r < TY; ++r) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 bf16x8 av[NCO];
 #pragma unroll
-                for (int o = 0; o < NCO; ++o)
-                    av[o] = read_fragment(dz_at + r * (kTX * 64) + o * (T::kDzSlab * 16) + h * (16 * 64));
+                for (int o = 0; o < NCO; ++o) av[o] = read_fragment(at_dz + o * (T::kDzSlab * 16) + h * (16 * 64));
 #pragma unroll
-                for (int q = 0; q < 7; ++q)
+                for (int i = 0; i < NCI; ++i) {
+                    bf16x8 bv[3];
+                    read_row(at_row + i * (T::kSlab * 16) + h * (16 * 64), bv);
 #pragma unroll
-                    for (int i = 0; i < NCI; ++i) {
-                        bf16x8 bv = read_fragment(tap_at[q] + r * (kHaloX * 64) + i * (T::kSlab * 16) + h * (16 * 64));
-                        if (q == 6 && bias_wave) bv = ones;
+                    for (int q = 0; q < 3; ++q)
 #pragma unroll
                         for (int o = 0; o < NCO; ++o)
-                            acc[q][o][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[o], bv, acc[q][o][i], 0, 0, 0);
+                            acc[q][o][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[o], bv[q], acc[q][o][i], 0, 0, 0);
+                }
+                if (wave < 4) {
+#pragma unroll
+                    for (int i = 0; i < NCI; ++i) {
+                        bf16x8 bv = read_fragment(at_tap + i * (T::kSlab * 16) + h * (16 * 64));
+                        if (wave == 3) {
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) bv[k] = (__bf16)1.0f;
+                        }
+#pragma unroll
+                        for (int o = 0; o < NCO; ++o)
+                            acc[3][o][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[o], bv, acc[3][o][i], 0, 0, 0);
                     }
+                }
             }
+            at_row += kHaloX * 64;
+            at_tap += kHaloX * 64;
+            at_dz += kTX * 64;
         }
     }
     // element e of lane l: row (output channel) 8 (e / 4) + 4 (l / 32) + e % 4,
     // column (input channel) l % 32
     const int n = lane & 31, half = lane >> 5;
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        const int t = 7 * wave + q;
+    for (int q = 0; q < 4; ++q) {
+        if (q == 3 && wave > 3) break;
+        const int t = q < 3 ? 3 * wave + q : 24 + wave;
 #pragma unroll
         for (int o = 0; o < NCO; ++o)
 #pragma unroll
@@ -1816,8 +1912,8 @@ namespace {
 
 // Launch plan of the weight gradient: the voxels are split into chunks so
 // that the (chunk, channel tile) workgroups fill the CUs once (one workgroup
-// per CU holds the accumulators), but no more chunks than there are units of
-// work.
+// per CU holds the accumulators, two of 32 x 32 channels), but no more chunks
+// than there are units of work.
 struct WgradPlan {
     WgradArgs a;
     int taps, tasks;      // channel tiles
@@ -1847,7 +1943,7 @@ bool wgrad_plan(const rt3d_dn_conv* c, WgradPlan* p) {
         p->tasks = (tco / p->nco) * (tci / p->nci);
         const int ty = p->nci == 3 ? 2 : 4;
         units = (long)((c->W + kTX - 1) / kTX) * ((c->H + ty - 1) / ty) * c->D;
-        most = kWgradWorkgroups / p->tasks;
+        most = (p->nco * p->nci == 1 ? 2 : 1) * kWgradWorkgroups / p->tasks;
     } else {
         p->nco = p->nci = 1;
         p->tasks = tco * tci;
@@ -1864,7 +1960,7 @@ bool wgrad_plan(const rt3d_dn_conv* c, WgradPlan* p) {
 template <int NCO, int NCI, int TY>
 rt3d_status wgrad3_launch(const WgradPlan& plan, const WgradArgs& a, hipStream_t st) {
     constexpr size_t lds = sizeof(uint4) * WgradTile<NCO, NCI, TY>::kPieces;
-    hipLaunchKernelGGL((conv3_wgrad_kernel<NCO, NCI, TY>), dim3((unsigned)(plan.tasks * a.chunks)), dim3(256), lds, st, a);
+    hipLaunchKernelGGL((conv3_wgrad_kernel<NCO, NCI, TY>), dim3((unsigned)(plan.tasks * a.chunks)), dim3(512), lds, st, a);
     DN_TRY(hipGetLastError());
     return RT3D_OK;
 }
