@@ -64,6 +64,27 @@ rt3d_status rt3d_dn_conv3d_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const 
                                const float* bias, int32_t relu, uint16_t* y1, uint16_t* y2, int32_t o1, float* yf,
                                void* stream);
 
+/* Bytes of device workspace with which rt3d_dn_conv3d_fwd_ws and
+ * rt3d_dn_conv3d_fwd_head_ws run this convolution faster (its weights are
+ * first packed there in the order in which they are read), 0 where they would
+ * not. */
+size_t rt3d_dn_conv_workspace_size(const rt3d_dn_conv* c);
+
+/* rt3d_dn_conv3d_fwd, bitwise, with a device workspace (16-byte aligned,
+ * contents need not be initialised; NULL or too small: not used). */
+rt3d_status rt3d_dn_conv3d_fwd_ws(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
+                                  const float* bias, int32_t relu, uint16_t* y1, uint16_t* y2, int32_t o1, float* yf,
+                                  void* workspace, size_t workspace_bytes, void* stream);
+
+/* The data gradient of a 3x3x3 convolution with weights w (as the forward
+ * call takes them, [c->c1][27][c->cout] here: c describes the gradient's own
+ * convolution, c1 channels of dz, c2 = 0, cout of the forward input): bitwise
+ * rt3d_dn_flip_weights followed by rt3d_dn_conv3d_fwd on dz, without bias and
+ * activation.  The workspace (c->cout * 27 * c->c1 * 2 bytes, 16-byte
+ * aligned) is needed. */
+rt3d_status rt3d_dn_conv3d_dgrad(const rt3d_dn_conv* c, const uint16_t* dz, const uint16_t* w, uint16_t* dx1,
+                                 uint16_t* dx2, int32_t o1, void* workspace, size_t workspace_bytes, void* stream);
+
 /* The network's last two layers in one launch (inference): a 3x3x3
  * convolution to exactly 32 channels, y = act(conv(concat(x1, x2), w) +
  * bias) rounded to BF16 (c1, c2 multiples of 16; up1 as above), followed by
@@ -76,6 +97,13 @@ rt3d_status rt3d_dn_conv3d_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const 
 rt3d_status rt3d_dn_conv3d_fwd_head(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
                                     const float* bias, int32_t relu, const uint16_t* hw, const float* hb, int32_t hcols,
                                     float* hy, void* stream);
+
+/* rt3d_dn_conv3d_fwd_head, bitwise, with a workspace as in
+ * rt3d_dn_conv3d_fwd_ws. */
+rt3d_status rt3d_dn_conv3d_fwd_head_ws(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2,
+                                       const uint16_t* w, const float* bias, int32_t relu, const uint16_t* hw,
+                                       const float* hb, int32_t hcols, float* hy, void* workspace,
+                                       size_t workspace_bytes, void* stream);
 
 /* The first layer followed by the 2x2x2 average pooling of its output, in
  * one launch (inference): c describes the packed first layer (c1 = 4, c2 =

@@ -70,7 +70,7 @@ struct ConvArgs {
     const uint16_t* x1;
     const uint16_t* x2;
     int c1, c2;            // input channels from x1 and x2 (multiples of 16)
-    const uint16_t* w;     // [cout][taps][c1 + c2]
+    const uint16_t* w;     // [cout][taps][c1 + c2], or packed (pack_weights_kernel)
     const float* bias;     // [cout] or null
     uint16_t* y1;          // channels [0, o1)
     uint16_t* y2;          // channels [o1, cout)
@@ -78,6 +78,7 @@ struct ConvArgs {
     float* yf;             // optional FP32 copy [vox][yf_cols] of channels < yf_cols
     int D, H, W, cout, relu;
     int up1;               // x1 at half resolution, read nearest-upsampled
+    int w_row, w_half, w_tap, w_chunk;  // byte steps of the 3x3x3 weights: output channel, 8 inputs, tap, 16 inputs
     int yf_cols;
     // optional 1x1x1 head fused after a 32-output 3x3x3 convolution:
     // hy[vox][hcols] = FP32 channels [0, hcols) of conv1(bf16(y), hw) + hb
@@ -298,13 +299,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
             for (int e = 0; e < 16; ++e) acc[oz][o][e] = 0.0f;
 
     const auto wres = weight_resource(a.w + (long)n0 * 27 * cin, 32L * 27 * cin);
-    const uint32_t lane_w = (uint32_t)(m * 27 * cin + 8 * half) * 2;
+    const uint32_t lane_w = (uint32_t)(m * a.w_row + half * a.w_half);
     // the 9 weight fragments of (chunk c, z-slice dz); past the last chunk the
     // address is clamped and the fragments are never used
     auto load_b = [&](int c, int dz, uint4* out) {
         const int cc = min(c, cin - 16);
 #pragma unroll
-        for (int t = 0; t < 9; ++t) out[t] = load_weights(wres, lane_w, (uint32_t)((dz * 9 + t) * cin + cc) * 2);
+        for (int t = 0; t < 9; ++t) out[t] = load_weights(wres, lane_w, (uint32_t)((dz * 9 + t) * a.w_tap + (cc >> 4) * a.w_chunk));
     };
     const uint4* const at = tile + (row0 * kHaloX + m) * 2 + half;
     uint4 bnext[9];
@@ -933,6 +934,34 @@ __global__ void flip_weights_kernel(const uint16_t* __restrict__ w, uint16_t* __
         const int t = (int)((i / cin) % taps);
         const int co = (int)(i / ((size_t)cin * taps));
         wt[((size_t)ci * taps + (taps - 1 - t)) * cout + co] = w[i];
+    }
+}
+
+// The 3x3x3 weights in the order in which conv3_kernel's waves read them,
+// [output channels / 32][input channels / 16][27 taps][64 lanes][8], so that a
+// fragment is 1 KB in a row.  In [cout][27][cin] its lanes read 32 bytes each of
+// 32 cache lines, whose other 96 bytes are fetched again for each of the next
+// three chunks: 192 -> 64 channels on 44x90x118 voxels 348 us that way, 305
+// packed; 96 -> 32 on 128x1024x1024 20.9 and 18.9 ms.  flip: the kernel of the data gradient, from
+// w [cin][27][cout] (flip_weights_kernel's input).  A thread packs one lane's 8.
+__global__ void pack_weights_kernel(const uint16_t* __restrict__ w, uint4* __restrict__ out, int cout, int cin,
+                                    int flip) {
+    const long n = (long)cout / 32 * (cin / 16) * 27 * 64;
+    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
+        const int lane = (int)(i & 63), t = (int)(i / 64 % 27);
+        const long rest = i / (64 * 27);
+        const int c = (int)(rest % (cin / 16)) * 16 + 8 * (lane >> 5);
+        const long co = rest / (cin / 16) * 32 + (lane & 31);
+        if (flip) {
+            const uint16_t* src = w + ((long)c * 27 + 26 - t) * cout + co;
+            uint32_t q[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                q[k] = src[2 * k * 27L * cout] | (uint32_t)src[(2 * k + 1) * 27L * cout] << 16;
+            out[i] = make_uint4(q[0], q[1], q[2], q[3]);
+        } else {
+            out[i] = *reinterpret_cast<const uint4*>(w + (co * 27 + t) * cin + c);
+        }
     }
 }
 
@@ -1791,11 +1820,91 @@ __global__ void unfeature_kernel(const float* __restrict__ pred, float scale, si
 // ===========================================================================
 namespace {
 
+// Packing (5 us beside other launches) pays from about 27 G multiply-adds on:
+// 384 -> 128 channels on 32^3 (43 G) 160 -> 146 us; at 192 -> 64 on 20x28x36
+// (6.7 G) 75 -> 70.  Up to 32 inputs the two chunks of a tap lie in the same
+// 64 bytes and little is fetched twice (32 -> 64 on 20x28x36: 18 us either way).
+constexpr double kPackProducts = 1e9;  // voxels x inputs x outputs
+constexpr int kPackInputs = 48;
+
+void natural_weights(ConvArgs* a) {
+    const int cin = a->c1 + a->c2;
+    a->w_row = 54 * cin; a->w_half = 16; a->w_tap = 2 * cin; a->w_chunk = 32;
+}
+
+size_t packed_bytes(const rt3d_dn_conv* c) { return (size_t)c->cout * 27 * (c->c1 + c->c2) * 2; }
+
+// Packs a->w into `work` and has a read it there.
+rt3d_status pack_weights(const rt3d_dn_conv* c, ConvArgs* a, int flip, void* work, hipStream_t st) {
+    hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks_for(packed_bytes(c) / 16)), dim3(256), 0, st, a->w, (uint4*)work,
+                       c->cout, c->c1 + c->c2, flip);
+    DN_TRY(hipGetLastError());
+    a->w = (const uint16_t*)work;
+    a->w_row = 16; a->w_half = 512; a->w_tap = 1024; a->w_chunk = 27 * 1024;
+    return RT3D_OK;
+}
+
 // Workgroups of conv3_kernel<NCT> per channel slab.
 template <int NCT>
 long conv3_tiles(const rt3d_dn_conv* c) {
     constexpr int rows = ConvTile<NCT>::kRows;
     return (long)((c->D + kZ - 1) / kZ) * ((c->H + rows - 1) / rows) * ((c->W + kTX - 1) / kTX);
+}
+
+rt3d_status conv_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
+                     const float* bias, int32_t relu, uint16_t* y1, uint16_t* y2, int32_t o1, float* yf, int flip,
+                     void* work, size_t work_bytes, void* stream) {
+    if (!c || !x1 || !w || (c->c2 > 0 && !x2) || (!y1 && !yf)) return RT3D_EINVAL;
+    // 4 input channels: only the first layer's packed form
+    const bool four = c->c1 == 4 && c->c2 == 0 && c->ksize == 3 && c->cout == 32 && !c->up1 && o1 == 32;
+    if (c->D <= 0 || c->H <= 0 || c->W <= 0 || c->c1 <= 0 || (c->c1 % 16 && !four) || c->c2 < 0 || c->c2 % 16)
+        return RT3D_EINVAL;
+    if (c->cout <= 0 || c->cout % 32 || (c->ksize != 1 && c->ksize != 3)) return RT3D_EINVAL;
+    if (o1 <= 0 || o1 > c->cout || o1 % 32 || (o1 < c->cout && !y2)) return RT3D_EINVAL;
+    if (c->up1 && (c->ksize != 3 || c->D % 2 || c->H % 2 || c->W % 2)) return RT3D_EINVAL;
+    if (c->yf_cols < 0 || c->yf_cols > c->cout) return RT3D_EINVAL;
+    ConvArgs a;
+    a.x1 = x1; a.x2 = x2; a.c1 = c->c1; a.c2 = c->c2; a.w = w; a.bias = bias;
+    a.y1 = y1; a.y2 = y2; a.o1 = o1; a.yf = yf;
+    a.D = c->D; a.H = c->H; a.W = c->W; a.cout = c->cout; a.relu = relu ? 1 : 0;
+    a.up1 = c->up1 ? 1 : 0;
+    a.yf_cols = c->yf_cols ? c->yf_cols : c->cout;
+    a.hw = nullptr; a.hb = nullptr; a.hy = nullptr; a.hcols = 0;
+    a.co_base = 0; a.slabs = 1; a.store16 = 0;
+    if (four) {
+        const long tiles = (long)c->D * ((c->H + kTY32 - 1) / kTY32) * ((c->W + kTX - 1) / kTX);
+        if (tiles > 0x7fffffffL) return RT3D_EINVAL;
+        hipLaunchKernelGGL(conv3_c4_kernel, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
+    } else if (c->ksize == 3) {
+        a.store16 = y1 && !yf && ((uintptr_t)y1 | (uintptr_t)(o1 < c->cout ? y2 : nullptr)) % 16 == 0;
+        const bool pack = work && work_bytes >= packed_bytes(c) && (uintptr_t)work % 16 == 0;
+        if (flip && !pack) return RT3D_EINVAL;
+        // 64 output channels per workgroup; 32 that are left over by themselves
+        const int wide = c->cout / 64, narrow = (c->cout / 32) % 2;
+        const long tiles = conv3_tiles<2>(c) * wide, rest = conv3_tiles<1>(c) * narrow;
+        if (tiles > 0x7fffffffL || rest > 0x7fffffffL) return RT3D_EINVAL;
+        natural_weights(&a);
+        if (pack) {
+            const rt3d_status r = pack_weights(c, &a, flip, work, (hipStream_t)stream);
+            if (r != RT3D_OK) return r;
+        }
+        if (wide) {
+            a.slabs = wide;
+            hipLaunchKernelGGL(conv3_kernel<2>, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
+            DN_TRY(hipGetLastError());
+        }
+        if (narrow) {
+            a.co_base = 64 * wide;
+            a.slabs = 1;
+            hipLaunchKernelGGL(conv3_kernel<1>, dim3((unsigned)rest), dim3(256), 0, (hipStream_t)stream, a);
+        }
+    } else {
+        const long waves = (long)c->D * c->H * ((c->W + 31) / 32) * (c->cout / 32);
+        const unsigned blocks = (unsigned)((waves + 3) / 4);
+        hipLaunchKernelGGL(conv_fwd_kernel<1>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, a);
+    }
+    DN_TRY(hipGetLastError());
+    return RT3D_OK;
 }
 
 }  // namespace
@@ -1824,58 +1933,41 @@ rt3d_status rt3d_dn_conv3d_fwd_pool(const rt3d_dn_conv* c, const uint16_t* x1, c
     return RT3D_OK;
 }
 
+size_t rt3d_dn_conv_workspace_size(const rt3d_dn_conv* c) {
+    if (!c || c->ksize != 3 || c->D <= 0 || c->H <= 0 || c->W <= 0) return 0;
+    if (c->c1 <= 0 || c->c1 % 16 || c->c2 < 0 || c->c2 % 16 || c->cout <= 0 || c->cout % 32) return 0;
+    const int cin = c->c1 + c->c2;
+    const bool pays = cin >= kPackInputs && (double)c->D * c->H * c->W * cin * c->cout >= kPackProducts;
+    return pays ? packed_bytes(c) : 0;
+}
+
 rt3d_status rt3d_dn_conv3d_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
                                const float* bias, int32_t relu, uint16_t* y1, uint16_t* y2, int32_t o1, float* yf,
                                void* stream) {
-    if (!c || !x1 || !w || (c->c2 > 0 && !x2) || (!y1 && !yf)) return RT3D_EINVAL;
-    // 4 input channels: only the first layer's packed form
-    const bool four = c->c1 == 4 && c->c2 == 0 && c->ksize == 3 && c->cout == 32 && !c->up1 && o1 == 32;
-    if (c->D <= 0 || c->H <= 0 || c->W <= 0 || c->c1 <= 0 || (c->c1 % 16 && !four) || c->c2 < 0 || c->c2 % 16)
-        return RT3D_EINVAL;
-    if (c->cout <= 0 || c->cout % 32 || (c->ksize != 1 && c->ksize != 3)) return RT3D_EINVAL;
-    if (o1 <= 0 || o1 > c->cout || o1 % 32 || (o1 < c->cout && !y2)) return RT3D_EINVAL;
-    if (c->up1 && (c->ksize != 3 || c->D % 2 || c->H % 2 || c->W % 2)) return RT3D_EINVAL;
-    if (c->yf_cols < 0 || c->yf_cols > c->cout) return RT3D_EINVAL;
-    ConvArgs a;
-    a.x1 = x1; a.x2 = x2; a.c1 = c->c1; a.c2 = c->c2; a.w = w; a.bias = bias;
-    a.y1 = y1; a.y2 = y2; a.o1 = o1; a.yf = yf;
-    a.D = c->D; a.H = c->H; a.W = c->W; a.cout = c->cout; a.relu = relu ? 1 : 0;
-    a.up1 = c->up1 ? 1 : 0;
-    a.yf_cols = c->yf_cols ? c->yf_cols : c->cout;
-    a.hw = nullptr; a.hb = nullptr; a.hy = nullptr; a.hcols = 0;
-    a.co_base = 0; a.slabs = 1; a.store16 = 0;
-    if (four) {
-        const long tiles = (long)c->D * ((c->H + kTY32 - 1) / kTY32) * ((c->W + kTX - 1) / kTX);
-        if (tiles > 0x7fffffffL) return RT3D_EINVAL;
-        hipLaunchKernelGGL(conv3_c4_kernel, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
-    } else if (c->ksize == 3) {
-        a.store16 = y1 && !yf && ((uintptr_t)y1 | (uintptr_t)(o1 < c->cout ? y2 : nullptr)) % 16 == 0;
-        // 64 output channels per workgroup; 32 that are left over by themselves
-        const int wide = c->cout / 64, narrow = (c->cout / 32) % 2;
-        const long tiles = conv3_tiles<2>(c) * wide, rest = conv3_tiles<1>(c) * narrow;
-        if (tiles > 0x7fffffffL || rest > 0x7fffffffL) return RT3D_EINVAL;
-        if (wide) {
-            a.slabs = wide;
-            hipLaunchKernelGGL(conv3_kernel<2>, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
-            DN_TRY(hipGetLastError());
-        }
-        if (narrow) {
-            a.co_base = 64 * wide;
-            a.slabs = 1;
-            hipLaunchKernelGGL(conv3_kernel<1>, dim3((unsigned)rest), dim3(256), 0, (hipStream_t)stream, a);
-        }
-    } else {
-        const long waves = (long)c->D * c->H * ((c->W + 31) / 32) * (c->cout / 32);
-        const unsigned blocks = (unsigned)((waves + 3) / 4);
-        hipLaunchKernelGGL(conv_fwd_kernel<1>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, a);
-    }
-    DN_TRY(hipGetLastError());
-    return RT3D_OK;
+    return conv_fwd(c, x1, x2, w, bias, relu, y1, y2, o1, yf, 0, nullptr, 0, stream);
+}
+
+rt3d_status rt3d_dn_conv3d_fwd_ws(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
+                                  const float* bias, int32_t relu, uint16_t* y1, uint16_t* y2, int32_t o1, float* yf,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+    return conv_fwd(c, x1, x2, w, bias, relu, y1, y2, o1, yf, 0, workspace, workspace_bytes, stream);
+}
+
+rt3d_status rt3d_dn_conv3d_dgrad(const rt3d_dn_conv* c, const uint16_t* dz, const uint16_t* w, uint16_t* dx1,
+                                 uint16_t* dx2, int32_t o1, void* workspace, size_t workspace_bytes, void* stream) {
+    if (!c || c->ksize != 3 || c->c1 % 16 || c->c2 || c->up1 || c->yf_cols) return RT3D_EINVAL;
+    return conv_fwd(c, dz, nullptr, w, nullptr, 0, dx1, dx2, o1, nullptr, 1, workspace, workspace_bytes, stream);
 }
 
 rt3d_status rt3d_dn_conv3d_fwd_head(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
                                     const float* bias, int32_t relu, const uint16_t* hw, const float* hb, int32_t hcols,
                                     float* hy, void* stream) {
+    return rt3d_dn_conv3d_fwd_head_ws(c, x1, x2, w, bias, relu, hw, hb, hcols, hy, nullptr, 0, stream);
+}
+
+rt3d_status rt3d_dn_conv3d_fwd_head_ws(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2,
+                                       const uint16_t* w, const float* bias, int32_t relu, const uint16_t* hw, const float* hb,
+                                       int32_t hcols, float* hy, void* workspace, size_t workspace_bytes, void* stream) {
     if (!c || !x1 || !w || (c->c2 > 0 && !x2) || !hw || !hy) return RT3D_EINVAL;
     if (c->D <= 0 || c->H <= 0 || c->W <= 0 || c->c1 <= 0 || c->c1 % 16 || c->c2 < 0 || c->c2 % 16)
         return RT3D_EINVAL;
@@ -1891,6 +1983,11 @@ rt3d_status rt3d_dn_conv3d_fwd_head(const rt3d_dn_conv* c, const uint16_t* x1, c
     a.co_base = 0; a.slabs = 1; a.store16 = 0;
     const long tiles = conv3_tiles<1>(c);
     if (tiles > 0x7fffffffL) return RT3D_EINVAL;
+    natural_weights(&a);
+    if (workspace && workspace_bytes >= packed_bytes(c) && (uintptr_t)workspace % 16 == 0) {
+        const rt3d_status r = pack_weights(c, &a, 0, workspace, (hipStream_t)stream);
+        if (r != RT3D_OK) return r;
+    }
     hipLaunchKernelGGL(conv3_kernel<1>, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
     DN_TRY(hipGetLastError());
     return RT3D_OK;

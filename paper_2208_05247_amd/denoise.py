@@ -61,7 +61,10 @@ def load():
     P, I, U = ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint64
     sig = {
         "rt3d_dn_conv3d_fwd": [ctypes.POINTER(_Conv), P, P, P, P, I, P, P, I, P, P],
+        "rt3d_dn_conv3d_fwd_ws": [ctypes.POINTER(_Conv), P, P, P, P, I, P, P, I, P, P, ctypes.c_size_t, P],
+        "rt3d_dn_conv3d_dgrad": [ctypes.POINTER(_Conv), P, P, P, P, I, P, ctypes.c_size_t, P],
         "rt3d_dn_conv3d_fwd_head": [ctypes.POINTER(_Conv), P, P, P, P, I, P, P, I, P, P],
+        "rt3d_dn_conv3d_fwd_head_ws": [ctypes.POINTER(_Conv), P, P, P, P, I, P, P, I, P, P, ctypes.c_size_t, P],
         "rt3d_dn_conv3d_fwd_pool": [ctypes.POINTER(_Conv), P, P, P, I, P, P, P],
         "rt3d_dn_flip_weights": [P, P, I, I, I, P],
         "rt3d_dn_conv3d_wgrad": [ctypes.POINTER(_Conv), P, P, P, P, P, P],
@@ -86,6 +89,8 @@ def load():
         f.argtypes = args
         f.restype = ctypes.c_int
     lib.rt3d_dn_last_error.restype = ctypes.c_char_p
+    lib.rt3d_dn_conv_workspace_size.argtypes = [ctypes.POINTER(_Conv)]
+    lib.rt3d_dn_conv_workspace_size.restype = ctypes.c_size_t
     lib.rt3d_dn_wgrad_workspace_size.argtypes = [ctypes.POINTER(_Conv)]
     lib.rt3d_dn_wgrad_workspace_size.restype = ctypes.c_size_t
     _lib = lib
@@ -121,6 +126,17 @@ def bf16_empty(*shape, device="cuda"):
 # Kernel wrappers
 # ---------------------------------------------------------------------------
 
+def _packed_weights(c, device):
+    """Room for a convolution's packed weights, from torch's allocator: of the
+    current stream, given back when the caller drops it.  (None, 0) where the
+    library asks for none, and under capture: a graph captured outside torch's
+    own would replay into memory that has been given back."""
+    need = int(load().rt3d_dn_conv_workspace_size(ctypes.byref(c)))
+    if need == 0 or torch.cuda.is_current_stream_capturing():
+        return None, 0
+    return torch.empty(need, dtype=torch.uint8, device=device), need
+
+
 def conv_fwd(x1, x2, w, bias, relu, cout, ksize, y1=None, y2=None, o1=None, yf=None, up1=False, yf_cols=0):
     """One convolution; with up1, x1 is at half resolution and read
     nearest-upsampled (the output grid is twice x1's); yf (FP32) keeps the
@@ -135,8 +151,19 @@ def conv_fwd(x1, x2, w, bias, relu, cout, ksize, y1=None, y2=None, o1=None, yf=N
     if yf is not None and yf.shape[-1] != (yf_cols or cout):
         raise ValueError("yf must have yf_cols channels")
     c = _Conv(D, H, W, c1, c2, cout, ksize, 1 if up1 else 0, int(yf_cols))
-    _check(load().rt3d_dn_conv3d_fwd(ctypes.byref(c), _p(x1), _p(x2), _p(w), _p(bias), int(relu), _p(y1), _p(y2),
-                                     int(o1), _p(yf), _s()), "rt3d_dn_conv3d_fwd")
+    ws, n = _packed_weights(c, x1.device)
+    _check(load().rt3d_dn_conv3d_fwd_ws(ctypes.byref(c), _p(x1), _p(x2), _p(w), _p(bias), int(relu), _p(y1), _p(y2),
+                                        int(o1), _p(yf), _p(ws), n, _s()), "rt3d_dn_conv3d_fwd")
+
+
+def conv_dgrad(dz, w, cin, dx1, dx2=None, o1=None):
+    """Data gradient of a 3x3x3 convolution: flip and conv_fwd of dz in one
+    call; w as the forward call takes it."""
+    D, H, W, cout = dz.shape
+    c = _Conv(D, H, W, cout, 0, cin, 3, 0, 0)
+    ws = torch.empty(2 * cin * 27 * cout, dtype=torch.uint8, device=dz.device)
+    _check(load().rt3d_dn_conv3d_dgrad(ctypes.byref(c), _p(dz), _p(w), _p(dx1), _p(dx2), int(cin if o1 is None else o1),
+                                       _p(ws), ws.numel(), _s()), "rt3d_dn_conv3d_dgrad")
 
 
 def conv_fwd_head(x1, x2, w, bias, relu, hw, hb, out, up1=False):
@@ -152,8 +179,10 @@ def conv_fwd_head(x1, x2, w, bias, relu, hw, hb, out, up1=False):
     if tuple(out.shape[:3]) != (D, H, W) or tuple(hw.shape[:1]) != (32,) or hw.numel() != 32 * 32:
         raise ValueError("out must be on the output grid and hw [32][32]")
     c = _Conv(D, H, W, c1, c2, 32, 3, 1 if up1 else 0, 0)
-    _check(load().rt3d_dn_conv3d_fwd_head(ctypes.byref(c), _p(x1), _p(x2), _p(w), _p(bias), int(relu), _p(hw),
-                                          _p(hb), int(out.shape[-1]), _p(out), _s()), "rt3d_dn_conv3d_fwd_head")
+    ws, n = _packed_weights(c, x1.device)
+    _check(load().rt3d_dn_conv3d_fwd_head_ws(ctypes.byref(c), _p(x1), _p(x2), _p(w), _p(bias), int(relu), _p(hw),
+                                             _p(hb), int(out.shape[-1]), _p(out), _p(ws), n, _s()),
+           "rt3d_dn_conv3d_fwd_head")
 
 
 def conv_fwd_pool(x1, w, bias, relu, y, ypool):
@@ -379,6 +408,9 @@ class Denoiser:
     def _data_grad(self, name, dz, out1, out2=None):
         L = next(l for l in self.layers if l.name == name)
         cin = L.c1 + L.c2
+        if L.ksize == 3:
+            conv_dgrad(dz, self.pb[name], cin, out1, out2, o1=L.c1)
+            return
         wt = bf16_empty(cin, L.ksize ** 3, L.cout)
         flip(self.pb[name], L.cout, cin, L.ksize, wt)
         conv_fwd(dz, None, wt, None, False, cin, L.ksize, y1=out1, y2=out2, o1=L.c1)
