@@ -179,13 +179,15 @@ __device__ __forceinline__ void wait_loads() { __asm__ volatile("s_waitcnt vmcnt
 // voxels of each row go through registers, their loads in flight together with
 // the others.  What lies outside the domain reads the 16-byte zero block.  The
 // caller's barrier afterwards publishes the tile.
-template <int NZ, int HY>
+// ALL: every voxel through registers, read (load) while the previous chunk is
+// computed; for tiles small enough.
+template <int NZ, int HY, bool ALL>
 struct Halo16 {
     static constexpr int kRows = NZ * HY;
     static constexpr int kOuter = (4 * kRows + 255) / 256;  // outer pieces a lane moves: i = 4 row + 2 side + half
     const uint16_t* base;
     int cs, hr, h, w;  // channels, 1 at half resolution, extent there
-    uint4 outer[kOuter];
+    uint4 outer[kOuter], inner[ALL ? (kRows + 3) / 4 : 1];
 
     // Before the barrier after which the tile may be overwritten.
     __device__ __forceinline__ void load_outer(const ConvArgs& a, int c0, int x0, int y0, int z0) {
@@ -218,6 +220,27 @@ struct Halo16 {
                                              0, 0);
         }
         wait_loads();
+        put_outer(tile);
+    }
+    __device__ __forceinline__ void load(const ConvArgs& a, int c0, int x0, int y0, int z0, int wave, int lane) {
+        load_outer(a, c0, x0, y0, z0);
+        const int x = x0 + (lane >> 1);
+        const uint32_t lane_at = (uint32_t)((x >> hr) * cs + 8 * (lane & 1));
+#pragma unroll
+        for (int k = 0; k < (kRows + 3) / 4; ++k) {
+            const int row = wave + 4 * k, y = y0 + row % HY - 1, z = z0 + row / HY - 1;
+            const bool in = row < kRows && y >= 0 && y < a.H && z >= 0 && z < a.D && x < a.W;
+            const uint16_t* const at = base + ((long)(z >> hr) * h + (y >> hr)) * w * cs;
+            inner[k] = load_global16(in ? at + lane_at : reinterpret_cast<const uint16_t*>(dn_zero16));
+        }
+    }
+    __device__ __forceinline__ void put(uint4* tile, int wave, int lane) {
+#pragma unroll
+        for (int k = 0; k < (kRows + 3) / 4; ++k)
+            if (wave + 4 * k < kRows) tile[((wave + 4 * k) * kHaloX + 1) * 2 + lane] = inner[k];
+        put_outer(tile);
+    }
+    __device__ __forceinline__ void put_outer(uint4* tile) {
 #pragma unroll
         for (int k = 0; k < kOuter; ++k) {
             const int i = (int)threadIdx.x + 256 * k, row = i >> 2, side = (i >> 1) & 1, part = i & 1;
@@ -238,42 +261,42 @@ __device__ __forceinline__ uint4 load_weights(__amdgpu_buffer_rsrc_t r, uint32_t
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane, (int)uniform, 0));
 }
 
-// Tiled 3x3x3 convolution.  A workgroup (4 waves) owns an output tile of kZ
-// z-slices x kRows y-rows x 32 voxels and NCT x 32 output channels (NCT 1: 16
-// rows, 4 a wave; NCT 2: 8 rows, a wave has 4 of them and one of the two
-// channel tiles).  For each 16-channel input chunk the
-// (kZ+2) x (kRows+2) x 34-voxel halo is loaded straight into LDS.  Per z-slice
+// Tiled 3x3x3 convolution.  A workgroup (4 waves) owns an output tile of KZ
+// z-slices x kRows y-rows x 32 voxels and NCT x 32 output channels; a wave has R
+// of the rows and 32 of the channels (NCT 2: two waves share the rows).  For
+// each 16-channel input chunk the (KZ+2) x (kRows+2) x 34-voxel halo is loaded
+// into LDS: straight, or where a lane's part of it fits beside its accumulators
+// through registers, read while the previous chunk is computed.  Per z-slice
 // of the kernel a wave keeps its 9 weight fragments in registers (the next
-// slice's are loaded meanwhile), walks the 6 staged input rows its outputs need
-// in both planes that slice reaches, 3 x-shifts each, and feeds every fragment
-// it reads from LDS to all (up to 3) of its output rows that use it: half an
-// LDS read and an eighth of a weight load per MFMA.  All LDS offsets are
-// constants from one lane address.
-// What bounds it (128 -> 64 and 64 -> 64 channels, 44x90x118 voxels, the launch
-// alone): 425 us when every wave loaded both channel tiles' weights (8.8 TB/s
-// from the L2; 291 with the loads left out), 354 in this split, 332 with
-// Halo16 (337 with its outer voxels waited for before its inner ones are
-// loaded); about 60 of those are staging that the CU's other workgroup does
-// not hide.
+// slice's are loaded meanwhile), walks the R + 2 staged input rows its outputs
+// need in each plane that slice reaches, 3 x-shifts each, and feeds every
+// fragment it reads from LDS to all (up to 3) of its output rows that use it: at
+// R = 4, KZ = 2 half an LDS read and an eighth of a weight load per MFMA.  All
+// LDS offsets are constants from one lane address.  An output's products and
+// their order are the same in every variant.
+// What bounds it (192 -> 64 channels, 44x90x118 voxels, the launch alone, R = 4,
+// KZ = 2): 425 us when every wave loaded both channel tiles' weights (8.8 TB/s
+// from the L2; 291 with the loads left out), 354 in this split, 337 with
+// cheaper staging, 332 with the halo's outer voxels in flight beside its inner
+// ones, 290 with packed weights; about 50 of those are staging that the CU's
+// other workgroup does not hide.
 // The matrix cores themselves sustain 1.6-1.8 PFLOP/s on such operands.
 // With a head (ConvArgs::hw, NCT 1) the
 // 1x1x1 convolution follows in the epilogue and only its output is stored.
-constexpr int kZ = 2;
-
-template <int NCT>
+template <int NCT, int R, int KZ>
 struct ConvTile {
-    static constexpr int kRows = 16 / NCT, kHaloY = kRows + 2;
-    static constexpr int kHaloVox = (kZ + 2) * kHaloY * kHaloX;
+    static constexpr int kRows = 4 / NCT * R, kHaloY = kRows + 2;
+    static constexpr int kHaloVox = (KZ + 2) * kHaloY * kHaloX;
+    // the fused head reuses the halo tile: 4 waves x KZ x R rows x 32 x 32 BF16
+    // activations, then per wave one output row of 32 voxels x 2 FP32
+    static constexpr int kHeadOut = 4 * KZ * R * 32 * 32 * 2;  // bytes
+    static_assert(NCT > 1 || kHeadOut + 4 * 32 * 2 * 4 <= kHaloVox * 2 * 16, "head scratch exceeds the halo tile");
 };
-// the fused head reuses the halo tile: 4 waves x kZ x 4 rows x 32 x 32 BF16
-// activations, then per wave one output row of 32 voxels x 2 FP32
-static_assert(4 * kZ * 4 * 32 * 32 * 2 <= ConvTile<1>::kHaloVox * 2 * 16, "head scratch exceeds the halo tile");
-constexpr int kHeadOutOffset = 4 * kZ * 4 * 32 * 32 * 2;  // bytes
-static_assert(kHeadOutOffset + 4 * 32 * 2 * 4 <= ConvTile<1>::kHaloVox * 2 * 16, "head output scratch exceeds the halo tile");
 
-template <int NCT>
+template <int NCT, int R, int KZ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) conv3_kernel(const ConvArgs a) {
-    using T = ConvTile<NCT>;
+    using T = ConvTile<NCT, R, KZ>;
+    constexpr bool kAhead = KZ * R <= 4;  // room for the next chunk's halo in registers
     __shared__ uint4 tile[tile_slots(T::kHaloVox)];  // 16 channels = two 16-byte halves per voxel
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int m = lane & 31, half = lane >> 5;
@@ -285,16 +308,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
     const int txi = (int)(b % tiles_x);
     b /= tiles_x;
     const int tyi = (int)(b % tiles_y);
-    const int z0 = (int)(b / tiles_y) * kZ;
+    const int z0 = (int)(b / tiles_y) * KZ;
     const int x0 = txi * kTX, y0 = tyi * T::kRows;
     const int cin = a.c1 + a.c2;
-    const int row0 = 4 * (wave / NCT);
+    const int row0 = R * (wave / NCT);
     const int n0 = a.co_base + 32 * (slab * NCT + wave % NCT);  // this wave's 32 output channels
-    f32x16 acc[kZ][4];
+    f32x16 acc[KZ][R];
 #pragma unroll
-    for (int oz = 0; oz < kZ; ++oz)
+    for (int oz = 0; oz < KZ; ++oz)
 #pragma unroll
-        for (int o = 0; o < 4; ++o)
+        for (int o = 0; o < R; ++o)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[oz][o][e] = 0.0f;
 
@@ -310,12 +333,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
     const uint4* const at = tile + (row0 * kHaloX + m) * 2 + half;
     uint4 bnext[9];
     load_b(0, 0, bnext);
+    Halo16<KZ + 2, T::kHaloY, kAhead> halo;
+    if (kAhead) halo.load(a, 0, x0, y0, z0, wave, lane);
     for (int c0 = 0; c0 < cin; c0 += 16) {
-        Halo16<kZ + 2, T::kHaloY> halo;
-        halo.load_outer(a, c0, x0, y0, z0);
+        if (!kAhead) halo.load_outer(a, c0, x0, y0, z0);
         __syncthreads();  // the previous chunk's halo is no longer read
-        halo.stage(tile, a, x0, y0, z0, wave, lane);
+        if (kAhead) halo.put(tile, wave, lane);
+        else halo.stage(tile, a, x0, y0, z0, wave, lane);
         __syncthreads();
+        if (kAhead && c0 + 16 < cin) halo.load(a, c0 + 16, x0, y0, z0, wave, lane);
 #pragma unroll
         for (int dz = 0; dz < 3; ++dz) {
             uint4 bv[9];
@@ -326,23 +352,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
             // the fragments of the next row are read before this row's MFMAs
             // run, so the LDS latency hides behind them
             auto row_frags = [&](int step, uint4* av) {
-                const int oz = step / 6, r = step % 6;  // output plane oz reads staged plane oz + dz
+                const int oz = step / (R + 2), r = step % (R + 2);  // output plane oz reads staged plane oz + dz
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) av[dx] = at[(((oz + dz) * T::kHaloY + r) * kHaloX + dx) * 2];
             };
             uint4 av[2][3];
             row_frags(0, av[0]);
 #pragma unroll
-            for (int step = 0; step < kZ * 6; ++step) {
-                const int oz = step / 6, r = step % 6;
-                if (step + 1 < kZ * 6) row_frags(step + 1, av[(step + 1) & 1]);
+            for (int step = 0; step < KZ * (R + 2); ++step) {
+                const int oz = step / (R + 2), r = step % (R + 2);
+                if (step + 1 < KZ * (R + 2)) row_frags(step + 1, av[(step + 1) & 1]);
                 // keeps the scheduler from hoisting the reads of later rows
                 // ahead of these MFMAs (it would spill at 2 waves/SIMD)
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-                    for (int o = 0; o < 4; ++o) {
+                    for (int o = 0; o < R; ++o) {
                         const int dy = r - o;  // output row o reads halo row o + dy
                         if (dy >= 0 && dy <= 2)
                             acc[oz][o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -361,17 +387,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
         // one voxel that the A operand takes; the head then runs the same
         // two MFMAs per row as the 1x1x1 convolution kernel, in the same
         // order, so its output is bitwise that of the unfused pair.
-        uint16_t* ht = reinterpret_cast<uint16_t*>(tile) + wave * (kZ * 4 * 32 * 32);
+        uint16_t* ht = reinterpret_cast<uint16_t*>(tile) + wave * (KZ * R * 32 * 32);
         __syncthreads();  // every wave is done reading the halo
 #pragma unroll
-        for (int oz = 0; oz < kZ; ++oz)
+        for (int oz = 0; oz < KZ; ++oz)
 #pragma unroll
-            for (int o = 0; o < 4; ++o)
+            for (int o = 0; o < R; ++o)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     float v = acc[oz][o][e] + bias;
                     if (a.relu) v = fmaxf(v, 0.0f);
-                    ht[((oz * 4 + o) * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * 32 + n] = f2bf(v);
+                    ht[((oz * R + o) * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * 32 + n] = f2bf(v);
                 }
         __syncthreads();
         uint4 hwv[2];
@@ -379,11 +405,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
         for (int c = 0; c < 2; ++c) hwv[c] = *(const uint4*)(a.hw + m * 32 + 16 * c + 8 * half);
         const float hbias = a.hb ? a.hb[n] : 0.0f;
 #pragma unroll
-        for (int oz = 0; oz < kZ; ++oz) {
+        for (int oz = 0; oz < KZ; ++oz) {
             const int zz = z0 + oz;
             if (zz >= a.D) continue;
 #pragma unroll
-            for (int o = 0; o < 4; ++o) {
+            for (int o = 0; o < R; ++o) {
                 const int y = y0 + row0 + o;
                 if (y >= a.H) continue;
                 f32x16 h;
@@ -391,7 +417,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
                 for (int e = 0; e < 16; ++e) h[e] = 0.0f;
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    const uint4 av = *(const uint4*)(ht + ((oz * 4 + o) * 32 + m) * 32 + 16 * c + 8 * half);
+                    const uint4 av = *(const uint4*)(ht + ((oz * R + o) * 32 + m) * 32 + 16 * c + 8 * half);
                     h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(av), as_bf16x8(hwv[c]), h, 0, 0, 0);
                 }
                 if (a.hcols == 2) {
@@ -399,7 +425,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
                     // the activations' part of the tile), so that the row is
                     // stored as one 8-byte piece per voxel by 32 lanes instead
                     // of 16 stores of 4 bytes by 4 lanes each
-                    float* hrow = reinterpret_cast<float*>(tile) + kHeadOutOffset / 4 + wave * 64;
+                    float* hrow = reinterpret_cast<float*>(tile) + T::kHeadOut / 4 + wave * 64;
                     if (n < 2) {
 #pragma unroll
                         for (int e = 0; e < 16; ++e) hrow[(8 * (e >> 2) + 4 * half + (e & 3)) * 2 + n] = h[e] + hbias;
@@ -440,10 +466,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
         uint16_t* const dst = n0 < a.o1 ? a.y1 + n0 : a.y2 + (n0 - a.o1);
         const int stride = n0 < a.o1 ? a.o1 : a.cout - a.o1;
 #pragma unroll
-        for (int oz = 0; oz < kZ; ++oz) {
+        for (int oz = 0; oz < KZ; ++oz) {
             const int zz = z0 + oz;
 #pragma unroll
-            for (int o = 0; o < 4; ++o) {
+            for (int o = 0; o < R; ++o) {
                 const int y = y0 + row0 + o;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
@@ -468,11 +494,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) c
         return;
     }
 #pragma unroll
-    for (int oz = 0; oz < kZ; ++oz) {
+    for (int oz = 0; oz < KZ; ++oz) {
         const int zz = z0 + oz;
         if (zz >= a.D) continue;
 #pragma unroll
-        for (int o = 0; o < 4; ++o) {
+        for (int o = 0; o < R; ++o) {
             const int y = y0 + row0 + o;
             if (y >= a.H) continue;
 #pragma unroll
@@ -1824,7 +1850,10 @@ namespace {
 // 384 -> 128 channels on 32^3 (43 G) 160 -> 146 us; at 192 -> 64 on 20x28x36
 // (6.7 G) 75 -> 70.  Up to 32 inputs the two chunks of a tap lie in the same
 // 64 bytes and little is fetched twice (32 -> 64 on 20x28x36: 18 us either way).
-constexpr double kPackProducts = 1e9;  // voxels x inputs x outputs
+// Packing (3 to 5 us) pays where the wave loads less than half of a cache line
+// of each row: 384 -> 128 channels on 10x14x18 93 us without (2 rows, 1
+// plane), 55 with.  Up to 32 inputs a tap's two chunks lie in the same 64
+// bytes and little is fetched twice (32 -> 64 on 20x28x36: 18 us either way).
 constexpr int kPackInputs = 48;
 
 void natural_weights(ConvArgs* a) {
@@ -1844,11 +1873,34 @@ rt3d_status pack_weights(const rt3d_dn_conv* c, ConvArgs* a, int flip, void* wor
     return RT3D_OK;
 }
 
-// Workgroups of conv3_kernel<NCT> per channel slab.
+template <int NCT, int R, int KZ>
+long conv3_groups(const ConvArgs& a) {
+    constexpr int rows = ConvTile<NCT, R, KZ>::kRows;
+    return (long)((a.D + KZ - 1) / KZ) * ((a.H + rows - 1) / rows) * ((a.W + kTX - 1) / kTX) * a.slabs;
+}
+
+template <int NCT, int R, int KZ>
+rt3d_status conv3_launch(const ConvArgs& a, hipStream_t st) {
+    const long n = conv3_groups<NCT, R, KZ>(a);
+    if (n > 0x7fffffffL) return RT3D_EINVAL;
+    hipLaunchKernelGGL((conv3_kernel<NCT, R, KZ>), dim3((unsigned)n), dim3(256), 0, st, a);
+    DN_TRY(hipGetLastError());
+    return RT3D_OK;
+}
+
+// a.slabs x 32 NCT channels from a.co_base.  The largest tile that fills the
+// CUs: it feeds a weight fragment to the most MFMAs, but one workgroup runs all
+// its input chunks in series.  Packed weights, the rows of a wave x planes:
+//   384 -> 128 on 10x14x18   (4, 2)  20 workgroups 129 us, (2, 2)  40 69, (1, 2)  70 48, (1, 1) 140 40
+//   128 -> 256 on 16^3       (4, 2)  64 60,                (2, 2) 128 32, (1, 2) 256 22, (1, 1) 512 25
+//   192 -> 64 on 20x28x36    (4, 2)  80 70,                (2, 2) 140 41, (1, 2) 280 42, (1, 1) 560 47
+//   192 -> 64 on 64^3        (4, 2) 512 158,               (2, 2) 1024 167, (1, 2) 2048 199
 template <int NCT>
-long conv3_tiles(const rt3d_dn_conv* c) {
-    constexpr int rows = ConvTile<NCT>::kRows;
-    return (long)((c->D + kZ - 1) / kZ) * ((c->H + rows - 1) / rows) * ((c->W + kTX - 1) / kTX);
+rt3d_status conv3_run(const ConvArgs& a, hipStream_t st) {
+    if (conv3_groups<NCT, 4, 2>(a) >= 512) return conv3_launch<NCT, 4, 2>(a, st);
+    if (conv3_groups<NCT, 2, 2>(a) > 128) return conv3_launch<NCT, 2, 2>(a, st);
+    if (conv3_groups<NCT, 1, 2>(a) > 128) return conv3_launch<NCT, 1, 2>(a, st);
+    return conv3_launch<NCT, 1, 1>(a, st);
 }
 
 rt3d_status conv_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
@@ -1881,8 +1933,6 @@ rt3d_status conv_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* 
         if (flip && !pack) return RT3D_EINVAL;
         // 64 output channels per workgroup; 32 that are left over by themselves
         const int wide = c->cout / 64, narrow = (c->cout / 32) % 2;
-        const long tiles = conv3_tiles<2>(c) * wide, rest = conv3_tiles<1>(c) * narrow;
-        if (tiles > 0x7fffffffL || rest > 0x7fffffffL) return RT3D_EINVAL;
         natural_weights(&a);
         if (pack) {
             const rt3d_status r = pack_weights(c, &a, flip, work, (hipStream_t)stream);
@@ -1890,13 +1940,13 @@ rt3d_status conv_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* 
         }
         if (wide) {
             a.slabs = wide;
-            hipLaunchKernelGGL(conv3_kernel<2>, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
-            DN_TRY(hipGetLastError());
+            const rt3d_status r = conv3_run<2>(a, (hipStream_t)stream);
+            if (r != RT3D_OK) return r;
         }
         if (narrow) {
             a.co_base = 64 * wide;
             a.slabs = 1;
-            hipLaunchKernelGGL(conv3_kernel<1>, dim3((unsigned)rest), dim3(256), 0, (hipStream_t)stream, a);
+            return conv3_run<1>(a, (hipStream_t)stream);
         }
     } else {
         const long waves = (long)c->D * c->H * ((c->W + 31) / 32) * (c->cout / 32);
@@ -1936,9 +1986,7 @@ rt3d_status rt3d_dn_conv3d_fwd_pool(const rt3d_dn_conv* c, const uint16_t* x1, c
 size_t rt3d_dn_conv_workspace_size(const rt3d_dn_conv* c) {
     if (!c || c->ksize != 3 || c->D <= 0 || c->H <= 0 || c->W <= 0) return 0;
     if (c->c1 <= 0 || c->c1 % 16 || c->c2 < 0 || c->c2 % 16 || c->cout <= 0 || c->cout % 32) return 0;
-    const int cin = c->c1 + c->c2;
-    const bool pays = cin >= kPackInputs && (double)c->D * c->H * c->W * cin * c->cout >= kPackProducts;
-    return pays ? packed_bytes(c) : 0;
+    return c->c1 + c->c2 >= kPackInputs ? packed_bytes(c) : 0;
 }
 
 rt3d_status rt3d_dn_conv3d_fwd(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* w,
@@ -1981,16 +2029,12 @@ rt3d_status rt3d_dn_conv3d_fwd_head_ws(const rt3d_dn_conv* c, const uint16_t* x1
     a.yf_cols = 32;
     a.hw = hw; a.hb = hb; a.hy = hy; a.hcols = hcols;
     a.co_base = 0; a.slabs = 1; a.store16 = 0;
-    const long tiles = conv3_tiles<1>(c);
-    if (tiles > 0x7fffffffL) return RT3D_EINVAL;
     natural_weights(&a);
     if (workspace && workspace_bytes >= packed_bytes(c) && (uintptr_t)workspace % 16 == 0) {
         const rt3d_status r = pack_weights(c, &a, 0, workspace, (hipStream_t)stream);
         if (r != RT3D_OK) return r;
     }
-    hipLaunchKernelGGL(conv3_kernel<1>, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)stream, a);
-    DN_TRY(hipGetLastError());
-    return RT3D_OK;
+    return conv3_run<1>(a, (hipStream_t)stream);
 }
 
 rt3d_status rt3d_dn_flip_weights(const uint16_t* w, uint16_t* wt, int32_t cout, int32_t cin, int32_t ksize,
