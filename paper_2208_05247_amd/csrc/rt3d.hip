@@ -591,6 +591,8 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     // the walk re-reads it only after a crossing or a new emission
     float kmaj = __uint_as_float(kNoMajorant);
     uint32_t w = 0, step = 0, iters = 0;
+    // random words of the current free path (id, step): event, cos(theta), phi
+    uint32_t r_event = 0, r_cos = 0, r_phi = 0;
     bool direct = false;
     // merged deposit: cell index, bit 31 set for diffuse; and the one before
     // it, which the next loop iteration writes out (amount 0: none)
@@ -607,7 +609,7 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     // ---- kBinned: the wave's chunk of the deposit buffer (wave-uniform)
     constexpr uint32_t kNoChunk = 0xffffffffu;
     uint32_t chunk = kNoChunk, chunk_pos = kChunk;
-    bool full = false, suspended = false;
+    bool full = false, suspended = false, resumed = false;
 
     // every word of a lane's state that lives from one round to the next
     auto each_word = [&](auto&& f) {
@@ -642,6 +644,7 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         pool_next = uniform(D.waves[wave]);
         pool_end = uniform(D.waves[D.nwaves + wave]);
         drained = pool_next >= cold_params()->photons;
+        resumed = true;
     }
     auto add_heat = [&](uint32_t key, uint32_t amt) {
         const uint32_t cell = key & 0x7fffffffu;
@@ -659,6 +662,15 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         asm volatile("" : "+s"(q));
         return q + (unsigned long long)(kFactored ? gp : 0);
     };
+    auto words = [&](uint32_t at_step) {
+        return philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), at_step, 0u), key());
+    };
+    auto keep_words = [&](uint4 r) {
+        r_event = r.y;
+        r_cos = r.z;
+        r_phi = r.w;
+    };
+    if (kTally == kBinned && resumed) keep_words(words(step));
     auto cell_ix = [&](float v, float inv, int b, int n) {
         return min(max((int)floorf(v * inv), b * n), b * n + n - 1);
     };
@@ -727,11 +739,9 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
                     count(C_ABSORBED, 1);
                     st = kEnded;
                 } else {
-                    // the free path's random words again (not kept while waiting)
-                    const uint4 r = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), step, 0u), key());
-                    const float mu = sqrtf(u01_open(r.z));
+                    const float mu = sqrtf(u01_open(r_cos));
                     float sp, cp;
-                    __sincosf(6.28318530717958647f * u01(r.w), &sp, &cp);
+                    __sincosf(6.28318530717958647f * u01(r_phi), &sp, &cp);
                     const float sn = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
                     ux = sn * cp;
                     uy = sn * sp;
@@ -873,9 +883,14 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         }
         if (st != kLive) continue;
 
-        // ---- random words of this free path: tau, event, cos(theta), phi
-        const uint4 r = philox(make_uint4((uint32_t)id, (uint32_t)(id >> 32), step, 0u), key());
-        if (tau < 0.f) tau = -__logf(u01_open(r.x));
+        // ---- a free path after an emission or a rare event: its length and
+        // random words (after a collision they are formed there)
+        if (tau < 0.f) {
+            const uint4 r = words(step);
+            tau = -__logf(u01_open(r.x));
+            asm volatile("" : "+v"(tau));
+            keep_words(r);
+        }
         const int maj_base = kFactored ? gp * P.nmaj : 0;  // this g-point's majorant grid
 
         // ---- walk acceleration-grid cells until the path ends
@@ -951,6 +966,12 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         }
         const float K = fabsf(kmaj);
         const Local L = local_props<kFactored>(P, gp, cell, k, clear);
+        // the next free path's random words and length, while the cell's
+        // record is on its way (16384 photons on 32x32x64, where few waves
+        // are live: 620 -> 596 us; none where many hide the latency)
+        uint4 rn = words(step + 1);
+        float tau_next = -__logf(u01_open(rn.x));
+        asm volatile("" : "+v"(tau_next), "+v"(rn.y), "+v"(rn.z), "+v"(rn.w));  // (not put off to their use)
         const float iK = rcp(K);
         ++n_coll;
         if (L.ka > 0.f) {
@@ -974,22 +995,27 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
         // scattering with probability k_sca / (K - k_abs), else null
         const float den = K - L.ka;
         const float ps = den > 0.f ? L.ks * rcp(den) : 0.f;
-        const float xi = u01(r.y);
+        const float xi = u01(r_event);
         if (xi < ps) {
             float mu;
             if (xi * L.ke < ps * L.kc) {
-                mu = hg_cos(L.g, u01(r.z));
+                mu = hg_cos(L.g, u01(r_cos));
                 n_scat += 0x10000u;
             } else {
-                mu = rayleigh_cos(u01(r.z));
+                mu = rayleigh_cos(u01(r_cos));
                 n_scat += 1u;
             }
-            turn(ux, uy, uz, mu, u01(r.w));
+            turn(ux, uy, uz, mu, u01(r_phi));
             direct = false;
             if ((n_scat & 0x8000u) | (n_scat & 0x80000000u)) flush_scat();
         }
-        if (w < P.rr_below) st = kRoulette;
-        else ++step;
+        if (w < P.rr_below) {
+            st = kRoulette;
+        } else {
+            ++step;
+            tau = tau_next;
+            keep_words(rn);
+        }
     }
 
     const TraceParams& Q = *cold_params();
