@@ -264,7 +264,7 @@ struct Slot {
 
 // Prefix sums of the full passes and of the photons left over per g-point.
 template <typename Count>
-__host__ __device__ inline void schedule_tables(const Count* photons, int ngp, unsigned long long ncol,
+inline void schedule_tables(const Count* photons, int ngp, unsigned long long ncol,
                                                 unsigned long long* pass_first, unsigned long long* rem_first) {
     unsigned long long passes = 0, rest = 0;
     for (int n = 0; n < ngp; ++n) {
@@ -1235,15 +1235,8 @@ __global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int
 // Heating entries of the energy ledger: ledger[ATM_DIR] = sum(abs_dir),
 // ledger[ATM_DIF] = sum(abs_dif), exact uint64 sums (the other entries are
 // counted by the tracing kernel, so the identity still checks that no
-// deposit was lost).  The two entries are cleared first (clear_atm_kernel);
-// every workgroup adds its partial sums.
-__global__ void clear_atm_kernel(unsigned long long* __restrict__ ledger) {
-    if (threadIdx.x == 0) {
-        ledger[L_ATM_DIR] = 0;
-        ledger[L_ATM_DIF] = 0;
-    }
-}
-
+// deposit was lost).  setup_kernel has cleared the two entries; every
+// workgroup adds its partial sums.
 __global__ void ledger_atm_kernel(const unsigned long long* __restrict__ abs_dir,
                                   const unsigned long long* __restrict__ abs_dif, size_t n,
                                   unsigned long long* __restrict__ ledger) {
@@ -1269,21 +1262,57 @@ __global__ void ledger_atm_kernel(const unsigned long long* __restrict__ abs_dir
     }
 }
 
+// Row maxima of the acceleration cells, formed while a wave packs 64 cells: a
+// row of bx (a power of two, at most a wave) cells is that many lanes next to
+// each other, and the first of them merges their maximum into `out` with an
+// integer max of the FP32 bits (exact, as every value is >= +0; non-positive
+// values and NaN count as 0).  Level k goes to out[k / bz][j / by][bi].  As a
+// pass of its own (a lane per row, reading its cells one after the other) the
+// levels' maxima of 1024x1024x128 cells took 2.3 ms; packing and maxima here
+// take 0.8 together.
+struct RowMax {
+    uint32_t* out;  // null: none (rows_fit is false)
+    FastDiv bx, mx, ny, by, bz;
+    int nmx, nmy;   // acceleration cells in x and y
+
+    __device__ __forceinline__ void operator()(uint32_t cell, bool valid, float v) const {
+        uint32_t m = valid && v > 0.0f ? __float_as_uint(v) : 0u;
+        for (uint32_t o = 1; o < bx.d; o <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, (int)o));
+        if (!valid || (threadIdx.x & (bx.d - 1))) return;
+        const uint32_t t = quotient(cell, bx), row = quotient(t, mx), k = quotient(row, ny);
+        const uint32_t bi = t - row * mx.d, j = row - k * ny.d;
+        atomicMax(&out[((size_t)quotient(k, bz) * nmy + quotient(j, by)) * nmx + bi], m);
+    }
+};
+
 // Interleave the four SoA property arrays into one 16-byte record per cell,
-// so a tentative collision needs a single random 16-byte gather.
+// so a tentative collision needs a single random 16-byte gather; and the
+// majorants of the acceleration cells.
 __global__ void pack_cells_kernel(const float* __restrict__ ke, const float* __restrict__ om,
                                   const float* __restrict__ kc, const float* __restrict__ g,
-                                  float4* __restrict__ out, size_t n) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        out[i] = make_float4(ke[i], om[i], kc[i], g[i]);
+                                  float4* __restrict__ out, size_t n, const RowMax rows) {
+    const int lane = threadIdx.x & 63;
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i - lane < n; i += (size_t)gridDim.x * blockDim.x) {
+        const float k = i < n ? ke[i] : 0.0f;
+        if (i < n) out[i] = make_float4(k, om[i], kc[i], g[i]);
+        if (rows.out) rows((uint32_t)i, i < n, k);
+    }
 }
 
-// Factored medium: per cell (k_ext_cloud, cloud k_abs, g, 0).
+// Factored medium: per cell (k_ext_cloud, cloud k_abs, g, 0), and per level and
+// acceleration column the largest cloud extinction; per g-point and level
+// (k_gas, gas k_abs).
 __global__ void pack_cloud_kernel(const float* __restrict__ kc, const float* __restrict__ om,
-                                  const float* __restrict__ g, float4* __restrict__ out, size_t n) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const float k = kc[i];
-        out[i] = make_float4(k, k * (1.0f - om[i]), g[i], 0.0f);
+                                  const float* __restrict__ g, float4* __restrict__ out, size_t n, const RowMax rows,
+                                  const float* __restrict__ kg, const float* __restrict__ og,
+                                  float2* __restrict__ gas, size_t ngas) {
+    const int lane = threadIdx.x & 63;
+    const size_t first = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = first; i < ngas; i += step) gas[i] = make_float2(kg[i], kg[i] * (1.0f - og[i]));
+    for (size_t i = first; i - lane < n; i += step) {
+        const float k = i < n ? kc[i] : 0.0f;
+        if (i < n) out[i] = make_float4(k, k * (1.0f - om[i]), g[i], 0.0f);
+        if (rows.out) rows((uint32_t)i, i < n, k);
     }
 }
 
@@ -1310,17 +1339,9 @@ __global__ void cell_mask_kernel(const float* __restrict__ kc, uint32_t* __restr
     }
 }
 
-// Factored medium: per g-point and level (k_gas, gas k_abs).
-__global__ void pack_gas_kernel(const float* __restrict__ kg, const float* __restrict__ om, float2* __restrict__ out,
-                                size_t n) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const float k = kg[i];
-        out[i] = make_float2(k, k * (1.0f - om[i]));
-    }
-}
-
 // Factored majorant, step 1: per level k and acceleration column (bi, bj),
 // the largest cloud extinction: layer[k][bj][bi] (FP32 bits, integer max).
+// For bricks whose rows RowMax does not take.
 __global__ void layer_max_kernel(const float4* __restrict__ cells, uint32_t* __restrict__ layer, int nx, int ny,
                                  int nz, int bx, int by) {
     const int mx = nx / bx, my = ny / by;
@@ -1369,37 +1390,59 @@ __global__ void gas_majorant_kernel(const uint32_t* __restrict__ layer, const fl
     }
 }
 
-// Per-g-point schedule tables (prefix sums of the full passes over all
-// columns and of the photons left over) and systematic-sampling column
-// offsets (Philox counter (0, 0, 0xfffffffe, 0) under the g-point's key,
-// word 0).
+// What a trace needs before its kernels, in one launch (a launch costs 2-3 us of
+// a small trace; these were 11 of its 16): the control block (photon-id queue,
+// validation flag) and the per-g-point schedule by the last workgroup, zeros in
+// the tallies and in the majorants to be merged by the others.
+// Schedule: prefix sums of the full passes over all columns and of the photons
+// left over, and systematic-sampling column offsets (Philox counter
+// (0, 0, 0xfffffffe, 0) under the g-point's key, word 0).
+constexpr size_t kCtrlBytes = 256;  // queue counter + validation flag
 constexpr int kMaxGpoints = 256;
-struct BatchInit {
+constexpr int kMaxClears = 10;
+struct Setup {
     unsigned long long photons[kMaxGpoints];
     unsigned long long seed, ncol;
-    int ngp;
+    unsigned long long *control, *pass_first, *rem_first, *gp_col_offset;  // control null: clears only
+    unsigned long long* clear[kMaxClears];
+    size_t words[kMaxClears];  // 64-bit words of each
+    int ngp, nclear;
 };
 
-__global__ void batch_init_kernel(const BatchInit a, unsigned long long* __restrict__ pass_first,
-                                  unsigned long long* __restrict__ rem_first,
-                                  unsigned long long* __restrict__ gp_col_offset) {
+__global__ void __launch_bounds__(256) setup_kernel(const Setup a) {
+    static_assert(kMaxGpoints <= 256, "one g-point a lane");
+    __shared__ unsigned long long s_pass[kMaxGpoints], s_rest[kMaxGpoints];
     const int t = threadIdx.x;
-    if (t == 0) schedule_tables(a.photons, a.ngp, a.ncol, pass_first, rem_first);
-    for (int n = t; n < a.ngp; n += blockDim.x) {
-        const unsigned long long key = a.seed + (unsigned long long)n;
-        const uint4 r = philox(make_uint4(0u, 0u, 0xfffffffeu, 0u), (uint32_t)key, (uint32_t)(key >> 32));
-        gp_col_offset[n] = ((unsigned long long)r.x * a.ncol) >> 32;
+    if (a.control && blockIdx.x == gridDim.x - 1) {
+        for (int i = t; i < (int)(kCtrlBytes / 8); i += 256) a.control[i] = 0;
+        if (t < a.ngp) {
+            s_pass[t] = a.photons[t] / a.ncol;
+            s_rest[t] = a.photons[t] % a.ncol;
+            const unsigned long long key = a.seed + (unsigned long long)t;
+            const uint4 r = philox(make_uint4(0u, 0u, 0xfffffffeu, 0u), (uint32_t)key, (uint32_t)(key >> 32));
+            a.gp_col_offset[t] = ((unsigned long long)r.x * a.ncol) >> 32;
+        }
+        __syncthreads();
+        for (int n = t; n <= a.ngp; n += 256) {
+            unsigned long long passes = 0, rest = 0;
+            for (int m = 0; m < n; ++m) {
+                passes += s_pass[m];
+                rest += s_rest[m];
+            }
+            a.pass_first[n] = passes;
+            a.rem_first[n] = rest;
+        }
+    }
+    for (int q = 0; q < a.nclear; ++q) {
+        unsigned long long* const p = a.clear[q];
+        const size_t n = a.words[q];
+        for (size_t i = blockIdx.x * (size_t)256 + t; i < n; i += (size_t)gridDim.x * 256) p[i] = 0;
     }
 }
 
 // ---------------------------------------------------------------------------
 // Small kernels
 // ---------------------------------------------------------------------------
-__global__ void fill_u64_kernel(unsigned long long* p, size_t n, unsigned long long v) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         p[i] = v;
@@ -1602,7 +1645,6 @@ bool shape_of(const rt3d_grid* g, const rt3d_options* o, Shape* s) {
     return true;
 }
 
-constexpr size_t kCtrlBytes = 256;  // queue counter + validation flag
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 unsigned grid_for(size_t n, unsigned block = 256, unsigned cap = 8192) {
@@ -1611,14 +1653,6 @@ unsigned grid_for(size_t n, unsigned block = 256, unsigned cap = 8192) {
     if (g > cap) g = cap;
     return (unsigned)g;
 }
-
-rt3d_status zero_u64(unsigned long long* p, size_t n, hipStream_t st) {
-    if (!n) return RT3D_OK;
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(grid_for(n)), dim3(256), 0, st, p, n, 0ull);
-    HIP_TRY(hipGetLastError());
-    return RT3D_OK;
-}
-
 
 // Workspace layout (every section 256-byte aligned):
 //   control  256 B: photon-id queue counter, validation flag
@@ -1772,6 +1806,7 @@ struct Launch {
     uint32_t* layer;
     uint32_t* mask;
     TraceParams P;
+    Setup setup;
 };
 
 rt3d_status prepare(const rt3d_grid* grid, int ngp, const uint64_t* photons, const float* albedo, double sza_deg,
@@ -1824,18 +1859,16 @@ rt3d_status prepare(const rt3d_grid* grid, int ngp, const uint64_t* photons, con
     unsigned long long* rem_first = pass_first + ngp + 1;
     unsigned long long* gp_col = rem_first + ngp + 1;
 
-    hipStream_t st = (hipStream_t)stream;
-    // control block (queue counter, validation flag), photon ranges, column offsets
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(1), dim3(32), 0, st, (unsigned long long*)L->ws, kCtrlBytes / 8, 0ull);
-    HIP_TRY(hipGetLastError());
-    BatchInit bi;
-    memset(&bi, 0, sizeof bi);
-    for (int n = 0; n < ngp; ++n) bi.photons[n] = photons[n];
-    bi.seed = seed;
-    bi.ncol = s.ncol;
-    bi.ngp = ngp;
-    hipLaunchKernelGGL(batch_init_kernel, dim3(1), dim3(256), 0, st, bi, pass_first, rem_first, gp_col);
-    HIP_TRY(hipGetLastError());
+    Setup& b = L->setup;
+    memset(&b, 0, sizeof b);
+    for (int n = 0; n < ngp; ++n) b.photons[n] = photons[n];
+    b.seed = seed;
+    b.ncol = s.ncol;
+    b.ngp = ngp;
+    b.control = (unsigned long long*)L->ws;
+    b.pass_first = pass_first;
+    b.rem_first = rem_first;
+    b.gp_col_offset = gp_col;
 
     TraceParams& P = L->P;
     memset(&P, 0, sizeof P);
@@ -1884,6 +1917,14 @@ rt3d_status prepare(const rt3d_grid* grid, int ngp, const uint64_t* photons, con
     return RT3D_OK;
 }
 
+rt3d_status run_setup(const Setup& b, hipStream_t st) {
+    size_t most = 1;
+    for (int q = 0; q < b.nclear; ++q) most = std::max(most, b.words[q]);
+    hipLaunchKernelGGL(setup_kernel, dim3(grid_for(most)), dim3(256), 0, st, b);
+    HIP_TRY(hipGetLastError());
+    return RT3D_OK;
+}
+
 rt3d_status validated(const Launch& L, hipStream_t st) {
     HIP_TRY(hipGetLastError());
     uint32_t h = 0;
@@ -1892,17 +1933,64 @@ rt3d_status validated(const Launch& L, hipStream_t st) {
     return h ? RT3D_EDOMAIN : RT3D_OK;
 }
 
-rt3d_status clear_outputs(const Launch& L, const rt3d_tallies* out, hipStream_t st) {
-    if (L.o.flags & RT3D_FLAG_ACCUMULATE) return RT3D_OK;
-    rt3d_status z;
-    if ((z = zero_u64((unsigned long long*)out->abs_dir, L.s.ncell, st)) != RT3D_OK) return z;
-    if ((z = zero_u64((unsigned long long*)out->abs_dif, L.s.ncell, st)) != RT3D_OK) return z;
-    if ((z = zero_u64((unsigned long long*)out->sfc_dir, L.s.ncol, st)) != RT3D_OK) return z;
-    if ((z = zero_u64((unsigned long long*)out->sfc_dif, L.s.ncol, st)) != RT3D_OK) return z;
-    if ((z = zero_u64((unsigned long long*)out->sfc_abs, L.s.ncol, st)) != RT3D_OK) return z;
-    if ((z = zero_u64((unsigned long long*)out->toa_up, L.s.ncol, st)) != RT3D_OK) return z;
-    if ((z = zero_u64((unsigned long long*)out->ledger, RT3D_LEDGER_N, st)) != RT3D_OK) return z;
-    return zero_u64((unsigned long long*)out->stats, RT3D_STATS_N, st);
+// The setup launch; with RT3D_FLAG_VALIDATE the control block is set up and
+// `validate` run before anything is cleared.  merged: the maxima that the
+// packing kernel merges (nmerged 32-bit words of a 256-byte aligned section).
+template <typename Validate>
+rt3d_status begin(Launch& L, const rt3d_tallies* out, uint32_t* merged, size_t nmerged, hipStream_t st,
+                  Validate&& validate) {
+    Setup& b = L.setup;
+    if (L.o.flags & RT3D_FLAG_VALIDATE) {
+        rt3d_status r = run_setup(b, st);
+        if (r != RT3D_OK) return r;
+        validate();
+        if ((r = validated(L, st)) != RT3D_OK) return r;
+        b.control = nullptr;
+    }
+    auto clear = [&](void* p, size_t words) {
+        b.clear[b.nclear] = (unsigned long long*)p;
+        b.words[b.nclear++] = words;
+    };
+    clear(merged, (nmerged + 1) / 2);
+    if (L.o.flags & RT3D_FLAG_ACCUMULATE) {  // only the entries that ledger_atm_kernel forms anew
+        clear(out->ledger + L_ATM_DIR, 1);
+        clear(out->ledger + L_ATM_DIF, 1);
+    } else {
+        clear(out->abs_dir, L.s.ncell);
+        clear(out->abs_dif, L.s.ncell);
+        clear(out->sfc_dir, L.s.ncol);
+        clear(out->sfc_dif, L.s.ncol);
+        clear(out->sfc_abs, L.s.ncol);
+        clear(out->toa_up, L.s.ncol);
+        clear(out->ledger, RT3D_LEDGER_N);
+        clear(out->stats, RT3D_STATS_N);
+    }
+    return run_setup(b, st);
+}
+
+// Row maxima with bricks of bz levels into out, by the packing kernel where a
+// brick's row is a power of two of at most 64 cells (then rows begin at
+// multiples of bx in the cell index, and in the wave).
+RowMax row_max(const Shape& s, int bz, uint32_t* out) {
+    RowMax r;
+    r.out = s.bx <= 64 && (s.bx & (s.bx - 1)) == 0 ? out : nullptr;
+    r.bx = fast_div((uint32_t)s.bx);
+    r.mx = fast_div((uint32_t)s.mx);
+    r.ny = fast_div((uint32_t)s.ny);
+    r.by = fast_div((uint32_t)s.by);
+    r.bz = fast_div((uint32_t)bz);
+    r.nmx = s.mx;
+    r.nmy = s.my;
+    return r;
+}
+
+// The row pass of the majorant build as a launch of its own.
+rt3d_status merge_majorants(const Shape& s, const float* k_ext, uint32_t* majorant, hipStream_t st) {
+    const size_t n = (size_t)s.mx * s.ny * s.nz;
+    hipLaunchKernelGGL(majorant_kernel, dim3(grid_for(n, 256, 16384)), dim3(256), 0, st, k_ext, majorant, s.nx, s.ny,
+                       s.nz, s.bx, s.by, s.bz);
+    HIP_TRY(hipGetLastError());
+    return RT3D_OK;
 }
 
 constexpr unsigned kWavePhotons = 16;  // photons a wave has at least, where there are few
@@ -1989,8 +2077,6 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
         HIP_TRY(hipEventRecord(g_t1, st));
         g_timed = true;
     }
-    hipLaunchKernelGGL(clear_atm_kernel, dim3(1), dim3(64), 0, st, L.P.ledger);
-    HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(ledger_atm_kernel, dim3(grid_for(L.s.ncell, 256, 2048)), dim3(256), 0, st, L.P.abs_dir,
                        L.P.abs_dif, L.s.ncell, L.P.ledger);
     HIP_TRY(hipGetLastError());
@@ -2091,11 +2177,7 @@ rt3d_status rt3d_majorant_build(const rt3d_grid* grid, const float* k_ext, int32
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(s.nmaj)), dim3(256), 0, st, (uint32_t*)majorant, s.nmaj, 0u);
     HIP_TRY(hipGetLastError());
-    const size_t n = (size_t)s.mx * s.ny * s.nz;
-    hipLaunchKernelGGL(majorant_kernel, dim3(grid_for(n, 256, 16384)), dim3(256), 0, st, k_ext,
-                       (uint32_t*)majorant, s.nx, s.ny, s.nz, s.bx, s.by, s.bz);
-    HIP_TRY(hipGetLastError());
-    return RT3D_OK;
+    return merge_majorants(s, k_ext, (uint32_t*)majorant, st);
 }
 
 rt3d_status rt3d_trace(const rt3d_grid* grid, const rt3d_optical_props* props, const float* surface_albedo,
@@ -2109,15 +2191,15 @@ rt3d_status rt3d_trace(const rt3d_grid* grid, const rt3d_optical_props* props, c
                              workspace_bytes, stream, false, &L);
     if (st != RT3D_OK) return st;
     hipStream_t hs = (hipStream_t)stream;
-    if (L.o.flags & RT3D_FLAG_VALIDATE) {
+    st = begin(L, out, (uint32_t*)L.maj, L.s.nmaj, hs, [&] {
         hipLaunchKernelGGL(validate_kernel, dim3(grid_for(L.s.ncell, 256, 4096)), dim3(256), 0, hs, props->k_ext,
                            props->k_ext_cloud, props->ssa, props->g, surface_albedo, L.s.ncell, L.s.ncol, L.flag);
-        if ((st = validated(L, hs)) != RT3D_OK) return st;
-    }
-    if ((st = clear_outputs(L, out, hs)) != RT3D_OK) return st;
-    if ((st = rt3d_majorant_build(grid, props->k_ext, L.s.bx, L.s.by, L.s.bz, L.maj, stream)) != RT3D_OK) return st;
+    });
+    if (st != RT3D_OK) return st;
+    const RowMax rows = row_max(L.s, L.s.bz, (uint32_t*)L.maj);
+    if (!rows.out && (st = merge_majorants(L.s, props->k_ext, (uint32_t*)L.maj, hs)) != RT3D_OK) return st;
     hipLaunchKernelGGL(pack_cells_kernel, dim3(grid_for(L.s.ncell, 256, 16384)), dim3(256), 0, hs, props->k_ext,
-                       props->ssa, props->k_ext_cloud, props->g, L.cells, L.s.ncell);
+                       props->ssa, props->k_ext_cloud, props->g, L.cells, L.s.ncell, rows);
     HIP_TRY(hipGetLastError());
     return launch_trace(L, false, hs);
 }
@@ -2158,32 +2240,30 @@ rt3d_status rt3d_trace_batched(const rt3d_grid* grid, int32_t n_gpoints, const r
     if (st != RT3D_OK) return st;
     L.P.gp_diffuse = medium->diffuse_fraction;
     hipStream_t hs = (hipStream_t)stream;
-    if (L.o.flags & RT3D_FLAG_VALIDATE) {
+    const size_t nlayer = (size_t)L.s.nz * L.s.my * L.s.mx;
+    st = begin(L, out, L.layer, nlayer, hs, [&] {
         hipLaunchKernelGGL(validate_batched_kernel, dim3(grid_for(L.s.ncell, 256, 4096)), dim3(256), 0, hs,
                            medium->k_gas, medium->ssa_gas, (size_t)n_gpoints * L.s.nz, medium->k_cloud,
                            medium->ssa_cloud, medium->g_cloud, surface_albedo, L.s.ncell, L.s.ncol,
                            medium->diffuse_fraction, n_gpoints, L.flag);
-        if ((st = validated(L, hs)) != RT3D_OK) return st;
-    }
-    if ((st = clear_outputs(L, out, hs)) != RT3D_OK) return st;
+    });
+    if (st != RT3D_OK) return st;
     const size_t ngas = (size_t)n_gpoints * L.s.nz;
-    hipLaunchKernelGGL(pack_cloud_kernel, dim3(grid_for(L.s.ncell, 256, 16384)), dim3(256), 0, hs, medium->k_cloud,
-                       medium->ssa_cloud, medium->g_cloud, L.cells, L.s.ncell);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(pack_gas_kernel, dim3(grid_for(ngas)), dim3(256), 0, hs, medium->k_gas, medium->ssa_gas,
-                       L.gas, ngas);
+    const RowMax rows = row_max(L.s, 1, L.layer);
+    hipLaunchKernelGGL(pack_cloud_kernel, dim3(grid_for(std::max(L.s.ncell, ngas), 256, 16384)), dim3(256), 0, hs,
+                       medium->k_cloud, medium->ssa_cloud, medium->g_cloud, L.cells, L.s.ncell, rows, medium->k_gas,
+                       medium->ssa_gas, L.gas, ngas);
     HIP_TRY(hipGetLastError());
     const size_t nmask = L.P.cell_mask ? L.s.nmaj * (size_t)L.P.mask_words : 0;
     if (nmask) hipLaunchKernelGGL(cell_mask_kernel, dim3(grid_for(nmask, 256, 16384)), dim3(256), 0, hs, medium->k_cloud, L.mask,
                        L.s.nx, L.s.ny, L.s.bx, L.s.by, L.s.bz, L.s.mx, L.s.my, L.P.mask_words, nmask);
     HIP_TRY(hipGetLastError());
-    const size_t nlayer = (size_t)L.s.nz * L.s.my * L.s.mx;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(nlayer)), dim3(256), 0, hs, L.layer, nlayer, 0u);
-    HIP_TRY(hipGetLastError());
-    const size_t nrow = (size_t)L.s.mx * L.s.ny * L.s.nz;
-    hipLaunchKernelGGL(layer_max_kernel, dim3(grid_for(nrow, 256, 16384)), dim3(256), 0, hs, L.cells, L.layer,
-                       L.s.nx, L.s.ny, L.s.nz, L.s.bx, L.s.by);
-    HIP_TRY(hipGetLastError());
+    if (!rows.out) {
+        const size_t nrow = (size_t)L.s.mx * L.s.ny * L.s.nz;
+        hipLaunchKernelGGL(layer_max_kernel, dim3(grid_for(nrow, 256, 16384)), dim3(256), 0, hs, L.cells, L.layer,
+                           L.s.nx, L.s.ny, L.s.nz, L.s.bx, L.s.by);
+        HIP_TRY(hipGetLastError());
+    }
     const size_t nm = L.s.nmaj * (size_t)n_gpoints;
     hipLaunchKernelGGL(gas_majorant_kernel, dim3(grid_for(nm, 256, 16384)), dim3(256), 0, hs, L.layer, L.gas,
                        L.maj, n_gpoints, L.s.nz, L.s.mx, L.s.my, L.s.bz);
