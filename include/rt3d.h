@@ -290,8 +290,8 @@ void rt3d_default_options(rt3d_options* opt);
  * (majorant grid, work-queue counter and flags).  Returns 0 on bad input.
  * What a workspace holds beyond that, rt3d_trace uses as a buffer for heating
  * deposits, where it is large enough for that (about 90 MB; 1 GiB is ample)
- * and the call has 2^24 photons or more on at most 2^24 cells: the tallies
- * are the same, and fewer of their updates are atomics. */
+ * and the call has 2^22 photons or more on more than 2^20 - 2^13 and at most
+ * 2^24 cells: the tallies are the same, and fewer of their updates are atomics. */
 size_t rt3d_workspace_size(const rt3d_grid* grid, const rt3d_options* opt);
 
 /* Acceleration grid (sec. 2.3, acceleration grid paragraph): majorant[b] =

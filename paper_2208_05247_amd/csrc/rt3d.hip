@@ -1755,20 +1755,28 @@ void schedule_of(const Shape& s, int ngp, const uint64_t* photons, const rt3d_op
 
 // The deposit buffer in the part of the workspace behind the sections above,
 // or false where there is no room for it or no use: at least kMinTiles tiles,
-// at most kMaxBins bins, kMinPhotons photons, one g-point.  256x256x128 cells
-// (1024 bins, a buffer of 1 GiB), whole call, atomics against the buffer: 2^22
-// photons 7.8 / 7.0 ms (one round), 2^23 14.1 / 14.4, 2^24 26.4 / 22.1, 2^25
-// 51.3 / 41.8, 2^26 101.1 / 81.4.  Of the 81.4 ms the sort takes 13.4 (2.5 TB/s)
-// and the addition 13.1.  The kernel for several g-points, slower itself,
-// gained at most 2 % (128^3 cells, 112 g-points, 3.4e7 photons: 38.3 / 37.4 ms)
-// and lost up to 4 % below 8e6 photons, so it keeps the atomics.
+// kMinBins to kMaxBins bins, kMinPhotons photons, one g-point.  Whole calls in
+// ms, atomics against the buffer (buffer of eight workspaces):
+//     cells (bins)          2^22 photons   2^23          2^24          2^26
+//   64x64x64 (32)            8.2 /  8.7   15.0 / 14.6   28.6 / 28.7
+//   90x66x50 (37), 6e6 photons 8.6 / 11.3: few workgroups add unlike bins
+//   64x64x128 (64)           8.5 /  8.3   15.9 / 15.3   30.5 / 29.1
+//   128x64x128 (128)         8.4 /  7.8   15.3 / 14.1   28.9 / 26.1
+//   128x128x128 (256)        7.3 /  6.2   13.4 / 11.0   25.2 / 20.0
+//   256x128x128 (512)        7.5 /  6.8   13.8 / 14.1   25.6 / 21.5
+//   256x256x128 (1024)       7.7 /  6.8   14.0 / 12.4   26.4 / 22.0   101 / 81.4
+// Of the 81.4 ms the sort takes 13.4 (2.5 TB/s) and the addition 13.1.  The
+// kernel for several g-points, slower itself, gained at most 2 % (128^3 cells,
+// 112 g-points, 3.4e7 photons: 38.3 / 37.4 ms) and lost up to 4 % below 8e6
+// photons, so it keeps the atomics.
 constexpr uint32_t kMinTiles = 256;
-constexpr unsigned long long kMinPhotons = 1ull << 24;
+constexpr size_t kMinBins = 128;
+constexpr unsigned long long kMinPhotons = 1ull << 22;
 
 bool deposit_buffer(const Shape& s, unsigned long long photons, char* at, size_t bytes, uint32_t nlanes,
                     Deposits* D) {
     const size_t nbins = (s.ncell + kBinCells - 1) / kBinCells;
-    if (nbins > kMaxBins || photons < kMinPhotons) return false;
+    if (nbins < kMinBins || nbins > kMaxBins || photons < kMinPhotons) return false;
     D->nbins = (uint32_t)nbins;
     D->nlanes = nlanes;
     D->nwaves = nlanes / 64;
