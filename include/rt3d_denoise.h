@@ -119,6 +119,10 @@ rt3d_status rt3d_dn_conv3d_fwd_head_ws(const rt3d_dn_conv* c, const uint16_t* x1
  * shape. */
 rt3d_status rt3d_dn_conv3d_fwd_pool(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* w, const float* bias,
                                     int32_t relu, uint16_t* y, uint16_t* ypool, void* stream);
+/* The same with weights of w_channels (4 or 16, of which the first 4 are used;
+ * with c1 = 5 16) inputs a tap. */
+rt3d_status rt3d_dn_conv3d_fwd_pool_w(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* w, int32_t w_channels,
+                                      const float* bias, int32_t relu, uint16_t* y, uint16_t* ypool, void* stream);
 
 /* wt[ci][k^3 - 1 - t][co] = w[co][t][ci]: the kernel of the data gradient. */
 rt3d_status rt3d_dn_flip_weights(const uint16_t* w, uint16_t* wt, int32_t cout, int32_t cin, int32_t ksize,
@@ -203,6 +207,13 @@ rt3d_status rt3d_dn_features(const float* hdir, const float* hdif, const float* 
                              float scale, uint64_t nvox, int32_t cpad, const float* direct, uint16_t* feat, float* base,
                              void* stream);
 
+/* rt3d_dn_features with the scale read on the device, in stream order: the
+ * first word of rt3d_dn_field_scale's work, rounded to FP32.  The caller checks
+ * that it is > 0 there. */
+rt3d_status rt3d_dn_features_at(const float* hdir, const float* hdif, const float* k_ext, const float* k_abs, float dz,
+                                const double* scale, uint64_t nvox, int32_t cpad, const float* direct, uint16_t* feat,
+                                float* base, void* stream);
+
 /* Direct-beam feature (an optional fifth network input, channel 4 of
  * rt3d_dn_features = direct/scale): a deterministic estimate of the heating
  * by the unscattered sun beam, in a gray medium k_ext, k_abs (FP32 device
@@ -238,6 +249,9 @@ rt3d_status rt3d_dn_field_scale(const float* hdir, const float* hdif, uint64_t n
  * out: FP32 [nvox][cpad] network output; all FP32 device arrays. */
 rt3d_status rt3d_dn_residual_unfeature(const float* out, int32_t cpad, const float* hdir_in, const float* hdif_in,
                                        float scale, uint64_t nvox, float* hdir, float* hdif, void* stream);
+/* The same with the scale read on the device, as in rt3d_dn_features_at. */
+rt3d_status rt3d_dn_residual_unfeature_at(const float* out, int32_t cpad, const float* hdir_in, const float* hdif_in,
+                                          const double* scale, uint64_t nvox, float* hdir, float* hdif, void* stream);
 
 /* hdir[v] = max(pred[v][0], 0) scale, hdif[v] = max(pred[v][1], 0) scale. */
 rt3d_status rt3d_dn_unfeature(const float* pred, float scale, uint64_t nvox, float* hdir, float* hdif,

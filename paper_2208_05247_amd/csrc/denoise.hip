@@ -78,7 +78,9 @@ struct ConvArgs {
     float* yf;             // optional FP32 copy [vox][yf_cols] of channels < yf_cols
     int D, H, W, cout, relu;
     int up1;               // x1 at half resolution, read nearest-upsampled
-    int w_row, w_half, w_tap, w_chunk;  // byte steps of the 3x3x3 weights: output channel, 8 inputs, tap, 16 inputs
+    // byte steps of the 3x3x3 weights: output channel, 8 inputs, tap, 16 inputs
+    // (w_row, conv3_c4_pool_kernel: weights of a tap, 4 used)
+    int w_row, w_half, w_tap, w_chunk;
     int yf_cols;
     // optional 1x1x1 head fused after a 32-output 3x3x3 convolution:
     // hy[vox][hcols] = FP32 channels [0, hcols) of conv1(bf16(y), hw) + hb
@@ -702,11 +704,11 @@ conv3_c4_pool_kernel(const ConvArgs a, uint16_t* __restrict__ yp) {
         }
     }
     uint4 bv[9];
-    const uint16_t* wrow = a.w + (long)m * 27 * 4;
+    const uint16_t* wrow = a.w + (long)m * 27 * a.w_row;
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
-        const uint2 lo = *(const uint2*)(wrow + (q * 3 + 2 * half) * 4);
-        const uint2 hi = half ? make_uint2(0u, 0u) : *(const uint2*)(wrow + (q * 3 + 1) * 4);
+        const uint2 lo = *(const uint2*)(wrow + (q * 3 + 2 * half) * a.w_row);
+        const uint2 hi = half ? make_uint2(0u, 0u) : *(const uint2*)(wrow + (q * 3 + 1) * a.w_row);
         bv[q] = make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
     __syncthreads();
@@ -1700,10 +1702,18 @@ __global__ void to_bf16_kernel(const float* __restrict__ x, uint16_t* __restrict
 // thickness for extinction and for absorption of the cell, zero padding to
 // cpad channels (BF16); the scaled heating is also written as the FP32
 // residual base [v][2].
+// The reciprocal of the field scale as the host forms it from its value: 1 / s
+// in FP32 (in FP64 and rounded, which is the same).
+__device__ __forceinline__ float inverse_of(float s) { return (float)(1.0 / (double)s); }
+
+// scale: read there by the kernel (the caller then need not wait for
+// field_scale_kernel), or null: inv_scale.
 __global__ void features_kernel(const float* __restrict__ hdir, const float* __restrict__ hdif,
                                 const float* __restrict__ k_ext, const float* __restrict__ k_abs, float dz,
                                 float inv_scale, size_t nvox, int cpad, const float* __restrict__ direct,
-                                uint16_t* __restrict__ feat, float* __restrict__ base) {
+                                uint16_t* __restrict__ feat, float* __restrict__ base,
+                                const double* __restrict__ scale) {
+    if (scale) inv_scale = inverse_of((float)*scale);
     for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < nvox; v += (size_t)gridDim.x * blockDim.x) {
         const float a = hdir[v] * inv_scale, b = hdif[v] * inv_scale;
         uint16_t* f = feat + v * cpad;
@@ -1841,7 +1851,12 @@ __device__ __forceinline__ float mul_rounded(float a, float b) {
 // features_kernel's base, mse_kernel and unfeature_kernel in turn.
 __global__ void residual_unfeature_kernel(const float* __restrict__ out, int cpad, const float* __restrict__ hdir_in,
                                           const float* __restrict__ hdif_in, float inv_scale, float scale, size_t nvox,
-                                          float* __restrict__ hdir, float* __restrict__ hdif) {
+                                          float* __restrict__ hdir, float* __restrict__ hdif,
+                                          const double* __restrict__ scale_at) {
+    if (scale_at) {
+        scale = (float)*scale_at;
+        inv_scale = inverse_of(scale);
+    }
     for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < nvox; v += (size_t)gridDim.x * blockDim.x) {
         const float p0 = out[v * cpad] + mul_rounded(hdir_in[v], inv_scale);
         const float p1 = out[v * cpad + 1] + mul_rounded(hdif_in[v], inv_scale);
@@ -1985,13 +2000,19 @@ const char* rt3d_dn_last_error(void) { return d_err; }
 
 rt3d_status rt3d_dn_conv3d_fwd_pool(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* w, const float* bias,
                                     int32_t relu, uint16_t* y, uint16_t* ypool, void* stream) {
+    return rt3d_dn_conv3d_fwd_pool_w(c, x1, w, c && c->c1 == 5 ? 16 : 4, bias, relu, y, ypool, stream);
+}
+
+rt3d_status rt3d_dn_conv3d_fwd_pool_w(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* w, int32_t w_channels,
+                                      const float* bias, int32_t relu, uint16_t* y, uint16_t* ypool, void* stream) {
     if (!c || !x1 || !w || !y || !ypool) return RT3D_EINVAL;
     if ((c->c1 != 4 && c->c1 != 5) || c->c2 != 0 || c->ksize != 3 || c->cout != 32 || c->up1 || c->yf_cols)
         return RT3D_EINVAL;
     if (c->D <= 0 || c->H <= 0 || c->W <= 0 || c->D % 2 || c->H % 2 || c->W % 2) return RT3D_EINVAL;
     ConvArgs a;
     memset(&a, 0, sizeof a);
-    a.x1 = x1; a.c1 = c->c1; a.w = w; a.bias = bias; a.y1 = y; a.o1 = 32;
+    if (w_channels != 16 && !(w_channels == 4 && c->c1 == 4)) return RT3D_EINVAL;
+    a.x1 = x1; a.c1 = c->c1; a.w = w; a.w_row = w_channels; a.bias = bias; a.y1 = y; a.o1 = 32;
     a.D = c->D; a.H = c->H; a.W = c->W; a.cout = 32; a.relu = relu ? 1 : 0;
     const long tiles = (long)(c->D / 2) * ((c->H + kTY32 - 1) / kTY32) * ((c->W + kTX - 1) / kTX);
     if (tiles > 0x7fffffffL) return RT3D_EINVAL;
@@ -2299,17 +2320,30 @@ rt3d_status rt3d_dn_to_bf16(const float* x, uint16_t* y, uint64_t n, void* strea
     return RT3D_OK;
 }
 
-rt3d_status rt3d_dn_features(const float* hdir, const float* hdif, const float* k_ext, const float* k_abs, float dz,
-                             float scale, uint64_t nvox, int32_t cpad, const float* direct, uint16_t* feat, float* base,
-                             void* stream) {
+static rt3d_status features_run(const float* hdir, const float* hdif, const float* k_ext, const float* k_abs, float dz,
+                                float scale, const double* scale_at, uint64_t nvox, int32_t cpad, const float* direct,
+                                uint16_t* feat, float* base, void* stream) {
     if (!hdir || !hdif || !k_ext || !k_abs || !feat || (cpad != 4 && cpad != 8 && (cpad < 16 || cpad % 16)) ||
         !(scale > 0.0f))
         return RT3D_EINVAL;
     if (direct && cpad < 5) return RT3D_EINVAL;
     hipLaunchKernelGGL(features_kernel, dim3(blocks_for(nvox)), dim3(256), 0, (hipStream_t)stream, hdir, hdif, k_ext,
-                       k_abs, dz, 1.0f / scale, (size_t)nvox, cpad, direct, feat, base);
+                       k_abs, dz, 1.0f / scale, (size_t)nvox, cpad, direct, feat, base, scale_at);
     DN_TRY(hipGetLastError());
     return RT3D_OK;
+}
+
+rt3d_status rt3d_dn_features(const float* hdir, const float* hdif, const float* k_ext, const float* k_abs, float dz,
+                             float scale, uint64_t nvox, int32_t cpad, const float* direct, uint16_t* feat, float* base,
+                             void* stream) {
+    return features_run(hdir, hdif, k_ext, k_abs, dz, scale, nullptr, nvox, cpad, direct, feat, base, stream);
+}
+
+rt3d_status rt3d_dn_features_at(const float* hdir, const float* hdif, const float* k_ext, const float* k_abs, float dz,
+                                const double* scale, uint64_t nvox, int32_t cpad, const float* direct, uint16_t* feat,
+                                float* base, void* stream) {
+    if (!scale) return RT3D_EINVAL;
+    return features_run(hdir, hdif, k_ext, k_abs, dz, 1.0f, scale, nvox, cpad, direct, feat, base, stream);
 }
 
 rt3d_status rt3d_dn_unfeature(const float* pred, float scale, uint64_t nvox, float* hdir, float* hdif,
@@ -2331,13 +2365,25 @@ rt3d_status rt3d_dn_field_scale(const float* hdir, const float* hdif, uint64_t n
     return RT3D_OK;
 }
 
-rt3d_status rt3d_dn_residual_unfeature(const float* out, int32_t cpad, const float* hdir_in, const float* hdif_in,
-                                       float scale, uint64_t nvox, float* hdir, float* hdif, void* stream) {
+static rt3d_status residual_unfeature_run(const float* out, int32_t cpad, const float* hdir_in, const float* hdif_in,
+                                          float scale, const double* scale_at, uint64_t nvox, float* hdir, float* hdif,
+                                          void* stream) {
     if (!out || !hdir_in || !hdif_in || !hdir || !hdif || cpad < 2 || !(scale > 0.0f)) return RT3D_EINVAL;
     hipLaunchKernelGGL(residual_unfeature_kernel, dim3(blocks_for(nvox)), dim3(256), 0, (hipStream_t)stream, out,
-                       cpad, hdir_in, hdif_in, 1.0f / scale, scale, (size_t)nvox, hdir, hdif);
+                       cpad, hdir_in, hdif_in, 1.0f / scale, scale, (size_t)nvox, hdir, hdif, scale_at);
     DN_TRY(hipGetLastError());
     return RT3D_OK;
+}
+
+rt3d_status rt3d_dn_residual_unfeature(const float* out, int32_t cpad, const float* hdir_in, const float* hdif_in,
+                                       float scale, uint64_t nvox, float* hdir, float* hdif, void* stream) {
+    return residual_unfeature_run(out, cpad, hdir_in, hdif_in, scale, nullptr, nvox, hdir, hdif, stream);
+}
+
+rt3d_status rt3d_dn_residual_unfeature_at(const float* out, int32_t cpad, const float* hdir_in, const float* hdif_in,
+                                          const double* scale, uint64_t nvox, float* hdir, float* hdif, void* stream) {
+    if (!scale) return RT3D_EINVAL;
+    return residual_unfeature_run(out, cpad, hdir_in, hdif_in, 1.0f, scale, nvox, hdir, hdif, stream);
 }
 
 rt3d_status rt3d_dn_direct_feature(const rt3d_dn_direct* d, const float* k_ext, const float* k_abs,

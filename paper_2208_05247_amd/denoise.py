@@ -66,6 +66,7 @@ def load():
         "rt3d_dn_conv3d_fwd_head": [ctypes.POINTER(_Conv), P, P, P, P, I, P, P, I, P, P],
         "rt3d_dn_conv3d_fwd_head_ws": [ctypes.POINTER(_Conv), P, P, P, P, I, P, P, I, P, P, ctypes.c_size_t, P],
         "rt3d_dn_conv3d_fwd_pool": [ctypes.POINTER(_Conv), P, P, P, I, P, P, P],
+        "rt3d_dn_conv3d_fwd_pool_w": [ctypes.POINTER(_Conv), P, P, I, P, I, P, P, P],
         "rt3d_dn_flip_weights": [P, P, I, I, I, P],
         "rt3d_dn_conv3d_wgrad": [ctypes.POINTER(_Conv), P, P, P, P, P, P],
         "rt3d_dn_conv3d_wgrad_ws": [ctypes.POINTER(_Conv), P, P, P, P, P, P, ctypes.c_size_t, P],
@@ -79,10 +80,12 @@ def load():
         "rt3d_dn_adam": [P, P, P, P, P, U, ctypes.c_float, ctypes.c_float, ctypes.c_float, ctypes.c_float, I, P],
         "rt3d_dn_to_bf16": [P, P, U, P],
         "rt3d_dn_features": [P, P, P, P, ctypes.c_float, ctypes.c_float, U, I, P, P, P, P],
+        "rt3d_dn_features_at": [P, P, P, P, ctypes.c_float, P, U, I, P, P, P, P],
         "rt3d_dn_direct_feature": [ctypes.POINTER(_Direct), P, P, P, P, P, P],
         "rt3d_dn_unfeature": [P, ctypes.c_float, U, P, P, P],
         "rt3d_dn_field_scale": [P, P, U, P, P],
         "rt3d_dn_residual_unfeature": [P, I, P, P, ctypes.c_float, U, P, P, P],
+        "rt3d_dn_residual_unfeature_at": [P, I, P, P, P, U, P, P, P],
     }
     for name, args in sig.items():
         f = getattr(lib, name)
@@ -188,15 +191,17 @@ def conv_fwd_head(x1, x2, w, bias, relu, hw, hb, out, up1=False):
 def conv_fwd_pool(x1, w, bias, relu, y, ypool):
     """The packed first layer and the 2x2x2 average pooling of its output in
     one launch: y [D][H][W][32] and ypool [D/2][H/2][W/2][32].  Four inputs:
-    x1 BF16 [D][H][W][4], w [32][27][4], bitwise conv_fwd followed by pool2;
+    x1 BF16 [D][H][W][4], w [32][27][4] (or the 16-channel weights, of which
+    the first four are used), bitwise conv_fwd followed by pool2;
     five inputs (the direct-beam feature): x1 [D][H][W][8] (channels 5-7
     zero), w the 16-channel weights [32][27][16]."""
     D, H, W, cx = x1.shape
     if cx not in (4, 8) or tuple(y.shape) != (D, H, W, 32) or tuple(ypool.shape) != (D // 2, H // 2, W // 2, 32):
         raise ValueError("conv_fwd_pool: x1 [D][H][W][4 or 8], y [D][H][W][32], ypool [D/2][H/2][W/2][32]")
     c = _Conv(D, H, W, 4 if cx == 4 else 5, 0, 32, 3, 0, 0)
-    _check(load().rt3d_dn_conv3d_fwd_pool(ctypes.byref(c), _p(x1), _p(w), _p(bias), int(relu), _p(y), _p(ypool),
-                                          _s()), "rt3d_dn_conv3d_fwd_pool")
+    wc = 16 if cx == 8 or w.shape[-1] == 16 else 4
+    _check(load().rt3d_dn_conv3d_fwd_pool_w(ctypes.byref(c), _p(x1), _p(w), wc, _p(bias), int(relu), _p(y), _p(ypool),
+                                            _s()), "rt3d_dn_conv3d_fwd_pool")
 
 
 def flip(w, cout, cin, ksize, out):
@@ -368,8 +373,7 @@ class Denoiser:
             L = self.layers[0]
             a["e0"] = bf16_empty(D, H, W, L.cout)
             a["p0"] = bf16_empty(D // 2, H // 2, W // 2, L.cout)
-            w0 = self.pb["e0"][:, :, :4].contiguous() if cf == 4 else self.pb["e0"]
-            conv_fwd_pool(feat, w0, self.bias["e0"], L.relu, a["e0"], a["p0"])
+            conv_fwd_pool(feat, self.pb["e0"], self.bias["e0"], L.relu, a["e0"], a["p0"])
         else:
             a["e0"] = self._conv("e0", feat)
             a["p0"] = pool2(a["e0"])
@@ -507,15 +511,20 @@ def direct_feature(k_ext: torch.Tensor, k_abs: torch.Tensor, grid, sza: float, a
 SCALE_WORK = 2049  # RT3D_DN_SCALE_WORK
 
 
-def field_scale(hdir: torch.Tensor, hdif: torch.Tensor) -> float:
-    """(mean hdir + mean hdif) / 2 (1 if not positive), reduced on the device
-    in FP64 in a fixed order (rt3d_dn_field_scale); returned to the host."""
+def _field_scale(hdir: torch.Tensor, hdif: torch.Tensor) -> torch.Tensor:
+    """field_scale on the device, the first word of an FP64 tensor."""
     if hdir.dtype != torch.float32 or hdif.dtype != torch.float32 or hdir.shape != hdif.shape:
         raise ValueError("field_scale: two FP32 fields of one shape")
     work = torch.empty(SCALE_WORK, dtype=torch.float64, device=hdir.device)
     _check(load().rt3d_dn_field_scale(_p(hdir.contiguous()), _p(hdif.contiguous()), hdir.numel(), _p(work), _s()),
            "rt3d_dn_field_scale")
-    return float(work[0].item())
+    return work
+
+
+def field_scale(hdir: torch.Tensor, hdif: torch.Tensor) -> float:
+    """(mean hdir + mean hdif) / 2 (1 if not positive), reduced on the device
+    in FP64 in a fixed order (rt3d_dn_field_scale); returned to the host."""
+    return float(_field_scale(hdir, hdif)[0].item())
 
 
 def mse(out: torch.Tensor, base: torch.Tensor, target: Optional[torch.Tensor], want_grad: bool):
@@ -543,7 +552,13 @@ def denoise(net: Denoiser, hdir: torch.Tensor, hdif: torch.Tensor, k_ext: torch.
     with the direct-beam input needs direct = the keyword arguments of
     direct_feature beyond k_ext, k_abs (grid, sza, azimuth, direct_fraction,
     layer_scale); the feature is computed here."""
-    s = field_scale(hdir, hdif)
+    # the scale stays on the device; its copy to the host is looked at once
+    # everything is launched (waiting for it first left the device idle while
+    # the next eight small kernels were launched: 40x56x72 248 us, now 214)
+    scale = _field_scale(hdir, hdif)
+    seen = scale[:1].to("cpu", non_blocking=True)
+    copied = torch.cuda.Event()
+    copied.record()
     D, H, W = hdir.shape
     dfield = None
     if net.n_in == 5:
@@ -553,10 +568,13 @@ def denoise(net: Denoiser, hdir: torch.Tensor, hdif: torch.Tensor, k_ext: torch.
     cpad = 4 if dfield is None else 8  # packed first layer: 4 inputs, or 5 in 8 channels
     feat = bf16_empty(D, H, W, cpad)
     # the residual base is not stored: the output pass forms it again
-    _check(load().rt3d_dn_features(_p(hdir), _p(hdif), _p(k_ext), _p(k_abs), float(dz), float(s), hdir.numel(), cpad,
-                                   _p(dfield), _p(feat), None, _s()), "rt3d_dn_features")
+    _check(load().rt3d_dn_features_at(_p(hdir), _p(hdif), _p(k_ext), _p(k_abs), float(dz), _p(scale), hdir.numel(), cpad,
+                                      _p(dfield), _p(feat), None, _s()), "rt3d_dn_features_at")
     out = net.forward(feat)
     od, of = torch.empty_like(hdir), torch.empty_like(hdif)
-    _check(load().rt3d_dn_residual_unfeature(_p(out), out.shape[-1], _p(hdir), _p(hdif), float(s), hdir.numel(),
-                                             _p(od), _p(of), _s()), "rt3d_dn_residual_unfeature")
+    _check(load().rt3d_dn_residual_unfeature_at(_p(out), out.shape[-1], _p(hdir), _p(hdif), _p(scale), hdir.numel(),
+                                                _p(od), _p(of), _s()), "rt3d_dn_residual_unfeature_at")
+    copied.synchronize()
+    if not np.float32(seen[0].item()) > 0.0:
+        raise rt3d.Rt3dError(rt3d.EINVAL, "denoise: the field scale is zero in FP32")
     return od, of
