@@ -1175,11 +1175,14 @@ __global__ void __launch_bounds__(512)
             x0 = (int)(tile % tiles_x) * kTX;
             y0 = (int)(tile / tiles_x) * TY;
             __syncthreads();
-            for (int k = -1; k <= 1; ++k) {
-                load_x(x0, y0, z + k);
-                put_edge(z + k, get_edge(x0, y0, z + k));
-            }
+            uint4 first[3];  // (all of them in flight at once)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) first[k] = get_edge(x0, y0, z + k - 1);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) load_x(x0, y0, z + k - 1);
             load_dz(x0, y0, z);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) put_edge(z + k - 1, first[k]);
         } else if (ahead) {
             put_edge(z + 1, edge);  // (no wave has read that place since the last barrier)
         }
@@ -1930,9 +1933,28 @@ rt3d_status conv3_launch(const ConvArgs& a, hipStream_t st) {
 //   128 -> 256 on 16^3       (4, 2)  64 60,                (2, 2) 128 32, (1, 2) 256 22, (1, 1) 512 25
 //   192 -> 64 on 20x28x36    (4, 2)  80 70,                (2, 2) 140 41, (1, 2) 280 42, (1, 1) 560 47
 //   192 -> 64 on 64^3        (4, 2) 512 158,               (2, 2) 1024 167, (1, 2) 2048 199
+// Tiles of 3 rows instead of 4 (64 channels) where they leave less of the last
+// round of 512 workgroups idle or of the last tile row outside the grid: time in
+// rows a wave, 0.6 of a round for up to one workgroup a CU, which has the CU to
+// itself, and 2 % for the larger halo.  Workgroups and whole calls, 4 / 3 rows:
+//   192 -> 64 on 44x90x118  1056 / 1320  339 / 318 us
+//    64 -> 64 on 96^3       1728 / 2304  202 / 176
+//   192 -> 64 on 64^3        512 /  704  154 / 178
+//   160 -> 64 on 52x104x88  1014 / 1404  259 / 273
+//    32 -> 64 on 128^3      4096 / 5632  230 / 249
+double rounds_of(long groups) {
+    const long rest = groups % 512;
+    return (double)(groups / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.6 : 1.0);
+}
+
 template <int NCT>
 rt3d_status conv3_run(const ConvArgs& a, hipStream_t st) {
-    if (conv3_groups<NCT, 4, 2>(a) >= 512) return conv3_launch<NCT, 4, 2>(a, st);
+    if (conv3_groups<NCT, 4, 2>(a) >= 512) {
+        if constexpr (NCT == 2)
+            if (3 * 1.02 * rounds_of(conv3_groups<2, 3, 2>(a)) < 4 * rounds_of(conv3_groups<2, 4, 2>(a)))
+                return conv3_launch<2, 3, 2>(a, st);
+        return conv3_launch<NCT, 4, 2>(a, st);
+    }
     if (conv3_groups<NCT, 2, 2>(a) > 128) return conv3_launch<NCT, 2, 2>(a, st);
     if (conv3_groups<NCT, 1, 2>(a) > 128) return conv3_launch<NCT, 1, 2>(a, st);
     return conv3_launch<NCT, 1, 1>(a, st);
