@@ -294,6 +294,23 @@ void rt3d_default_options(rt3d_options* opt);
  * 2^24 cells: the tallies are the same, and fewer of their updates are atomics. */
 size_t rt3d_workspace_size(const rt3d_grid* grid, const rt3d_options* opt);
 
+/* The deposit buffer of a rt3d_trace call with this workspace whose tracing
+ * launch has `lanes` lanes (a multiple of 64), evaluated on the HOST (no device
+ * work), for tests and inspection.  Writes plan[RT3D_DEPOSIT_N] (host), all 0
+ * where the call adds every deposit by an atomic; offsets are in bytes from the
+ * start of the workspace. */
+enum {
+    RT3D_DEPOSIT_TILES = 0,    /* tiles of 16384 deposits */
+    RT3D_DEPOSIT_BINS = 1,     /* bins of 8192 cells */
+    RT3D_DEPOSIT_ROUNDS = 2,   /* rounds launched */
+    RT3D_DEPOSIT_END = 3,      /* end of the deposits */
+    RT3D_DEPOSIT_READ_END = 4, /* end of what is read of them, all tiles in use */
+    RT3D_DEPOSIT_USED = 5,     /* end of what the call uses */
+    RT3D_DEPOSIT_N = 6
+};
+rt3d_status rt3d_deposit_plan(const rt3d_grid* grid, const rt3d_options* opt, uint64_t photons,
+                              size_t workspace_bytes, uint32_t lanes, uint64_t* plan);
+
 /* Acceleration grid (sec. 2.3, acceleration grid paragraph): majorant[b] =
  * max of k_ext over the fine cells of brick b, exactly (FP32 max).
  * majorant: device FP32 [nz/bz][ny/by][nx/bx].  k_ext must be >= 0. */

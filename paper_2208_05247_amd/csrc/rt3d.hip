@@ -365,6 +365,14 @@ struct Deposits {
     uint2* item;            // [ntiles][kTileChunks][kChunk] (cell | diffuse << 31, amount)
     uint32_t ntiles, nbins, nwaves, nlanes;
 
+    // Where the addition reads the run [first, last) of the lane'th tile of a
+    // group, counted from the group's first tile.  Its loads are not
+    // predicated, so a run without deposits (the tile may then lie past the
+    // last one, and `first` at the end of the tile) reads the group's first.
+    __device__ __host__ static uint32_t run_at(uint32_t lane, uint32_t first, uint32_t last) {
+        return last != first ? lane * kTileDeposits + first : 0u;
+    }
+
     // column q's counter in round r (its set is cleared during round r - 1)
     __device__ uint32_t* used_in(int r, uint32_t q) const { return used + 32 * (kTileChunks * (r & 1) + q); }
 };
@@ -1188,7 +1196,7 @@ __global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int
         const uint32_t first = first_next, last = last_next;
         place(t0 + 16 * 64 + lane, first_next, last_next);
         // the run of tile t0 + l: where it starts (counted from tile t0) and its length
-        const uint32_t at = lane * kTileDeposits + first, len = last - first;
+        const uint32_t at = Deposits::run_at(lane, first, last), len = last - first;
         const uint2* item = D.item + (size_t)t0 * kTileDeposits;
         auto sum = [&](const uint2& v) {
             atomicAdd(&s_sum[(v.x & (kBinCells - 1)) | ((v.x >> 31) << kBinShift)], (unsigned long long)v.y);
@@ -1799,6 +1807,32 @@ bool deposit_buffer(const Shape& s, unsigned long long photons, char* at, size_t
     return true;
 }
 
+// Rounds launched: 64 deposits a photon are more than the fields in use give
+// (26 to 31).
+int deposit_rounds(const Deposits& D, unsigned long long photons) {
+    const unsigned long long room = (unsigned long long)D.ntiles * kTileDeposits;
+    return (int)std::min<unsigned long long>(kMaxRounds, 1 + photons / (room / 64 + 1));
+}
+
+// One past the last deposit that the addition reads when `ntiles` tiles are in
+// use: its groups of 64 tiles, with runs at every edge of a tile.
+unsigned long long deposit_reach(uint32_t ntiles) {
+    unsigned long long end = 0;
+    for (uint32_t t = 0; t < (ntiles + 63) / 64 * 64; ++t) {
+        const unsigned long long group = (unsigned long long)(t & ~63u) * kTileDeposits;
+        auto run = [&](uint32_t first, uint32_t last) {
+            const uint32_t len = last - first;
+            end = std::max(end, group + Deposits::run_at(t & 63u, first, last) + (len ? len : 1u));
+        };
+        run(0, 0);
+        if (t >= ntiles) continue;
+        run(0, kTileDeposits);
+        run(kTileDeposits - 1, kTileDeposits);
+        run(kTileDeposits, kTileDeposits);
+    }
+    return end;
+}
+
 struct Launch {
     rt3d_options o;
     Shape s;
@@ -2061,9 +2095,7 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     if (!factored && !(L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) &&
         deposit_buffer(L.s, L.total, L.spare, L.spare_bytes, blocks * (unsigned)threads, &D)) {
         kernel = use_lds ? trace_kernel<true, false, kBinned> : trace_kernel<false, false, kBinned>;
-        // 64 deposits a photon are more than the fields in use give (26 to 31)
-        const unsigned long long room = (unsigned long long)D.ntiles * kTileDeposits;
-        const int rounds = (int)std::min<unsigned long long>(kMaxRounds, 1 + L.total / (room / 64 + 1));
+        const int rounds = deposit_rounds(D, L.total);
         hipLaunchKernelGGL(fill_u32_kernel, dim3(4), dim3(256), 0, st, D.used, (size_t)2 * kTileChunks * 32, 0u);
         HIP_TRY(hipGetLastError());
         for (int r = 0; r < rounds; ++r) {
@@ -2173,6 +2205,30 @@ size_t rt3d_workspace_size_batched(const rt3d_grid* grid, int32_t n_gpoints, con
     Shape s;
     if (!shape_of(grid, &o, &s)) return 0;
     return layout_of(s, n_gpoints, true).total;
+}
+
+rt3d_status rt3d_deposit_plan(const rt3d_grid* grid, const rt3d_options* opt, uint64_t photons,
+                              size_t workspace_bytes, uint32_t lanes, uint64_t* plan) {
+    rt3d_options o;
+    if (!grid_ok(grid) || !plan || lanes == 0 || lanes % 64) return RT3D_EINVAL;
+    resolve_options(grid, opt, &o);
+    Shape s;
+    if (!shape_of(grid, &o, &s)) return RT3D_EINVAL;
+    const size_t need = layout_of(s, 1, false).total;
+    if (workspace_bytes < need) return RT3D_EINVAL;
+    for (int i = 0; i < RT3D_DEPOSIT_N; ++i) plan[i] = 0;
+    char* const base = (char*)(uintptr_t)256;
+    Deposits D;
+    if ((o.flags & RT3D_FLAG_WAVE_AGGREGATE) ||
+        !deposit_buffer(s, photons, base + need, workspace_bytes - need, lanes, &D))
+        return RT3D_OK;
+    plan[RT3D_DEPOSIT_TILES] = D.ntiles;
+    plan[RT3D_DEPOSIT_BINS] = D.nbins;
+    plan[RT3D_DEPOSIT_ROUNDS] = (uint64_t)deposit_rounds(D, photons);
+    plan[RT3D_DEPOSIT_END] = (uint64_t)((char*)(D.item + (size_t)D.ntiles * kTileDeposits) - base);
+    plan[RT3D_DEPOSIT_READ_END] = (uint64_t)((char*)(D.item + deposit_reach(D.ntiles)) - base);
+    plan[RT3D_DEPOSIT_USED] = (uint64_t)((char*)(D.start + (size_t)D.ntiles * (D.nbins + 1)) - base);
+    return RT3D_OK;
 }
 
 rt3d_status rt3d_majorant_build(const rt3d_grid* grid, const float* k_ext, int32_t bx, int32_t by, int32_t bz,

@@ -33,7 +33,7 @@ EXPORTS = ("rt3d_abi_version", "rt3d_status_string", "rt3d_last_device_error",
            "rt3d_default_options", "rt3d_workspace_size", "rt3d_majorant_build",
            "rt3d_trace", "rt3d_last_trace_ms", "rt3d_finalize", "rt3d_philox4x32_10",
            "rt3d_workspace_size_batched", "rt3d_trace_batched", "rt3d_sobol_entry", "rt3d_two_stream",
-           "rt3d_phase_sample", "rt3d_turn", "rt3d_trace_noalloc", "rt3d_schedule_slots")
+           "rt3d_phase_sample", "rt3d_turn", "rt3d_trace_noalloc", "rt3d_schedule_slots", "rt3d_deposit_plan")
 MAX_GPOINTS = 256
 
 
@@ -93,6 +93,7 @@ def load(path: str = LIB_PATH):
     lib.rt3d_default_options.argtypes = [ctypes.POINTER(Options)]
     lib.rt3d_workspace_size.argtypes = [ctypes.POINTER(Grid), ctypes.POINTER(Options)]
     lib.rt3d_workspace_size.restype = Z
+    lib.rt3d_deposit_plan.argtypes = [ctypes.POINTER(Grid), ctypes.POINTER(Options), ctypes.c_uint64, Z, ctypes.c_uint32, P]
     lib.rt3d_majorant_build.argtypes = [ctypes.POINTER(Grid), P, ctypes.c_int32, ctypes.c_int32,
                                         ctypes.c_int32, P, P]
     lib.rt3d_trace.argtypes = [ctypes.POINTER(Grid), ctypes.POINTER(OpticalProps), P, ctypes.c_double,
@@ -119,7 +120,7 @@ def load(path: str = LIB_PATH):
                                         ctypes.c_uint64, ctypes.c_uint64, P, P, P]
     for name in ("rt3d_majorant_build", "rt3d_trace", "rt3d_trace_noalloc", "rt3d_last_trace_ms", "rt3d_finalize",
                  "rt3d_philox4x32_10", "rt3d_trace_batched", "rt3d_sobol_entry", "rt3d_two_stream",
-                 "rt3d_phase_sample", "rt3d_turn", "rt3d_trace_noalloc", "rt3d_schedule_slots"):
+                 "rt3d_phase_sample", "rt3d_turn", "rt3d_trace_noalloc", "rt3d_schedule_slots", "rt3d_deposit_plan"):
         getattr(lib, name).restype = ctypes.c_int
     if lib.rt3d_abi_version() != 3:
         raise RuntimeError("librt3d.so ABI version mismatch")
@@ -234,6 +235,15 @@ def workspace_size(grid, opt: Options) -> int:
     if grid.nx * grid.ny * grid.nz <= DEPOSIT_BUFFER_CELLS:
         size.spare = max(8 * size, 128 << 20)
     return size
+
+
+def deposit_plan(grid, opt: Options, photons: int, workspace_bytes: int, lanes: int) -> dict:
+    """Host evaluation of the deposit buffer of a trace with this workspace and
+    `lanes` lanes in its tracing launch (rt3d_deposit_plan); no device work."""
+    plan = np.empty(6, np.uint64)
+    _check(load().rt3d_deposit_plan(ctypes.byref(grid_struct(grid)), ctypes.byref(opt), int(photons),
+                                    int(workspace_bytes), int(lanes), plan.ctypes.data), "rt3d_deposit_plan")
+    return dict(zip(("tiles", "bins", "rounds", "end", "read_end", "used"), (int(v) for v in plan)))
 
 
 def alloc_tallies(grid, device="cuda") -> dict:

@@ -1,0 +1,58 @@
+"""The deposit buffer's layout, evaluated on the host (rt3d_deposit_plan): all
+that the addition reads lies in the deposits and all that a call uses lies in
+its workspace, for tile counts around multiples of the 64 tiles that the
+addition takes at a time, for few and many lanes and bins."""
+import pytest
+
+from paper_2208_05247_amd import rt3d as r
+from paper_2208_05247_amd.synthetic import Grid
+
+TILE = 16384 * 8  # bytes of deposits
+
+
+def spare_for(grid, opt, photons, lanes, tiles, start=32 << 20):
+    """Smallest workspace surplus (to 256 bytes) that holds `tiles` tiles."""
+    n = int(r.workspace_size(grid, opt))
+    lo, hi = start, (tiles + 8) * (TILE + 8192) + lanes * 128 + (1 << 20)
+    assert r.deposit_plan(grid, opt, photons, n + hi, lanes)["tiles"] >= tiles
+    while hi - lo > 256:
+        mid = (lo + hi) // 2
+        if r.deposit_plan(grid, opt, photons, n + mid, lanes)["tiles"] >= tiles:
+            hi = mid
+        else:
+            lo = mid
+    return hi
+
+
+@pytest.mark.parametrize("shape,brick", [((128, 64, 128), (8, 8, 8)), ((104, 100, 104), (8, 4, 8)),
+                                         ((110, 100, 100), (5, 5, 5)), ((256, 256, 256), (8, 8, 8))])
+@pytest.mark.parametrize("lanes", [64, 768, 7 * 768, 32 * 768, 512 * 768])
+def test_reads_stay_inside_the_deposits(shape, brick, lanes):
+    grid = Grid(*shape, 50.0, 40.0, 30.0)
+    opt = r.options(brick=brick)
+    n = int(r.workspace_size(grid, opt))
+    seen = set()
+    for tiles in (4096, 4097, 4127, 4159, 4160, 4161):
+        size = n + spare_for(grid, opt, 1 << 22, lanes, tiles)
+        plan = r.deposit_plan(grid, opt, 1 << 22, size, lanes)
+        assert plan["tiles"] == tiles and plan["bins"] == -(-grid.nx * grid.ny * grid.nz // 8192)
+        assert plan["end"] == n + tiles * TILE
+        assert plan["read_end"] <= plan["end"], (tiles, plan["read_end"] - plan["end"])
+        assert plan["end"] < plan["used"] <= size
+        seen.add(plan["tiles"] % 64)
+    assert 1 in seen and 0 in seen
+
+
+def test_calls_without_a_buffer():
+    grid = Grid(128, 64, 128, 50.0, 40.0, 30.0)
+    opt = r.options()
+    n = int(r.workspace_size(grid, opt))
+    none = dict(tiles=0, bins=0, rounds=0, end=0, read_end=0, used=0)
+    assert r.deposit_plan(grid, opt, 1 << 22, n, 768) == none
+    assert r.deposit_plan(grid, opt, (1 << 22) - 1, n + (1 << 30), 768) == none
+    assert r.deposit_plan(grid, r.options(flags=r.FLAG_WAVE_AGGREGATE), 1 << 22, n + (1 << 30), 768) == none
+    few = Grid(128, 64, 127, 50.0, 40.0, 30.0)  # 127 bins
+    assert r.deposit_plan(few, r.options(brick=(8, 8, 1)), 1 << 22, 2 << 30, 768) == none
+    for bad in ((n - 1, 768), (n, 0), (n, 100)):
+        with pytest.raises(r.Rt3dError):
+            r.deposit_plan(grid, opt, 1 << 22, *bad)

@@ -1,0 +1,63 @@
+"""Traces through the deposit buffer on grids that it is used for (128 bins and
+more), with few workgroups and tile counts one past a multiple of the 64 tiles
+that the addition takes at a time: tallies bit for bit those of the plain
+workspace.  All sums are of integers, so equality is exact.  Each case checks
+that the buffer was taken: the surplus of its workspace has been written."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2208_05247_amd import rt3d as r  # noqa: E402
+from paper_2208_05247_amd import synthetic as syn  # noqa: E402
+from test_deposit_plan_cpu import spare_for  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+KEYS = r.TALLY3 + r.TALLY2 + ("ledger", "stats")
+LANES = 768  # of a workgroup
+
+
+def fields(shape, seed=6, k_max=0.01):
+    grid = syn.Grid(*shape, 50.0, 40.0, 30.0)
+    return r.DeviceFields.from_host(syn.random_fields(grid, seed=seed, k_max=k_max, albedo_range=(0.1, 0.4)))
+
+
+def plain(df, brick):
+    """The needed workspace and nothing more."""
+    return r.alloc_workspace(int(r.workspace_size(df.grid, r.options(brick=brick))))
+
+
+def buffered(df, brick, spare):
+    """The needed workspace and `spare` bytes, which hold a pattern."""
+    n = int(r.workspace_size(df.grid, r.options(brick=brick)))
+    ws = r.alloc_workspace(n + spare)
+    ws[n:] = 0x5a
+    return ws
+
+
+def used(df, brick, ws):
+    n = int(r.workspace_size(df.grid, r.options(brick=brick)))
+    return bool((ws[n:n + 16384 * 8] != 0x5a).any())
+
+
+def same(a, b):
+    torch.cuda.synchronize()
+    for k in KEYS:
+        assert torch.equal(a[k], b[k]), k
+    led = [int(v) for v in r.as_uint64(a["ledger"])]
+    assert led[0] + led[5] == sum(led[1:5]) + led[6] + led[7]
+
+
+@pytest.mark.parametrize("shape,brick", [((128, 64, 128), (8, 8, 8)), ((104, 100, 104), (8, 4, 8))])
+@pytest.mark.parametrize("groups,tiles", [(7, 321), (32, 513)])
+def test_few_workgroups(shape, brick, groups, tiles):
+    df = fields(shape)
+    photons = (1 << 22) + 5
+    spare = spare_for(df.grid, r.options(brick=brick), photons, groups * LANES, tiles)
+    print("deposit case", shape, brick, groups, tiles, spare, flush=True)
+    kw = dict(brick=brick, diffuse_fraction=0.1, grid_blocks=groups)
+    ws = buffered(df, brick, spare)
+    got = r.trace(df, 35.0, 20.0, photons, 7, workspace=ws, **kw)
+    ref = r.trace(df, 35.0, 20.0, photons, 7, workspace=plain(df, brick), **kw)
+    same(got, ref)
+    assert used(df, brick, ws)
