@@ -131,7 +131,8 @@ rt3d_status rt3d_dn_flip_weights(const uint16_t* w, uint16_t* wt, int32_t cout, 
 /* dw[co][t][ci] += sum_v dz[v][co] x[v + offset(t)][ci] (FP32, accumulated
  * with atomics: clear dw first); db[co] += sum_v dz[v][co] if db != NULL.
  * x = concat(x1, x2) is the forward input (c->up1 must be 0), dz the
- * gradient at the convolution output (after the activation's derivative). */
+ * gradient at the convolution output (after the activation's derivative).
+ * Fast for ksize 3 where x1, x2 and dz are 16-byte aligned. */
 rt3d_status rt3d_dn_conv3d_wgrad(const rt3d_dn_conv* c, const uint16_t* x1, const uint16_t* x2, const uint16_t* dz,
                                  float* dw, float* db, void* stream);
 

@@ -1266,18 +1266,24 @@ __global__ void __launch_bounds__(512)
     }
 }
 
-// The 1x1x1 weight gradient (the head): one wave per 32 x 32 channels and
-// chunk of rows; the same chunk's bias gradient from the first input tile.
-__global__ void __launch_bounds__(256) conv1_wgrad_kernel(const WgradArgs a) {
+// The weight gradient by 2-byte loads: one wave per 32 x 32 channels, tap and
+// chunk of rows; the same chunk's bias gradient from the first input tile and
+// tap.  For the 1x1x1 head, and for the 3x3x3 gradient of tensors that are not
+// 16-byte aligned, which the kernel above cannot load.
+template <int KS>
+__global__ void __launch_bounds__(256) conv_wgrad_kernel(const WgradArgs a) {
+    constexpr int taps = KS * KS * KS;
     const int lane = threadIdx.x & 63;
     const long wave = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int cin = a.c1 + a.c2;
     const int ntco = a.cout / 32, ntci = (cin + 31) / 32;
     const long nrows = (long)a.D * a.H;
-    if (wave >= (long)ntco * ntci * a.chunks) return;
+    if (wave >= (long)ntco * ntci * taps * a.chunks) return;
     const int cot = (int)(wave % ntco);
     const int cit = (int)((wave / ntco) % ntci);
-    const long chunk = wave / ((long)ntco * ntci);
+    const int t = (int)((wave / ((long)ntco * ntci)) % taps);
+    const long chunk = wave / ((long)ntco * ntci * taps);
+    const int dz = t / (KS * KS) - KS / 2, dy = (t / KS) % KS - KS / 2, dx = t % KS - KS / 2;
     const int m = lane & 31, half = lane >> 5;
     const int co = cot * 32 + m;
     const int ci = cit * 32 + m;
@@ -1291,15 +1297,17 @@ __global__ void __launch_bounds__(256) conv1_wgrad_kernel(const WgradArgs a) {
     for (int k = 0; k < 8; ++k) ones[k] = (__bf16)1.0f;
     const long r0 = nrows * chunk / a.chunks, r1 = nrows * (chunk + 1) / a.chunks;
     for (long row = r0; row < r1; ++row) {
-        const long vrow = row * a.W;
+        const int z = (int)(row / a.H) + dz, y = (int)(row % a.H) + dy;
+        const bool row_ok = KS == 1 || (z >= 0 && z < a.D && y >= 0 && y < a.H);
+        const long vrow = row * a.W, srow = KS == 1 ? vrow : ((long)z * a.H + y) * a.W;
         for (int x0 = 0; x0 < a.W; x0 += 16) {
             bf16x8 av, bv;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const int x = x0 + 8 * half + i;
-                const bool xin = x < a.W;
+                const int x = x0 + 8 * half + i, sx = x + dx;
+                const bool xin = x < a.W, sin = row_ok && xin && ci_ok && sx >= 0 && sx < a.W;
                 const uint16_t g = xin ? a.dz[(vrow + x) * a.cout + co] : (uint16_t)0;
-                const uint16_t v = xin && ci_ok ? xs[(vrow + x) * xc + xci] : (uint16_t)0;
+                const uint16_t v = sin ? xs[(srow + sx) * xc + xci] : (uint16_t)0;
                 av[i] = __builtin_bit_cast(__bf16, g);
                 bv[i] = __builtin_bit_cast(__bf16, v);
             }
@@ -1309,13 +1317,13 @@ __global__ void __launch_bounds__(256) conv1_wgrad_kernel(const WgradArgs a) {
     }
     for (int r = 0; r < 16; ++r) {
         const int mm = cot * 32 + 8 * (r >> 2) + 4 * half + (r & 3);  // output channel (row)
-        if (a.db && cit == 0 && m == 0) {
+        if (a.db && cit == 0 && t == 0 && m == 0) {
             if (a.partial) a.partial_b[chunk * a.cout + mm] = accb[r];
             else atomicAdd(&a.db[mm], accb[r]);
         }
         if (!ci_ok) continue;
-        if (a.partial) a.partial[(chunk * a.cout + mm) * cin + ci] = acc[r];
-        else atomicAdd(&a.dw[(long)mm * cin + ci], acc[r]);
+        if (a.partial) a.partial[((chunk * a.cout + mm) * taps + t) * cin + ci] = acc[r];
+        else atomicAdd(&a.dw[((long)mm * taps + t) * cin + ci], acc[r]);
     }
 }
 
@@ -2169,13 +2177,20 @@ rt3d_status wgrad3_launch(const WgradPlan& plan, const WgradArgs& a, hipStream_t
     return RT3D_OK;
 }
 
+template <typename... P>
+bool aligned16(const P*... p) {
+    return ((reinterpret_cast<uintptr_t>(p) | ...) & 15) == 0;
+}
+
 rt3d_status wgrad_run(const rt3d_dn_conv* c, const WgradPlan& plan, const uint16_t* x1, const uint16_t* x2,
                       const uint16_t* dz, float* dw, float* db, float* part_w, float* part_b, hipStream_t st) {
     WgradArgs a = plan.a;
     a.dz = dz; a.x1 = x1; a.x2 = x2; a.dw = dw; a.db = db; a.partial = part_w; a.partial_b = part_b;
     rt3d_status r = RT3D_OK;
-    if (c->ksize == 1) {
-        hipLaunchKernelGGL(conv1_wgrad_kernel, dim3((unsigned)((plan.tasks * a.chunks + 3) / 4)), dim3(256), 0, st, a);
+    if (c->ksize == 1 || !aligned16(x1, dz) || (c->c2 && !aligned16(x2))) {
+        const long waves = (long)(c->cout / 32) * ((c->c1 + c->c2 + 31) / 32) * plan.taps * a.chunks;
+        hipLaunchKernelGGL((c->ksize == 1 ? conv_wgrad_kernel<1> : conv_wgrad_kernel<3>), dim3((unsigned)((waves + 3) / 4)),
+                           dim3(256), 0, st, a);
         DN_TRY(hipGetLastError());
     } else if (plan.nco == 2) {
         r = wgrad3_launch<2, 1, 4>(plan, a, st);
@@ -2197,12 +2212,6 @@ rt3d_status wgrad_run(const rt3d_dn_conv* c, const WgradPlan& plan, const uint16
         DN_TRY(hipGetLastError());
     }
     return RT3D_OK;
-}
-
-
-template <typename... P>
-bool aligned16(const P*... p) {
-    return ((reinterpret_cast<uintptr_t>(p) | ...) & 15) == 0;
 }
 
 }  // namespace

@@ -1,0 +1,44 @@
+"""The 3x3x3 weight gradient of inputs that its 16-byte loads do not take:
+tensors 2 and 8 bytes into their storage, one at a time and together.  Against
+FP64 sums of the same BF16 values, within the 1e-5 of the aligned call (FP32
+accumulation of n products: n^0.5 2^-24 relative, 3e-6 at the 2e3 terms here)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from test_gpu_wgrad import reference  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def at_offset(t, elements):
+    """The same values, `elements` elements into a 16-byte aligned storage."""
+    s = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")
+    v = s[elements:elements + t.numel()].view(t.shape)
+    v.copy_(t)
+    assert v.data_ptr() % 16 == 2 * elements
+    return v
+
+
+@pytest.mark.parametrize("c1,c2,cout,k", [(32, 0, 64, 3), (16, 32, 32, 3), (64, 32, 32, 3), (32, 0, 32, 1)])
+@pytest.mark.parametrize("o1,o2,oz", [(1, 0, 0), (0, 4, 0), (0, 0, 1), (4, 1, 4)])
+def test_any_alignment(c1, c2, cout, k, o1, o2, oz):
+    from paper_2208_05247_amd import denoise as dn
+    D, H, W = 5, 7, 35
+    g = torch.Generator().manual_seed(c1 + 10 * o1 + oz)
+    x = torch.randn(D, H, W, c1 + c2, generator=g).to(torch.bfloat16)
+    dz = torch.randn(D, H, W, cout, generator=g).to(torch.bfloat16)
+    rw, rb = reference(x.double(), dz.double())
+    if k == 1:
+        rw = rw[:, 13:14]
+    x1, dzg = at_offset(x[..., :c1].contiguous(), o1), at_offset(dz, oz)
+    x2 = at_offset(x[..., c1:].contiguous(), o2) if c2 else None
+    rel = lambda a, b: float((a.double().cpu() - b).norm() / b.norm())
+    for ws in (None, torch.empty(dn.wgrad_workspace_size(x1, x2, cout, k), dtype=torch.uint8, device="cuda")):
+        print("alignment case", c1, c2, cout, k, o1, o2, oz, ws is not None, flush=True)
+        dw, db = torch.zeros(cout, k ** 3, c1 + c2, device="cuda"), torch.zeros(cout, device="cuda")
+        dn.conv_wgrad(x1, x2, dzg, cout, k, dw, db, workspace=ws)
+        assert rel(dw, rw) < 1e-5 and rel(db, rb) < 1e-5
+        only = torch.zeros_like(dw)
+        dn.conv_wgrad(x1, x2, dzg, cout, k, only, None, workspace=ws)
+        assert rel(only, rw) < 1e-5
