@@ -42,3 +42,29 @@ def test_any_alignment(c1, c2, cout, k, o1, o2, oz):
         only = torch.zeros_like(dw)
         dn.conv_wgrad(x1, x2, dzg, cout, k, only, None, workspace=ws)
         assert rel(only, rw) < 1e-5
+
+
+@pytest.mark.parametrize("D,H,W", [(2, 3, 33), (3, 5, 7), (1, 6, 40), (2, 7, 56), (2, 1, 47), (2, 4, 32), (1, 3, 64)])
+@pytest.mark.parametrize("c1,c2,cout", [(16, 0, 32), (32, 0, 64), (48, 16, 32), (64, 32, 32)])
+@pytest.mark.parametrize("what", ["input", "gradient"])
+def test_infinities_at_the_domain_edge(D, H, W, c1, c2, cout, what):
+    """An infinity or NaN in the last column, row or plane reaches the taps that
+    meet it inside the domain and no other."""
+    from paper_2208_05247_amd import denoise as dn
+    g = torch.Generator().manual_seed(W * 10 + c1)
+    x = torch.randn(D, H, W, c1 + c2, generator=g).to(torch.bfloat16)
+    dz = torch.randn(D, H, W, cout, generator=g).to(torch.bfloat16)
+    t = x if what == "input" else dz
+    t[0, 0, W - 1, 3] = float("inf")
+    t[D - 1, H - 1, 0, 9] = float("-inf")
+    t[D - 1, H - 1, W - 1, 12] = float("nan")
+    rw, rb = reference(x.double(), dz.double())
+    x1 = x[..., :c1].contiguous().cuda()
+    x2 = x[..., c1:].contiguous().cuda() if c2 else None
+    ws = torch.empty(dn.wgrad_workspace_size(x1, x2, cout, 3), dtype=torch.uint8, device="cuda")
+    dw, db = torch.zeros(cout, 27, c1 + c2, device="cuda"), torch.zeros(cout, device="cuda")
+    dn.conv_wgrad(x1, x2, dz.cuda(), cout, 3, dw, db, workspace=ws)
+    for got, want in ((dw.double().cpu(), rw), (db.double().cpu(), rb)):
+        ok = torch.isfinite(want)
+        assert torch.equal(torch.isfinite(got), ok)
+        assert float((got[ok] - want[ok]).norm()) <= 1e-5 * float(want[ok].norm())
