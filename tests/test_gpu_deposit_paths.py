@@ -61,3 +61,31 @@ def test_few_workgroups(shape, brick, groups, tiles):
     ref = r.trace(df, 35.0, 20.0, photons, 7, workspace=plain(df, brick), **kw)
     same(got, ref)
     assert used(df, brick, ws)
+
+
+def zeroed(df):
+    t = r.alloc_tallies(df.grid)
+    for v in t.values():
+        v.zero_()
+    return t
+
+
+def test_calls_that_overlap_add_to_the_same_tallies():
+    """Two calls over disjoint photons that accumulate on two streams, each with
+    a buffer of its own: no deposit of either is lost."""
+    df, brick, n = fields((128, 64, 128)), (8, 8, 8), 1 << 23
+    kw = dict(brick=brick, diffuse_fraction=0.1, accumulate=True)
+    ref = r.trace(df, 35.0, 20.0, 2 * n, 7, workspace=plain(df, brick), out=zeroed(df), **kw)
+    spaces = [buffered(df, brick, 128 << 20) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    out = zeroed(df)
+    torch.cuda.synchronize()
+    for k in range(2):
+        print("overlap case", k, flush=True)
+        r.trace(df, 35.0, 20.0, n, 7, photon_offset=k * n, workspace=spaces[k], out=out, stream=streams[k], **kw)
+    torch.cuda.synchronize()
+    for k in r.TALLY3 + r.TALLY2 + ("stats",):
+        assert torch.equal(out[k], ref[k]), k
+    for k in ("incoming", "toa", "sfc", "rr_gain", "rr_loss", "lost"):
+        assert out["ledger"][r.LEDGER.index(k)] == ref["ledger"][r.LEDGER.index(k)], k
+    assert all(used(df, brick, ws) for ws in spaces)
