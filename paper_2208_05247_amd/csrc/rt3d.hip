@@ -1245,11 +1245,15 @@ __global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int
     }
 }
 
+__global__ void clear_atm_kernel(unsigned long long* ledger) {
+    if (threadIdx.x == 0) ledger[L_ATM_DIR] = ledger[L_ATM_DIF] = 0;
+}
+
 // Heating entries of the energy ledger: ledger[ATM_DIR] = sum(abs_dir),
 // ledger[ATM_DIF] = sum(abs_dif), exact uint64 sums (the other entries are
 // counted by the tracing kernel, so the identity still checks that no
-// deposit was lost).  setup_kernel has cleared the two entries; every
-// workgroup adds its partial sums.
+// deposit was lost).  The two entries hold 0 here; every workgroup adds its
+// partial sums.
 __global__ void ledger_atm_kernel(const unsigned long long* __restrict__ abs_dir,
                                   const unsigned long long* __restrict__ abs_dif, size_t n,
                                   unsigned long long* __restrict__ ledger) {
@@ -1999,10 +2003,7 @@ rt3d_status begin(Launch& L, const rt3d_tallies* out, uint32_t* merged, size_t n
         b.words[b.nclear++] = words;
     };
     clear(merged, (nmerged + 1) / 2);
-    if (L.o.flags & RT3D_FLAG_ACCUMULATE) {  // only the entries that ledger_atm_kernel forms anew
-        clear(out->ledger + L_ATM_DIR, 1);
-        clear(out->ledger + L_ATM_DIF, 1);
-    } else {
+    if (!(L.o.flags & RT3D_FLAG_ACCUMULATE)) {
         clear(out->abs_dir, L.s.ncell);
         clear(out->abs_dif, L.s.ncell);
         clear(out->sfc_dir, L.s.ncol);
@@ -2121,6 +2122,12 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     if (L.o.flags & RT3D_FLAG_TIME) {
         HIP_TRY(hipEventRecord(g_t1, st));
         g_timed = true;
+    }
+    // The two entries that ledger_atm_kernel forms anew, at the end: another
+    // call that accumulates into the same tallies may have run meanwhile.
+    if (L.o.flags & RT3D_FLAG_ACCUMULATE) {
+        hipLaunchKernelGGL(clear_atm_kernel, dim3(1), dim3(64), 0, st, L.P.ledger);
+        HIP_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL(ledger_atm_kernel, dim3(grid_for(L.s.ncell, 256, 2048)), dim3(256), 0, st, L.P.abs_dir,
                        L.P.abs_dif, L.s.ncell, L.P.ledger);

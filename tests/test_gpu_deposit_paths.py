@@ -89,3 +89,20 @@ def test_calls_that_overlap_add_to_the_same_tallies():
     for k in ("incoming", "toa", "sfc", "rr_gain", "rr_loss", "lost"):
         assert out["ledger"][r.LEDGER.index(k)] == ref["ledger"][r.LEDGER.index(k)], k
     assert all(used(df, brick, ws) for ws in spaces)
+
+
+def test_ledger_of_a_short_call_within_a_long_one():
+    """The ledger's heating entries are the sums of the tallies once all calls
+    have ended, also where one began and ended while another ran."""
+    df, brick = fields((64, 64, 64)), (8, 8, 8)
+    kw = dict(brick=brick, accumulate=True)
+    out = zeroed(df)
+    r.trace(df, 35.0, 20.0, 1 << 14, 3, workspace=plain(df, brick), out=out, **kw)
+    spaces, streams = [plain(df, brick) for _ in range(2)], [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    r.trace(df, 35.0, 20.0, 1 << 26, 7, workspace=spaces[0], out=out, stream=streams[0], **kw)
+    r.trace(df, 35.0, 20.0, 1 << 12, 8, workspace=spaces[1], out=out, stream=streams[1], **kw)
+    torch.cuda.synchronize()
+    led = [int(v) for v in r.as_uint64(out["ledger"])]
+    assert led[2] == int(out["abs_dir"].sum()) and led[3] == int(out["abs_dif"].sum())
+    assert led[0] + led[5] == sum(led[1:5]) + led[6] + led[7]
