@@ -1171,8 +1171,7 @@ __global__ void __launch_bounds__(1024) deposit_sort_kernel(const Deposits D, in
 // other streams meanwhile, else by this workgroup alone.  Neighbouring bins run on the same XCD, so that the
 // 128-byte lines of the table are shared in its L2.
 __global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int round, uint32_t ncell, bool shared,
-                                                           unsigned long long* __restrict__ abs_dir,
-                                                           unsigned long long* __restrict__ abs_dif) {
+                                                           unsigned long long* abs_dir, unsigned long long* abs_dif) {
     __shared__ unsigned long long s_sum[2 * kBinCells];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t per_xcd = (D.nbins + 7) / 8;
@@ -1240,7 +1239,7 @@ __global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int
             if (v && shared) atomicAdd(&tally[cell], v);
             else if (v) tally[cell] += v;
         };
-        add(abs_dir, s_sum[i]);
+        add(abs_dir, s_sum[i]);  // (may be one array, as with the atomics)
         add(abs_dif, s_sum[kBinCells + i]);
     }
 }

@@ -106,3 +106,17 @@ def test_ledger_of_a_short_call_within_a_long_one():
     led = [int(v) for v in r.as_uint64(out["ledger"])]
     assert led[2] == int(out["abs_dir"].sum()) and led[3] == int(out["abs_dif"].sum())
     assert led[0] + led[5] == sum(led[1:5]) + led[6] + led[7]
+
+
+def test_one_array_for_direct_and_diffuse_heating():
+    """Both heating tallies in one array: their sum."""
+    df, brick, n = fields((128, 64, 128)), (8, 8, 8), 1 << 22
+    kw = dict(brick=brick, diffuse_fraction=0.3)
+    ref = r.trace(df, 35.0, 20.0, n, 7, workspace=plain(df, brick), **kw)
+    out = r.alloc_tallies(df.grid)
+    out["abs_dif"] = out["abs_dir"]
+    for accumulate in (False, True):
+        ws = buffered(df, brick, 128 << 20)
+        r.trace(df, 35.0, 20.0, n, 7, workspace=ws, out=out, accumulate=accumulate, **kw)
+        assert used(df, brick, ws)
+        assert torch.equal(out["abs_dir"], (ref["abs_dir"] + ref["abs_dif"]) * (2 if accumulate else 1))
