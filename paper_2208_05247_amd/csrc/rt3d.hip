@@ -574,9 +574,13 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     const uint32_t lane_ix = blockIdx.x * blockDim.x + threadIdx.x;
     bool drained = false;
     if (kTally == kBinned && P.round) {
-        // nothing left to do for the whole workgroup: end
-        drained = P.dep.waves[2 * P.dep.nwaves + wave] != 0;
-        if (!__syncthreads_or(!drained)) return;
+        // nothing left to do for the whole workgroup: end (each wave looks at
+        // the flags of all: a workgroup reduction takes LDS that the majorants
+        // may fill; none is written before all waves are at the next barrier)
+        const uint32_t mine = threadIdx.x / 64, lane = threadIdx.x % 64;
+        const uint64_t left = __ballot(lane < blockDim.x / 64 && P.dep.waves[2 * P.dep.nwaves + wave - mine + lane] == 0);
+        if (!left) return;
+        drained = !((left >> mine) & 1);
     }
 
     for (int i = threadIdx.x; i < C_N * kCntSlots; i += blockDim.x) s_cnt[i / kCntSlots][i % kCntSlots] = 0;

@@ -120,3 +120,15 @@ def test_one_array_for_direct_and_diffuse_heating():
         r.trace(df, 35.0, 20.0, n, 7, workspace=ws, out=out, accumulate=accumulate, **kw)
         assert used(df, brick, ws)
         assert torch.equal(out["abs_dir"], (ref["abs_dir"] + ref["abs_dif"]) * (2 if accumulate else 1))
+
+
+def test_majorants_that_fill_the_lds():
+    """39900 majorants in LDS on request, beside the tracing kernel's own: no
+    room for another 256 bytes."""
+    df, brick, n = fields((76, 84, 200)), (4, 4, 2), 1 << 22
+    kw = dict(brick=brick, diffuse_fraction=0.1, lds_majorant=1)
+    ref = r.trace(df, 35.0, 20.0, n, 7, workspace=plain(df, brick), **kw)
+    ws = buffered(df, brick, 256 << 20)
+    got = r.trace(df, 35.0, 20.0, n, 7, workspace=ws, **kw)
+    same(got, ref)
+    assert used(df, brick, ws)
