@@ -229,6 +229,12 @@ inline FastDiv33 fast_div33(unsigned long long d) { return FastDiv33{d, 1.0 / (d
 
 __device__ __host__ __forceinline__ unsigned long long quotient(unsigned long long n, const FastDiv33& f,
                                                                 unsigned long long* rem) {
+#ifndef __HIP_DEVICE_COMPILE__
+    if (n >> 33) {  // (a launch has fewer photons; rt3d_schedule_slots takes any number)
+        *rem = n % f.d;
+        return n / f.d;
+    }
+#endif
     unsigned long long q = (unsigned long long)((double)n * f.inv);
     long long r = (long long)(n - q * f.d);
     if (r < 0) {
