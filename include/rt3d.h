@@ -486,8 +486,9 @@ rt3d_status rt3d_turn(const float* dir_in, const float* mu, const float* t, floa
  *   tod_diffuse_fraction [n_cols] FP32 or NULL: its diffuse share (0 where
  *                    the flux is 0), the input of rt3d_batched_medium.
  * mu0 = cos(solar zenith angle) in (0, 1] (host); 0 <= tod_level <= nlay.
- * RT3D_EINVAL on bad arguments (nothing launched).  A workgroup per column
- * (beyond 1024 layers a lane); asynchronous on `stream`. */
+ * RT3D_EINVAL on bad arguments (nothing launched).  A workgroup per column, or
+ * a lane where there are many columns or layers (over 1024); asynchronous on
+ * `stream`. */
 rt3d_status rt3d_two_stream(int32_t n_cols, int32_t nlay, const double* tau,
                             const double* ssa, const double* g,
                             const double* albedo, double mu0,

@@ -3,8 +3,9 @@
 // C ABI declared in include/rt3d.h (rt3d_two_stream).
 //
 // One workgroup per column (a column is typically one g-point's clear-sky
-// profile, a few hundred layers); columns of more than kMaxLayers layers, one
-// lane per column.  FP64 throughout.
+// profile, a few hundred layers), or one lane per column where there are many
+// of them or they are longer than the workgroup's LDS (lane_per_column).  FP64
+// throughout.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -220,6 +221,35 @@ two_stream_column_kernel(int nlay, const double* __restrict__ tau, const double*
     }
 }
 
+// Which of the two.  A lane's sweeps take 2.3 us a layer, for up to 16384
+// columns (a wave a CU) at the same time; a workgroup's 0.21, but its 64 lanes
+// repeat one recursion: 0.12 ns a layer and column once the CUs are full, more
+// beyond 256 layers, where its LDS lets few share a CU.  From 40000 to 60000
+// columns on the lanes' columns no longer fit the caches.  Whole calls in us,
+// lane / workgroup:
+//   layers    4096 cols    8192       12288      16384      32768      49152      65536     262144
+//      4      19 / 19    19 / 19       -        19 / 29       -          -       19 / 115   94 / 441
+//     12      26 / 20    27 / 25    28 / 36     28 / 46    37 / 91    60 / 134  127 / 177  626 / 691
+//     16      36 / 19    37 / 30    38 / 42     39 / 54    55 / 105  137 / 158  239 / 209 1036 / 815
+//     24      53 / 21    54 / 39    56 / 55     58 / 71    88 / 139  212 / 206  354 / 272     -
+//     48     111 / 37   112 / 67   117 / 94    124 / 123  188 / 238  418 / 350  696 / 462     -
+//    100        -       243 / 129  251 / 188   260 / 234  361 / 451  796 / 668     -     6290 / 3457
+//    200     470 / 135  482 / 246  495 / 352   521 / 457  934 / 878 1659 / 1302 2705 / 1720   -
+//    400     935 / 317  953 / 591 1011 / 851  1081 / 1119 1934 / 2172 3302 / 3236 5409 / 4292 -
+//    500    1182 / 503 1261 / 992 1325 / 1476 1416 / 1953 2625 / 3864 4482 / 5769 6712 / 7672 31552 / 30524
+//   1024    2494 / 1864 2636 / 3699 2759 / 5535 2949 / 7359 5013 / 14671 8326 / 21982 12377 / 29235 62394 / 116449
+// A launch has fewer than 2^32 lanes: 2^25 columns and more by lanes.
+bool lane_per_column(int64_t cols, int64_t nlay) {
+    if (nlay > kMaxLayers || cols * kColumnLanes >= (int64_t)1 << 32) return true;
+    if (nlay <= 12) return cols > 8192;
+    if (nlay <= 16) return cols > 10000 && cols <= 60000;
+    if (nlay <= 24) return cols > 12288 && cols <= 49152;
+    if (nlay <= 100) return cols > 16384 && cols <= 40960;
+    if (nlay <= 352) return false;
+    if (nlay <= 400) return cols > 16384 && cols <= 32768;
+    return cols * nlay > 6000000 && (nlay > 480 || cols <= 57344);
+}
+
 }  // namespace
 
 extern "C" {
@@ -232,14 +262,14 @@ rt3d_status rt3d_two_stream(int32_t n_cols, int32_t nlay, const double* tau, con
         return RT3D_EINVAL;
     if (!(mu0 > 0.0 && mu0 <= 1.0)) return RT3D_EINVAL;
     if (tod_level < 0 || tod_level > nlay) return RT3D_EINVAL;
-    if (nlay <= kMaxLayers)
+    if (lane_per_column(n_cols, nlay))
+        hipLaunchKernelGGL(two_stream_kernel, dim3((unsigned)(((int64_t)n_cols + 63) / 64)), dim3(64), 0, (hipStream_t)stream,
+                           n_cols, nlay, tau, ssa, g, albedo, mu0, flux_toa, flux_dir, flux_dn_dif, flux_up, tod_level,
+                           tod_flux, tod_diffuse_fraction);
+    else
         hipLaunchKernelGGL(two_stream_column_kernel, dim3((unsigned)n_cols), dim3(kColumnLanes),
                            sizeof(double) * (8 * (size_t)nlay + 2), (hipStream_t)stream, nlay, tau, ssa, g, albedo, mu0,
                            flux_toa, flux_dir, flux_dn_dif, flux_up, tod_level, tod_flux, tod_diffuse_fraction);
-    else
-        hipLaunchKernelGGL(two_stream_kernel, dim3((n_cols + 63) / 64), dim3(64), 0, (hipStream_t)stream, n_cols, nlay,
-                       tau, ssa, g, albedo, mu0, flux_toa, flux_dir, flux_dn_dif, flux_up, tod_level, tod_flux,
-                       tod_diffuse_fraction);
     return hipGetLastError() == hipSuccess ? RT3D_OK : RT3D_EDEVICE;
 }
 
