@@ -2051,6 +2051,7 @@ rt3d_status merge_majorants(const Shape& s, const float* k_ext, uint32_t* majora
 }
 
 constexpr unsigned kWavePhotons = 16;  // photons a wave has at least, where there are few
+constexpr unsigned kGrabs = 2048;      // grabs of fewer than 64 photons in a launch
 
 rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     int dev = 0;
@@ -2098,7 +2099,8 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     if (blocks < 1) blocks = 1;
     if (L.o.pool_photons == 0) {
         const unsigned long long share = L.total / ((unsigned long long)blocks * (threads / 64));
-        const unsigned long long least = std::min<unsigned long long>(64, std::max<unsigned long long>(16, share));
+        const unsigned long long least =
+            std::min<unsigned long long>(64, std::max<unsigned long long>(16, std::max(share, L.total / kGrabs)));
         L.P.pool = (uint32_t)std::min<unsigned long long>(256, std::max<unsigned long long>(least, share / 64 * 16));
     }
     if (L.o.flags & RT3D_FLAG_TIME) {
