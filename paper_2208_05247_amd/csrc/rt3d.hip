@@ -2051,6 +2051,7 @@ rt3d_status merge_majorants(const Shape& s, const float* k_ext, uint32_t* majora
 }
 
 constexpr unsigned kWavePhotons = 16;  // photons a wave has at least, where there are few
+constexpr size_t kStagedPerLane = 32;  // majorants that a lane of a smaller workgroup stages in LDS, unless told to
 constexpr unsigned kGrabs = 2048;      // grabs of fewer than 64 photons in a launch
 
 rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
@@ -2061,22 +2062,10 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     const size_t maj_bytes = L.s.nmaj * sizeof(float);
     const size_t own_lds = 8 * (C_N * kCntSlots + C_N);  // the kernel's static LDS
     const size_t lds_limit = L.o.lds_majorant > 0 ? (size_t)max_lds - own_lds : kLdsMajorantBytes;
-    const bool use_lds =
-        L.ngp == 1 && L.o.lds_majorant >= 0 && maj_bytes <= lds_limit && maj_bytes + own_lds <= (size_t)max_lds;
-    const size_t lds = use_lds ? maj_bytes : 0;
-    // crossings per loop iteration: a short walk keeps the lanes of a wave
-    // in step (a long clear-sky walk of one lane would hold the others)
-    L.P.max_walk = L.o.max_walk > 0 ? L.o.max_walk : (use_lds ? 3 : 2);
-    auto pick = [&](auto tally) {
-        constexpr int kTally = decltype(tally)::value;
-        return factored ? (use_lds ? trace_kernel<true, true, kTally> : trace_kernel<false, true, kTally>)
-                        : (use_lds ? trace_kernel<true, false, kTally> : trace_kernel<false, false, kTally>);
-    };
-    auto kernel = (L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) ? pick(std::integral_constant<int, kAggregated>{})
-                                                         : pick(std::integral_constant<int, kDirect>{});
     int ncu = 0;
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    int threads = factored ? Shape_<true>::threads : Shape_<false>::threads;
+    const int most = factored ? Shape_<true>::threads : Shape_<false>::threads;
+    int threads = most;
     // Few photons: a wave per kWavePhotons of them, spread over the CUs in
     // smaller workgroups (a launch then lasts as long as its longest photon,
     // and an iteration is shorter the fewer lanes and waves share it), and
@@ -2088,6 +2077,23 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
     const unsigned long long few = (L.total + kWavePhotons - 1) / kWavePhotons;
     if (!L.o.grid_blocks && !L.o.block_threads)
         threads = (int)std::min<unsigned long long>(threads, 64 * ((few + ncu - 1) / ncu));
+    // What few lanes stage takes longer than it saves: 16384 majorants for one
+    // photon, 185 us staged by 64 lanes, 126 from the L2; 2048 majorants, 166 and
+    // 160, with 2^14 photons 232 and 233.
+    const bool use_lds = L.ngp == 1 && L.o.lds_majorant >= 0 && maj_bytes <= lds_limit &&
+                         maj_bytes + own_lds <= (size_t)max_lds &&
+                         (L.o.lds_majorant > 0 || threads == most || L.s.nmaj <= kStagedPerLane * (size_t)threads);
+    const size_t lds = use_lds ? maj_bytes : 0;
+    // crossings per loop iteration: a short walk keeps the lanes of a wave
+    // in step (a long clear-sky walk of one lane would hold the others)
+    L.P.max_walk = L.o.max_walk > 0 ? L.o.max_walk : (use_lds ? 3 : 2);
+    auto pick = [&](auto tally) {
+        constexpr int kTally = decltype(tally)::value;
+        return factored ? (use_lds ? trace_kernel<true, true, kTally> : trace_kernel<false, true, kTally>)
+                        : (use_lds ? trace_kernel<true, false, kTally> : trace_kernel<false, false, kTally>);
+    };
+    auto kernel = (L.o.flags & RT3D_FLAG_WAVE_AGGREGATE) ? pick(std::integral_constant<int, kAggregated>{})
+                                                         : pick(std::integral_constant<int, kDirect>{});
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds));
     if (per_cu < 1) per_cu = 1;
