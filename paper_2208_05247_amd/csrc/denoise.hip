@@ -2285,7 +2285,8 @@ rt3d_status wgrad_run(const rt3d_dn_conv* c, const WgradPlan& plan, const uint16
         const int nb = db ? c->cout : 0;
         // few sums: more lanes to each (55000 of 256 chunks: 2 us slower that way)
         const size_t quads = (plan.nw + nb) / 4;
-        const int width = quads < 64 * 64 ? 16 : 64;
+        int width = quads < 64 * 64 ? 16 : 64;
+        while (1024 / width > a.chunks) width *= 2;  // no lanes without a chunk
         hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((quads + width - 1) / width)), dim3(1024), 0, st, part_w,
                            dw, plan.nw, part_b, db, nb, a.chunks, width);
         DN_TRY(hipGetLastError());

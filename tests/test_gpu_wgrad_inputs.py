@@ -68,3 +68,20 @@ def test_infinities_at_the_domain_edge(D, H, W, c1, c2, cout, what):
         ok = torch.isfinite(want)
         assert torch.equal(torch.isfinite(got), ok)
         assert float((got[ok] - want[ok]).norm()) <= 1e-5 * float(want[ok].norm())
+
+
+@pytest.mark.parametrize("D,H,W,c1,c2,cout", [(1, 1, 1, 128, 0, 256), (1, 4, 32, 32, 0, 64), (3, 4, 32, 128, 0, 256),
+                                              (5, 4, 32, 16, 0, 32), (16, 4, 32, 32, 0, 32), (17, 4, 32, 32, 0, 32)])
+def test_few_partial_sums(D, H, W, c1, c2, cout):
+    """Fewer partial sums than lane groups to add them (1, 3, 5, 16, 17 chunks)."""
+    from paper_2208_05247_amd import denoise as dn
+    g = torch.Generator().manual_seed(D)
+    x = torch.randn(D, H, W, c1, generator=g).to(torch.bfloat16)
+    dz = torch.randn(D, H, W, cout, generator=g).to(torch.bfloat16)
+    rw, rb = reference(x.double(), dz.double())
+    start = torch.randn(cout, 27, c1, generator=g)
+    ws = torch.empty(dn.wgrad_workspace_size(x, None, cout, 3), dtype=torch.uint8, device="cuda")
+    dw, db = start.cuda(), torch.ones(cout, device="cuda")
+    dn.conv_wgrad(x.cuda(), None, dz.cuda(), cout, 3, dw, db, workspace=ws)
+    rel = lambda a, b: float((a.double().cpu() - b).norm() / b.norm())
+    assert rel(dw, rw + start) < 1e-5 and rel(db, rb + 1.0) < 1e-5
