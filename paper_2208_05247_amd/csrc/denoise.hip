@@ -21,6 +21,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "rt3d.h"
 #include "rt3d_denoise.h"
 
@@ -2261,13 +2263,34 @@ bool aligned16(const P*... p) {
     return ((reinterpret_cast<uintptr_t>(p) | ...) & 15) == 0;
 }
 
+// Where there is little to sum, the element kernel: a wave per tap and channel
+// tile against eight that share all taps of one, and an eighth of the sums to
+// write.  With a workspace, us, 3x3x3 kernel / elements (channel tiles):
+//   32 -> 32 (1)     16^3 18.5 / 16.6, 20^3 20.8 / 24.2
+//   32 -> 64 (2)      8^3 21.8 / 13.5, 16^3 27.4 / 23.2, 20^3 29.7 / 32.2
+//   64 -> 128 (8)     8^3 28.5 / 24.3, 12^3 32.8 / 32.3, 16^3 33.4 / 42.3
+//   128 -> 256 (32)   4x6x10 33.7 / 26.9, 8^3 41.1 / 41.8, 10^3 44.1 / 55.3
+//   384 -> 128 (48)   4x6x10 36.8 / 30.8, 8^3 41.0 / 51.1
+// Without one every sum of every chunk is an atomic, and the line lies higher:
+//   32 -> 64 (2)     32^3 108 / 57, 40^3 114 / 100, 64^3 132 / 307
+//   96 -> 32 (3)     24^3 110 / 41, 32^3 116 / 68, 40^3 121 / 142
+//   96 -> 96 (9)     16^3 95 / 36, 20^3 92 / 71, 24^3 94 / 110
+//   384 -> 128 (48)   8^3 52 / 42, 12^3 58 / 83
+bool few_voxels(double voxels, double tiles, bool workspace) {
+    if (workspace) return voxels <= 6144 && voxels * tiles <= 12288;
+    return voxels * tiles <= (tiles <= 3 ? 98304 : 65536);
+}
+
 rt3d_status wgrad_run(const rt3d_dn_conv* c, const WgradPlan& plan, const uint16_t* x1, const uint16_t* x2,
                       const uint16_t* dz, float* dw, float* db, float* part_w, float* part_b, hipStream_t st) {
     WgradArgs a = plan.a;
     a.dz = dz; a.x1 = x1; a.x2 = x2; a.dw = dw; a.db = db; a.partial = part_w; a.partial_b = part_b;
     rt3d_status r = RT3D_OK;
-    if (c->ksize == 1 || !aligned16(x1, dz) || (c->c2 && !aligned16(x2))) {
-        const long waves = (long)(c->cout / 32) * ((c->c1 + c->c2 + 31) / 32) * plan.taps * a.chunks;
+    const long tiles = (long)(c->cout / 32) * ((c->c1 + c->c2 + 31) / 32);
+    const bool few = few_voxels((double)c->D * c->H * c->W, (double)tiles, part_w != nullptr);
+    if (c->ksize == 1 || few || !aligned16(x1, dz) || (c->c2 && !aligned16(x2))) {
+        if (c->ksize == 3) a.chunks = (int)std::min<long>(a.chunks, std::max<long>(1, 4096 / (27 * tiles)));
+        const long waves = tiles * plan.taps * a.chunks;
         hipLaunchKernelGGL((c->ksize == 1 ? conv_wgrad_kernel<1> : conv_wgrad_kernel<3>), dim3((unsigned)((waves + 3) / 4)),
                            dim3(256), 0, st, a);
         DN_TRY(hipGetLastError());

@@ -85,3 +85,24 @@ def test_few_partial_sums(D, H, W, c1, c2, cout):
     dn.conv_wgrad(x.cuda(), None, dz.cuda(), cout, 3, dw, db, workspace=ws)
     rel = lambda a, b: float((a.double().cpu() - b).norm() / b.norm())
     assert rel(dw, rw + start) < 1e-5 and rel(db, rb + 1.0) < 1e-5
+
+
+@pytest.mark.parametrize("D,H,W,c1,c2,cout,workspace", [
+    (16, 16, 24, 16, 0, 32, True), (5, 1229, 1, 16, 0, 32, True), (2, 8, 16, 256, 128, 128, True), (1, 1, 257, 256, 128, 128, True),
+    (32, 32, 48, 64, 32, 32, False), (1, 127, 259, 64, 32, 32, False), (5, 13, 21, 256, 128, 128, False),
+    (1, 2, 683, 256, 128, 128, False)])
+def test_few_voxels(D, H, W, c1, c2, cout, workspace):
+    """The most voxels that the element kernel takes for a number of channel
+    tiles, with and without a workspace, and one or a few more."""
+    from paper_2208_05247_amd import denoise as dn
+    g = torch.Generator().manual_seed(D + W)
+    x = torch.randn(D, H, W, c1 + c2, generator=g).to(torch.bfloat16)
+    dz = torch.randn(D, H, W, cout, generator=g).to(torch.bfloat16)
+    rw, rb = reference(x.double(), dz.double())
+    x1 = x[..., :c1].contiguous().cuda()
+    x2 = x[..., c1:].contiguous().cuda() if c2 else None
+    ws = torch.empty(dn.wgrad_workspace_size(x1, x2, cout, 3), dtype=torch.uint8, device="cuda") if workspace else None
+    rel = lambda a, b: float((a.double().cpu() - b).norm() / b.norm())
+    dw, db = torch.zeros(cout, 27, c1 + c2, device="cuda"), torch.zeros(cout, device="cuda")
+    dn.conv_wgrad(x1, x2, dz.cuda(), cout, 3, dw, db, workspace=ws)
+    assert rel(dw, rw) < 1e-5 and rel(db, rb) < 1e-5
