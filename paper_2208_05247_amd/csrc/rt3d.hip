@@ -1176,11 +1176,12 @@ __global__ void __launch_bounds__(1024) deposit_sort_kernel(const Deposits D, in
 // Adds the deposits of one bin to the tallies: each half-wave takes the bin's
 // run of one sorted tile at a time (the run's place from the table, read for
 // 64 tiles at once), 16 tiles in flight per half-wave, and sums it in LDS;
-// the sums that are not zero are then added to the tallies: by atomics where
-// the call accumulates (`shared`), as other calls may add to the same tallies on
-// other streams meanwhile, else by this workgroup alone.  Neighbouring bins run on the same XCD, so that the
+// the sums that are not zero are then added to the tallies, by atomics (other
+// calls may accumulate into the same tallies on other streams meanwhile; and a
+// load and a store take longer: 2^26 photons on 256x256x128 cells 80.9 against
+// 80.2 ms, with a buffer of 1024 tiles 92.5 against 88.2).  Neighbouring bins run on the same XCD, so that the
 // 128-byte lines of the table are shared in its L2.
-__global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int round, uint32_t ncell, bool shared,
+__global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int round, uint32_t ncell,
                                                            unsigned long long* abs_dir, unsigned long long* abs_dif) {
     __shared__ unsigned long long s_sum[2 * kBinCells];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1245,12 +1246,8 @@ __global__ void __launch_bounds__(1024) deposit_add_kernel(const Deposits D, int
     for (uint32_t i = tid; i < kBinCells; i += 1024) {
         const size_t cell = (size_t)bin * kBinCells + i;
         if (cell >= ncell) break;
-        auto add = [&](unsigned long long* tally, unsigned long long v) {
-            if (v && shared) atomicAdd(&tally[cell], v);
-            else if (v) tally[cell] += v;
-        };
-        add(abs_dir, s_sum[i]);  // (may be one array, as with the atomics)
-        add(abs_dif, s_sum[kBinCells + i]);
+        if (s_sum[i]) atomicAdd(&abs_dir[cell], s_sum[i]);
+        if (s_sum[kBinCells + i]) atomicAdd(&abs_dif[cell], s_sum[kBinCells + i]);
     }
 }
 
@@ -2129,7 +2126,7 @@ rt3d_status launch_trace(Launch& L, bool factored, hipStream_t st) {
             hipLaunchKernelGGL(deposit_sort_kernel, dim3(std::min<unsigned>(D.ntiles, (unsigned)ncu)), dim3(1024), 0, st, D, r);
             HIP_TRY(hipGetLastError());
             hipLaunchKernelGGL(deposit_add_kernel, dim3((D.nbins + 7) / 8 * 8), dim3(1024), 0, st, D, r,
-                               (uint32_t)L.s.ncell, (L.o.flags & RT3D_FLAG_ACCUMULATE) != 0, L.P.abs_dir, L.P.abs_dif);
+                               (uint32_t)L.s.ncell, L.P.abs_dir, L.P.abs_dif);
             HIP_TRY(hipGetLastError());
         }
     } else {
