@@ -289,9 +289,10 @@ void rt3d_default_options(rt3d_options* opt);
 /* Bytes of device workspace rt3d_trace needs for this grid and options
  * (majorant grid, work-queue counter and flags).  Returns 0 on bad input.
  * What a workspace holds beyond that, rt3d_trace uses as a buffer for heating
- * deposits, where it is large enough for that (about 90 MB; 1 GiB is ample)
- * and the call has 2^22 photons or more on more than 2^20 - 2^13 and at most
- * 2^24 cells: the tallies are the same, and fewer of their updates are atomics. */
+ * deposits, where it is large enough for that (about 180 MB, 450 MB beyond 1.05e7
+ * cells; eight times the workspace is ample) and the call has 2^22 photons or
+ * more (2^23 beyond 1.05e7 cells) on more than 2^20 - 2^13 and at most 2^24
+ * cells: the tallies are the same, and fewer of their updates are atomics. */
 size_t rt3d_workspace_size(const rt3d_grid* grid, const rt3d_options* opt);
 
 /* The deposit buffer of a rt3d_trace call with this workspace whose tracing

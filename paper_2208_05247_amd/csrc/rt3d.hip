@@ -1777,36 +1777,48 @@ void schedule_of(const Shape& s, int ngp, const uint64_t* photons, const rt3d_op
 }
 
 // The deposit buffer in the part of the workspace behind the sections above,
-// or false where there is no room for it or no use: at least kMinTiles tiles,
-// kMinBins to kMaxBins bins, kMinPhotons photons, one g-point.  Whole calls in
-// ms, atomics against the buffer (buffer of eight workspaces):
-//     cells (bins)          2^22 photons   2^23          2^24          2^26
-//   64x64x64 (32)            8.2 /  8.7   15.0 / 14.6   28.6 / 28.7
-//   90x66x50 (37), 6e6 photons 8.6 / 11.3: few workgroups add unlike bins
-//   64x64x128 (64)           8.5 /  8.3   15.9 / 15.3   30.5 / 29.1
-//   128x64x128 (128)         8.4 /  7.8   15.3 / 14.1   28.9 / 26.1
-//   128x128x128 (256)        7.3 /  6.2   13.4 / 11.0   25.2 / 20.0
-//   256x128x128 (512)        7.5 /  6.8   13.8 / 14.1   25.6 / 21.5
-//   256x256x128 (1024)       7.7 /  6.8   14.0 / 12.4   26.4 / 22.0   101 / 81.4
-// Of the 81.4 ms the sort takes 13.4 (2.5 TB/s) and the addition 13.1.  The
-// kernel for several g-points, slower itself, gained at most 2 % (128^3 cells,
-// 112 g-points, 3.4e7 photons: 38.3 / 37.4 ms) and lost up to 4 % below 8e6
-// photons, so it keeps the atomics.
-constexpr uint32_t kMinTiles = 256;
+// or false where there is no room for it or no use: one g-point, 128 to 2048
+// bins, and enough tiles and photons (a round costs its three launches, the
+// lanes' states written and read, and a pass over the tallies).  Whole calls in
+// ms on a cumulus field, 16-byte records of 256x256x128 cells being 134 MB:
+//                             atomics   buffer of 256 tiles  512   1024   2048   4096   8192
+//   128x64x128   (128)  2^22     8.36       11.0   8.6    7.4    7.2    7.3    7.3
+//                       2^26   110.5       158.6 113.4   90.5   92.1   92.3   92.9
+//   128x128x128  (256)  2^22     7.37        8.9   7.4    6.3    6.2    6.3    6.1
+//                       2^26    95.8       120.7  90.2   74.4   74.6   72.5   70.9
+//   256x128x128  (512)  2^22     7.60       11.5   7.8    6.9    6.8    6.7    6.7
+//                       2^23    13.76       18.3  14.6   12.1   12.0   11.9   12.4
+//   256x256x128 (1024)  2^22     7.77       10.2   8.3    7.2    7.0    6.8    6.8
+//                       2^26   100.7       140.0 103.9   88.2   84.4   81.5   80.2
+//   256x256x160 (1280)  2^22     8.20         -     -     7.9    7.6    7.6     -
+//                       2^24    27.8          -     -    26.0   25.0   24.4     -
+//   256x256x256 (2048)  2^22     8.94       13.2  10.8    9.5    9.4    9.1    9.1
+//                       2^23    16.1        24.9  19.4   16.9   16.1   15.9   15.7
+//                       2^26   115.4       190.5 141.9  120.0  114.0  109.7  108.4
+// Fewer bins (tiles of eight workspaces, before the last changes): 64x64x64 (32
+// bins) 8.2 / 8.7 at 2^22 photons, 28.6 / 28.7 at 2^24; 90x66x50 (37), 6e6
+// photons 8.6 / 11.3: few workgroups add unlike bins.  Of the 80 ms at 2^26
+// photons on 256x256x128 cells the sort takes 13 (2.5 TB/s) and the addition 13.
+// The kernel for several g-points, slower itself, gained at most 2 % (128^3
+// cells, 112 g-points, 3.4e7 photons: 38.3 / 37.4 ms) and lost up to 4 % below
+// 8e6 photons, so it keeps the atomics.
 constexpr size_t kMinBins = 128;
-constexpr unsigned long long kMinPhotons = 1ull << 22;
+constexpr size_t kFewBins = 1280;
+
+unsigned long long min_photons(size_t nbins) { return 1ull << (nbins <= kFewBins ? 22 : 23); }
+size_t min_tiles(size_t nbins) { return nbins <= kFewBins ? 1024 : 3072; }
 
 bool deposit_buffer(const Shape& s, unsigned long long photons, char* at, size_t bytes, uint32_t nlanes,
                     Deposits* D) {
     const size_t nbins = (s.ncell + kBinCells - 1) / kBinCells;
-    if (nbins < kMinBins || nbins > kMaxBins || photons < kMinPhotons) return false;
+    if (nbins < kMinBins || nbins > kMaxBins || photons < min_photons(nbins)) return false;
     D->nbins = (uint32_t)nbins;
     D->nlanes = nlanes;
     D->nwaves = nlanes / 64;
     const size_t fixed = 2 * kTileChunks * 128 + align256(24 * (size_t)D->nwaves) +
                          align256(4 * (size_t)kLaneWords * nlanes);
     const size_t per_tile = 8 * (size_t)kTileDeposits + 4 * kTileChunks + 2 * (nbins + 1);
-    if (bytes < fixed + 1024 + kMinTiles * per_tile) return false;
+    if (bytes < fixed + 1024 + min_tiles(nbins) * per_tile) return false;
     D->ntiles = (uint32_t)std::min<size_t>((bytes - fixed - 1024) / per_tile, 1u << 20);
     D->item = (uint2*)at;
     at += 8 * (size_t)kTileDeposits * D->ntiles;

@@ -233,7 +233,7 @@ def workspace_size(grid, opt: Options) -> int:
         raise Rt3dError(EINVAL, "rt3d_workspace_size")
     size = _WorkspaceBytes(n)
     if grid.nx * grid.ny * grid.nz <= DEPOSIT_BUFFER_CELLS:
-        size.spare = max(8 * size, 128 << 20)
+        size.spare = max(8 * size, 192 << 20)
     return size
 
 
@@ -257,7 +257,7 @@ def alloc_tallies(grid, device="cuda") -> dict:
 def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
     """A workspace of nbytes, 256-byte aligned.  For a size that came from
     workspace_size it is larger by a deposit buffer (eight times the size, at
-    least 128 MiB, for grids of up to DEPOSIT_BUFFER_CELLS; left out where
+    least 192 MiB, for grids of up to DEPOSIT_BUFFER_CELLS; left out where
     memory is short): with many photons rt3d_trace collects heating deposits
     there instead of adding each to its tally by an atomic (same results)."""
     spare = getattr(nbytes, "spare", 0)

@@ -13,7 +13,7 @@ TILE = 16384 * 8  # bytes of deposits
 def spare_for(grid, opt, photons, lanes, tiles, start=32 << 20):
     """Smallest workspace surplus (to 256 bytes) that holds `tiles` tiles."""
     n = int(r.workspace_size(grid, opt))
-    lo, hi = start, (tiles + 8) * (TILE + 8192) + lanes * 128 + (1 << 20)
+    lo, hi = start, (max(tiles, 4096) + 8) * (TILE + 8192) + lanes * 128 + (1 << 20)
     assert r.deposit_plan(grid, opt, photons, n + hi, lanes)["tiles"] >= tiles
     while hi - lo > 256:
         mid = (lo + hi) // 2
@@ -33,8 +33,8 @@ def test_reads_stay_inside_the_deposits(shape, brick, lanes):
     n = int(r.workspace_size(grid, opt))
     seen = set()
     for tiles in (4096, 4097, 4127, 4159, 4160, 4161):
-        size = n + spare_for(grid, opt, 1 << 22, lanes, tiles)
-        plan = r.deposit_plan(grid, opt, 1 << 22, size, lanes)
+        size = n + spare_for(grid, opt, 1 << 23, lanes, tiles)
+        plan = r.deposit_plan(grid, opt, 1 << 23, size, lanes)
         assert plan["tiles"] == tiles and plan["bins"] == -(-grid.nx * grid.ny * grid.nz // 8192)
         assert plan["end"] == n + tiles * TILE
         assert plan["read_end"] <= plan["end"], (tiles, plan["read_end"] - plan["end"])
@@ -56,3 +56,16 @@ def test_calls_without_a_buffer():
     for bad in ((n - 1, 768), (n, 0), (n, 100)):
         with pytest.raises(r.Rt3dError):
             r.deposit_plan(grid, opt, 1 << 22, *bad)
+
+
+def test_least_buffer():
+    """The fewest tiles and photons that the buffer is used for, and one less."""
+    for shape, tiles, photons in (((128, 64, 128), 1024, 1 << 22), ((256, 256, 160), 1024, 1 << 22),
+                                  ((256, 256, 168), 3072, 1 << 23)):
+        grid, lanes = Grid(*shape, 50.0, 40.0, 30.0), 512 * 768
+        opt = r.options()
+        n = int(r.workspace_size(grid, opt))
+        spare = spare_for(grid, opt, photons, lanes, 1)
+        assert r.deposit_plan(grid, opt, photons, n + spare, lanes)["tiles"] == tiles
+        assert r.deposit_plan(grid, opt, photons, n + spare - 256, lanes)["tiles"] == 0
+        assert r.deposit_plan(grid, opt, photons - 1, n + spare, lanes)["tiles"] == 0

@@ -49,7 +49,7 @@ def same(a, b):
 
 
 @pytest.mark.parametrize("shape,brick", [((128, 64, 128), (8, 8, 8)), ((104, 100, 104), (8, 4, 8))])
-@pytest.mark.parametrize("groups,tiles", [(7, 321), (32, 513)])
+@pytest.mark.parametrize("groups,tiles", [(7, 1025), (32, 1089)])
 def test_few_workgroups(shape, brick, groups, tiles):
     df = fields(shape)
     photons = (1 << 22) + 5
@@ -76,7 +76,7 @@ def test_calls_that_overlap_add_to_the_same_tallies():
     df, brick, n = fields((128, 64, 128)), (8, 8, 8), 1 << 23
     kw = dict(brick=brick, diffuse_fraction=0.1, accumulate=True)
     ref = r.trace(df, 35.0, 20.0, 2 * n, 7, workspace=plain(df, brick), out=zeroed(df), **kw)
-    spaces = [buffered(df, brick, 128 << 20) for _ in range(2)]
+    spaces = [buffered(df, brick, 192 << 20) for _ in range(2)]
     streams = [torch.cuda.Stream() for _ in range(2)]
     out = zeroed(df)
     torch.cuda.synchronize()
@@ -116,7 +116,7 @@ def test_one_array_for_direct_and_diffuse_heating():
     out = r.alloc_tallies(df.grid)
     out["abs_dif"] = out["abs_dir"]
     for accumulate in (False, True):
-        ws = buffered(df, brick, 128 << 20)
+        ws = buffered(df, brick, 192 << 20)
         r.trace(df, 35.0, 20.0, n, 7, workspace=ws, out=out, accumulate=accumulate, **kw)
         assert used(df, brick, ws)
         assert torch.equal(out["abs_dir"], (ref["abs_dir"] + ref["abs_dif"]) * (2 if accumulate else 1))
