@@ -223,8 +223,10 @@ class _WorkspaceBytes(int):
     spare = 0
 
 
-# largest grid whose deposits the tracer collects in a buffer
-DEPOSIT_BUFFER_CELLS = 2048 << 13
+# grids (cells: more than the first, up to the second) and photons for which the
+# tracer collects deposits in a buffer
+DEPOSIT_BUFFER_CELLS = (127 << 13, 2048 << 13)
+DEPOSIT_BUFFER_PHOTONS = 1 << 22
 
 
 def workspace_size(grid, opt: Options) -> int:
@@ -232,7 +234,7 @@ def workspace_size(grid, opt: Options) -> int:
     if n == 0:
         raise Rt3dError(EINVAL, "rt3d_workspace_size")
     size = _WorkspaceBytes(n)
-    if grid.nx * grid.ny * grid.nz <= DEPOSIT_BUFFER_CELLS:
+    if DEPOSIT_BUFFER_CELLS[0] < grid.nx * grid.ny * grid.nz <= DEPOSIT_BUFFER_CELLS[1]:
         size.spare = max(8 * size, 192 << 20)
     return size
 
@@ -257,7 +259,7 @@ def alloc_tallies(grid, device="cuda") -> dict:
 def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
     """A workspace of nbytes, 256-byte aligned.  For a size that came from
     workspace_size it is larger by a deposit buffer (eight times the size, at
-    least 192 MiB, for grids of up to DEPOSIT_BUFFER_CELLS; left out where
+    least 192 MiB, for grids within DEPOSIT_BUFFER_CELLS; left out where
     memory is short): with many photons rt3d_trace collects heating deposits
     there instead of adding each to its tally by an atomic (same results)."""
     spare = getattr(nbytes, "spare", 0)
@@ -268,6 +270,12 @@ def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
         ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
     off = (-ws.data_ptr()) % 256
     return ws[off:off + nbytes + spare]
+
+
+def _bytes_for(size: int, photons: int, wave_aggregate: bool) -> int:
+    """The workspace of one call: without the deposit buffer where the call has
+    no use for it."""
+    return int(size) if photons < DEPOSIT_BUFFER_PHOTONS or wave_aggregate else size
 
 
 def tallies_struct(t: dict) -> TalliesStruct:
@@ -297,7 +305,7 @@ def trace(df: DeviceFields, sza: float, azimuth: float, photons: int, seed: int,
     gs = grid_struct(grid)
     nws = workspace_size(grid, opt)
     if workspace is None:
-        workspace = alloc_workspace(nws, df.k_ext.device)
+        workspace = alloc_workspace(_bytes_for(nws, photons, wave_aggregate), df.k_ext.device)
     if out is None:
         out = alloc_tallies(grid, df.k_ext.device)
     props = OpticalProps(df.k_ext.data_ptr(), df.k_ext_cloud.data_ptr(), df.ssa.data_ptr(), df.g.data_ptr())
