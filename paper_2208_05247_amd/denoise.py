@@ -100,10 +100,14 @@ def load():
     return lib
 
 
-EXPORTS = ("rt3d_dn_last_error", "rt3d_dn_conv3d_fwd", "rt3d_dn_conv3d_fwd_head", "rt3d_dn_flip_weights", "rt3d_dn_conv3d_wgrad",
+EXPORTS = ("rt3d_dn_last_error", "rt3d_dn_conv3d_fwd", "rt3d_dn_conv_workspace_size", "rt3d_dn_conv3d_fwd_ws",
+           "rt3d_dn_conv3d_dgrad", "rt3d_dn_conv3d_fwd_head", "rt3d_dn_conv3d_fwd_head_ws", "rt3d_dn_conv3d_fwd_pool",
+           "rt3d_dn_conv3d_fwd_pool_w", "rt3d_dn_flip_weights", "rt3d_dn_conv3d_wgrad",
            "rt3d_dn_conv3d_wgrad_ws", "rt3d_dn_wgrad_workspace_size",
-           "rt3d_dn_relu_bwd", "rt3d_dn_add", "rt3d_dn_pool2", "rt3d_dn_up2", "rt3d_dn_mse", "rt3d_dn_adam",
-           "rt3d_dn_to_bf16", "rt3d_dn_features", "rt3d_dn_unfeature")
+           "rt3d_dn_relu_bwd", "rt3d_dn_add", "rt3d_dn_pool2", "rt3d_dn_up2", "rt3d_dn_up2_relu_bwd",
+           "rt3d_dn_pool2_add_relu_bwd", "rt3d_dn_mse", "rt3d_dn_adam", "rt3d_dn_to_bf16", "rt3d_dn_features",
+           "rt3d_dn_features_at", "rt3d_dn_direct_feature", "rt3d_dn_field_scale", "rt3d_dn_residual_unfeature",
+           "rt3d_dn_residual_unfeature_at", "rt3d_dn_unfeature")
 
 
 def _p(t: Optional[torch.Tensor]):
