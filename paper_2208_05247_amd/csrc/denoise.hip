@@ -1929,10 +1929,14 @@ __global__ void field_scale_kernel(const double* __restrict__ partial, size_t n,
 
 // a * b rounded to FP32 on its own: the library is built with FP contraction,
 // which would otherwise fuse it with a following addition into one FMA (and
-// the backend does so even where the source forbids it)
+// the backend does so even where the source forbids it).  The empty asm hides
+// where the addend comes from.  (Not a multiplication in asm: the compiler knows
+// no hazards there, and one right behind a v_rcp_f32 whose result it takes reads
+// the register before it is written; here the scale's reciprocal is formed on
+// the device.)
 __device__ __forceinline__ float mul_rounded(float a, float b) {
-    float r;
-    asm("v_mul_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    float r = a * b;
+    asm("" : "+v"(r));
     return r;
 }
 
