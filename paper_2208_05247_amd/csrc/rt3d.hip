@@ -629,6 +629,10 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     uint32_t chunk = kNoChunk, chunk_pos = kChunk;
     bool full = false, suspended = false, resumed = false;
 
+    auto uniform = [](unsigned long long v) {
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+               (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+    };
     // every word of a lane's state that lives from one round to the next
     auto each_word = [&](auto&& f) {
         uint32_t lo = (uint32_t)id, hi = (uint32_t)(id >> 32), fl = (uint32_t)st | (direct ? 256u : 0u);
@@ -655,10 +659,6 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
     if (kTally == kBinned && P.round && !drained) {
         const Deposits& D = cold_params()->dep;
         each_word([&](int n, uint32_t& v) { v = D.lanes[(size_t)n * D.nlanes + lane_ix]; });
-        auto uniform = [](unsigned long long v) {
-            return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
-                   (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-        };
         pool_next = uniform(D.waves[wave]);
         pool_end = uniform(D.waves[D.nwaves + wave]);
         drained = pool_next >= cold_params()->photons;
@@ -718,8 +718,13 @@ __global__ void __launch_bounds__(Shape_<kFactored>::threads)
                     // no new photons come, the few deposits left are added by
                     // atomics (the longest photons' time is spent once then)
                     full = true;
-                    const unsigned long long handed_out =
-                        __hip_atomic_load(cold_params()->queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    // (one lane's load for all: read 16 lanes at a time, the
+                    // counter may pass the photons in between, and the wave's
+                    // lanes must not part here)
+                    unsigned long long handed_out = 0;
+                    if (__lane_id() == 0)
+                        handed_out = __hip_atomic_load(cold_params()->queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    handed_out = uniform(handed_out);
                     if (!cold_params()->last_round && handed_out < cold_params()->photons) {
                         suspended = true;
                         break;
