@@ -8,6 +8,7 @@ uint64 tallies are held in torch.int64 tensors (same bits); use
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import dataclasses
 import os
@@ -272,6 +273,12 @@ def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
     return ws[off:off + nbytes + spare]
 
 
+def _on(stream):
+    """The stream that a call's own workspace is allocated on: the one that the
+    call runs on, as it is given back when the call returns."""
+    return torch.cuda.stream(stream) if isinstance(stream, torch.cuda.Stream) else contextlib.nullcontext()
+
+
 def _bytes_for(size: int, photons: int, wave_aggregate: bool) -> int:
     """The workspace of one call: without the deposit buffer where the call has
     no use for it."""
@@ -305,7 +312,8 @@ def trace(df: DeviceFields, sza: float, azimuth: float, photons: int, seed: int,
     gs = grid_struct(grid)
     nws = workspace_size(grid, opt)
     if workspace is None:
-        workspace = alloc_workspace(_bytes_for(nws, photons, wave_aggregate), df.k_ext.device)
+        with _on(stream):
+            workspace = alloc_workspace(_bytes_for(nws, photons, wave_aggregate), df.k_ext.device)
     if out is None:
         out = alloc_tallies(grid, df.k_ext.device)
     props = OpticalProps(df.k_ext.data_ptr(), df.k_ext_cloud.data_ptr(), df.ssa.data_ptr(), df.g.data_ptr())
@@ -407,7 +415,8 @@ def trace_batched(dm: DeviceBatchedMedium, sza: float, azimuth: float, photons: 
     gs = grid_struct(grid)
     nws = workspace_size_batched(grid, ngp, opt)
     if workspace is None:
-        workspace = alloc_workspace(nws, dm.k_cloud.device)
+        with _on(stream):
+            workspace = alloc_workspace(nws, dm.k_cloud.device)
     if out is None:
         out = alloc_tallies(grid, dm.k_cloud.device)
     med = BatchedMedium(dm.k_gas.data_ptr(), dm.ssa_gas.data_ptr(), dm.k_cloud.data_ptr(),
