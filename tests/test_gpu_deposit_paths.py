@@ -1,8 +1,9 @@
 """Traces through the deposit buffer on grids that it is used for (128 bins and
-more), with few workgroups and tile counts one past a multiple of the 64 tiles
-that the addition takes at a time: tallies bit for bit those of the plain
-workspace.  All sums are of integers, so equality is exact.  Each case checks
-that the buffer was taken: the surplus of its workspace has been written."""
+more): every option, the fewest tiles, few workgroups with tile counts one past
+a multiple of the 64 tiles that the addition takes at a time, calls that
+overlap, a graph.  Tallies bit for bit those of the plain workspace; all sums are
+of integers, so equality is exact.  Each case checks that the buffer was taken:
+the surplus of its workspace has been written."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -132,3 +133,66 @@ def test_majorants_that_fill_the_lds():
     got = r.trace(df, 35.0, 20.0, n, 7, workspace=ws, **kw)
     same(got, ref)
     assert used(df, brick, ws)
+
+
+# 128 bins, 129 with a ragged last one, 1344 (beyond the line of 1280)
+@pytest.mark.parametrize("shape,brick,photons", [((128, 64, 128), (8, 8, 8), (1 << 22) + 12345),
+                                                 ((110, 99, 97), (5, 3, 1), (1 << 22) + 1), ((256, 256, 168), (8, 8, 8), 1 << 23)])
+@pytest.mark.parametrize("kw", [dict(), dict(merge=False), dict(lds_majorant=-1), dict(sobol_entry=True, photon_offset=77),
+                                dict(pool_photons=64, refill_lanes=64, max_walk=1)], ids=lambda k: "-".join(k) or "plain")
+def test_options_through_the_buffer(shape, brick, photons, kw):
+    """Every option of a trace, with the fewest tiles, one more, and many; then
+    added to what is there."""
+    df = fields(shape)
+    opt = r.options(brick=brick)
+    kw = dict(kw, brick=brick, diffuse_fraction=0.2)
+    ref = r.trace(df, 35.0, 20.0, photons, 7, workspace=plain(df, brick), **kw)
+    least = spare_for(df.grid, opt, photons, 512 * LANES, 1)
+    for spare in (least, least + 140000, 8 * least):
+        print("options case", shape, photons, spare, flush=True)
+        ws = buffered(df, brick, spare)
+        got = r.trace(df, 35.0, 20.0, photons, 7, workspace=ws, **kw)
+        same(got, ref)
+        assert used(df, brick, ws)
+    more = dict(kw, photon_offset=photons + 1000)
+    r.trace(df, 35.0, 20.0, photons, 8, workspace=plain(df, brick), out=ref, accumulate=True, **more)
+    r.trace(df, 35.0, 20.0, photons, 8, workspace=ws, out=got, accumulate=True, **more)
+    same(got, ref)
+
+
+def test_capped_photons_and_sums_beyond_32_bits():
+    """Photons stopped by max_iters while the buffer fills several times, and cells
+    whose sum in one round passes 32 bits."""
+    grid, brick, n = syn.Grid(128, 64, 128, 50.0, 50.0, 50.0), (8, 8, 8), 1 << 24
+    df = r.DeviceFields.from_host(syn.uniform_fields(grid, 0.02, 0.01, 0.3, 0.5, 0.3))
+    kw = dict(brick=brick, max_iters=9, rr_threshold=0.05)
+    spare = spare_for(grid, r.options(brick=brick), n, 512 * LANES, 1)
+    ref = r.trace(df, 10.0, 0.0, n, 5, workspace=plain(df, brick), **kw)
+    ws = buffered(df, brick, spare)
+    got = r.trace(df, 10.0, 0.0, n, 5, workspace=ws, **kw)
+    same(got, ref)
+    assert used(df, brick, ws)
+    assert int(ref["stats"][r.STATS.index("capped")]) > 0
+    assert int(ref["abs_dir"].max()) > 1 << 36 and int((ref["abs_dir"] + ref["abs_dif"]).sum() >> 31) > 0
+
+
+def test_captured_in_a_graph():
+    """The rounds recorded in a graph: each replay is the eager call, whatever the
+    workspace and the outputs hold and the device does in between."""
+    df, brick, n = fields((128, 64, 128)), (8, 8, 8), 1 << 22
+    kw = dict(brick=brick, diffuse_fraction=0.1)
+    ref = r.trace(df, 35.0, 20.0, n, 7, workspace=plain(df, brick), **kw)
+    ws, out = buffered(df, brick, 256 << 20), r.alloc_tallies(df.grid)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        r.trace(df, 35.0, 20.0, n, 7, workspace=ws, out=out, **kw)
+    out.pop("photons")
+    for k in range(4):
+        ws.fill_(0xff if k & 1 else 0)
+        for v in out.values():
+            v.fill_(k)
+        graph.replay()
+        same(out, ref)
+        other = r.trace(df, 35.0, 20.0, 1 << 16, 9, workspace=plain(df, brick), **kw)
+        assert int(other["stats"][0]) == 1 << 16
