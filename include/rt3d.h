@@ -220,9 +220,13 @@ typedef struct {
                                 RT3D_LEDGER_LOST.  0 = default (1<<24) */
     uint64_t photon_offset;  /* first photon id of this call (chunked runs) */
     int32_t grid_blocks;     /* persistent workgroups, 0 = automatic */
-    int32_t block_threads;   /* threads per workgroup, 0 = automatic */
-    int32_t lds_majorant;    /* stage the majorant grid in LDS: 0 = automatic,
-                                1 = when it fits, -1 = never */
+    int32_t block_threads;   /* 0 = automatic; 1024 (rt3d_trace), 256 (batched):
+                                workgroups of the kernel's full size (768, 256
+                                threads) also where there are few photons;
+                                other values: RT3D_EINVAL */
+    int32_t lds_majorant;    /* stage the majorant grid in LDS: 0 = automatic
+                                (64 KiB at most, less in the small workgroups
+                                of few photons), 1 = when it fits, -1 = never */
     int32_t max_walk;        /* acceleration-grid crossings a lane makes per
                                 loop iteration before the wave re-converges;
                                 0 = automatic (3 with LDS majorants, else 2) */
@@ -469,8 +473,8 @@ rt3d_status rt3d_turn(const float* dir_in, const float* mu, const float* t, floa
  * Weaver 1980, Table 1) gamma1 = (8 - w(5 + 3g))/4, gamma2 = 3w(1 - g)/4,
  * gamma3 = (2 - 3 mu0 g)/4, gamma4 = 1 - gamma3; homogeneous layers combined
  * by the adding method; Lambertian surface with one albedo; near the
- * resonance k mu0 = 1 (|1 - k^2 mu0^2| < 1e-3) the direct-beam terms of a
- * layer are the mean of their values at mu0 (1 -+ 1e-3).
+ * resonance k mu0 = 1 (|1 - k^2 mu0^2| < 1e-5) the direct-beam terms of a
+ * layer are the mean of their values at mu0 (1 -+ 1e-5).
  * n_cols independent columns (e.g. the g-points of a spectral set) of nlay
  * layers, layer 0 at the top of the atmosphere; all arrays DEVICE FP64:
  *   tau, ssa, g      [n_cols][nlay] optical depth, single-scattering albedo,

@@ -1038,7 +1038,7 @@ struct WgradArgs {
 // accumulation registers, the compiler moved them around every MFMA.  With
 // operands gathered from global memory by 2-byte loads, a wave per (32 x 32
 // channels, tap), 3.8 and 1.0 ms (32 -> 64 channels on 64x60x52 voxels, whole
-// call: 394 us, then 70, now 55).
+// call: 394 us, then 70, now 56).
 template <int NCO, int NCI, int TY>
 struct WgradTile {
     static constexpr int kRows = TY + 2;
@@ -1977,10 +1977,6 @@ __global__ void unfeature_kernel(const float* __restrict__ pred, float scale, si
 // ===========================================================================
 namespace {
 
-// Packing (5 us beside other launches) pays from about 27 G multiply-adds on:
-// 384 -> 128 channels on 32^3 (43 G) 160 -> 146 us; at 192 -> 64 on 20x28x36
-// (6.7 G) 75 -> 70.  Up to 32 inputs the two chunks of a tap lie in the same
-// 64 bytes and little is fetched twice (32 -> 64 on 20x28x36: 18 us either way).
 // Packing (3 to 5 us) pays where the wave loads less than half of a cache line
 // of each row: 384 -> 128 channels on 10x14x18 93 us without (2 rows, 1
 // plane), 55 with.  Up to 32 inputs a tap's two chunks lie in the same 64
