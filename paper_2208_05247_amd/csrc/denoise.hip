@@ -2036,14 +2036,14 @@ double rounds_of(long groups) {
     return (double)(groups / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.6 : 1.0);
 }
 
-// Weights that are not packed bound the smaller tiles, which load them more
-// often: the large ones for 64 channels from 129 workgroups on.  Large / (2, 2):
+// Weights that could be packed and are not bound the smaller tiles, which load
+// them more often: the large ones for 64 channels from 129 workgroups on.  Large / (2, 2):
 //   128 -> 256 on 28x32x64  448 workgroups  100 / 130 us    8x32x64 (128)  44 / 40
 //   384 -> 128 on 18x32x64  144             123 / 183      12x32x64  (96) 121 / 105
 //   192 -> 64 on 40x64x96   480             155 / 200       8x64x128 (128) 66 / 59
 template <int NCT>
 rt3d_status conv3_run(const ConvArgs& a, hipStream_t st) {
-    const bool natural = a.w_row == 54 * (a.c1 + a.c2);
+    const bool natural = a.c1 + a.c2 >= kPackInputs && a.w_row == 54 * (a.c1 + a.c2);
     const long groups = conv3_groups<NCT, 4, 2>(a);
     if (groups >= (NCT == 2 && natural ? 129 : 512)) {
         if constexpr (NCT == 2)
